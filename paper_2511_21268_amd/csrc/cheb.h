@@ -27,6 +27,33 @@ namespace amgk {
 //                                of the smoothed iterate in r)
 // x is read by every row (gathered); u, r and dn are per-row, and dn never
 // aliases x (the directions ping-pong between two buffers).
+template <int MODE> struct ChebRow {
+    double xr, fr, di, ur;   // fr: f, or the running residual
+    __device__ __forceinline__ void load(int64_t row, const double *__restrict__ x, const double *__restrict__ f,
+                                         const double *__restrict__ r, const double *__restrict__ invd,
+                                         const double *__restrict__ u, int first)
+    {
+        fr = (MODE == 0 || first) ? f[row] : r[row];
+        if (MODE != 2) di = invd[row];
+        if (MODE != 0) {
+            xr = x[row];
+            if (!first) ur = u[row];
+        }
+    }
+    __device__ __forceinline__ void finish(int64_t row, double acc, double *__restrict__ r, double *__restrict__ u,
+                                           double *__restrict__ dn, double a, double b, int first) const
+    {
+        const double rr = fr - acc;
+        r[row] = rr;
+        if (MODE == 0) {
+            dn[row] = b * (di * rr);
+        } else {
+            u[row] = first ? xr : ur + xr;
+            if (MODE == 1) dn[row] = a * xr + b * (di * rr);
+        }
+    }
+};
+
 template <typename IT, int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sell_cheb(
     const Sell<double, IT> A, const double *__restrict__ x, const double *__restrict__ f, double *__restrict__ r,
@@ -43,17 +70,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         for (int t = 0; t < 8; t++) acc = fma(v[t], ld32(x, c[t]), acc);
     });
     if (row < 0) return;
-    if (MODE == 0) {
-        const double rr = f[row] - acc;
-        r[row] = rr;
-        dn[row] = b * (invd[row] * rr);
-    } else {
-        const double dold = x[row];
-        u[row] = first ? dold : u[row] + dold;
-        const double rr = (first ? f[row] : r[row]) - acc;
-        r[row] = rr;
-        if (MODE == 1) dn[row] = a * dold + b * (invd[row] * rr);
-    }
+    ChebRow<MODE> ops;
+    ops.load(row, x, f, r, invd, u, first);
+    ops.finish(row, acc, r, u, dn, a, b, first);
 }
 
 // ---- CSR with LPR lanes per row ---------------------------------------------
@@ -161,7 +180,7 @@ __device__ inline void cg_sum2(double &a, double &b, double *lds /* 2 * CG_WAVES
 // workgroup; vectors in LDS; the matrix (CSR, int32) is read from global
 // memory (L2-resident at these sizes), one wavefront per row.  Every scalar is
 // formed identically in all threads, so the loop exits uniformly.
-__global__ __launch_bounds__(CG_THREADS) void k_coarse_cg(int n, const int32_t *__restrict__ rp,
+static __global__ __launch_bounds__(CG_THREADS) void k_coarse_cg(int n, const int32_t *__restrict__ rp,
                                                           const int32_t *__restrict__ ci,
                                                           const double *__restrict__ v,
                                                           const double *__restrict__ dj,

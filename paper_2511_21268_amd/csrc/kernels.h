@@ -175,6 +175,8 @@ template <typename VT, typename IT> struct Sell {
     const int32_t *wgtab;   // window stages shared by the four waves of a block
     const int32_t *wgst;    // (layout in host.h: WgStages); nullptr: none
     int xwin;               // k_sell walks the slices with run tables through x windows
+    const int32_t *gcol;    // 16-bit deltas: column before each group of 8 entries, per slot
+                            // (parallel to idx / 8; images of split.h only)
 
     // row held by slot q, or -1
     __device__ __forceinline__ int64_t row_of(int64_t q) const
@@ -434,6 +436,43 @@ __device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane((int)(th
 // VT: matrix, x and invd type; FT: type of f; OT: type of y; IT: index stream
 // (uint16_t deltas or int32_t columns).  NDOT dots are accumulated in FP64 and
 // written as one partial per block to partial[blockIdx.x * 2 + d].
+// What one row's epilogue reads, and its result from the row sum.
+template <typename VT, typename FT, int EPI, int NDOT> struct RowOps {
+    VT xr, di;
+    FT fr;
+    double g0, g1;
+    __device__ __forceinline__ void load(int64_t row, const VT *__restrict__ x, const FT *__restrict__ f,
+                                         const VT *__restrict__ invd, const double *__restrict__ G0,
+                                         const double *__restrict__ G1)
+    {
+        if (EPI == EPI_SMOOTH || (EPI == EPI_SPMV && NDOT >= 1)) xr = x[row];
+        if (EPI != EPI_SPMV) fr = f[row];
+        if (EPI == EPI_SMOOTH || EPI == EPI_POLY) di = invd[row];
+        if (EPI == EPI_SMOOTH && NDOT >= 1) g0 = G0[row];
+        if (NDOT >= 2) g1 = G1[row];
+    }
+    template <typename OT>
+    __device__ __forceinline__ OT finish(VT acc, VT coef, double &d0, double &d1) const
+    {
+        if (EPI == EPI_SPMV) {
+            if (NDOT >= 1) d0 = (double)xr * (double)acc;
+            if (NDOT >= 2) d1 = (double)xr * g1;
+            return (OT)acc;
+        } else if (EPI == EPI_RESID) {
+            return (OT)((VT)fr - acc);
+        } else if (EPI == EPI_SMOOTH) {
+            VT out = xr + di * ((VT)fr - acc);
+            if (NDOT >= 1) d0 = (double)out * g0;
+            if (NDOT >= 2) d1 = (double)out * g1;
+            return (OT)out;
+        } else if (EPI == EPI_ADD) {
+            return (OT)((VT)fr + acc);
+        } else {
+            return (OT)(coef * (di * (VT)fr) + di * acc);
+        }
+    }
+};
+
 template <typename VT, typename FT, typename OT, typename IT, int EPI, int NDOT>
 // 8 wavefronts per SIMD (at most 64 VGPRs): the pass is bound by loads in flight
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sell(const Sell<VT, IT> A, const VT *__restrict__ x,
@@ -468,23 +507,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
             });
         }
         if (row >= 0) {
-            if (EPI == EPI_SPMV) {
-                y[row] = (OT)acc;
-                if (NDOT >= 1) d0 = (double)x[row] * (double)acc;
-                if (NDOT >= 2) d1 = (double)x[row] * g1[row];
-            } else if (EPI == EPI_RESID) {
-                y[row] = (OT)((VT)f[row] - acc);
-            } else if (EPI == EPI_SMOOTH) {
-                VT out = x[row] + invd[row] * ((VT)f[row] - acc);
-                y[row] = (OT)out;
-                if (NDOT >= 1) d0 = (double)out * g0[row];
-                if (NDOT >= 2) d1 = (double)out * g1[row];
-            } else if (EPI == EPI_ADD) {
-                y[row] = (OT)((VT)f[row] + acc);
-            } else {
-                VT di = invd[row];
-                y[row] = (OT)(coef * (di * (VT)f[row]) + di * acc);
-            }
+            RowOps<VT, FT, EPI, NDOT> ops;
+            ops.load(row, x, f, invd, g0, g1);
+            y[row] = ops.template finish<OT>(acc, coef, d0, d1);
         }
     }
     if (NDOT >= 1) {
@@ -644,7 +669,7 @@ __global__ __launch_bounds__(256) void k_coarse_solve(int n, int ld, const doubl
 }
 
 // Dot-product partials: one per block of a fixed grid (grid-stride).
-__global__ void k_dot2(int64_t n, const double *__restrict__ a, const double *__restrict__ b,
+static __global__ void k_dot2(int64_t n, const double *__restrict__ a, const double *__restrict__ b,
                        const double *__restrict__ c, double *__restrict__ partial)
 {
     __shared__ double lds[8];
@@ -659,7 +684,7 @@ __global__ void k_dot2(int64_t n, const double *__restrict__ a, const double *__
 
 // u += alpha p ; r -= alpha q ; partials of (r, r).  Skipped once a breakdown
 // flag is set (so u keeps the last valid iterate).
-__global__ void k_cg_update(int64_t n, const double *__restrict__ sc, double *__restrict__ u,
+static __global__ void k_cg_update(int64_t n, const double *__restrict__ sc, double *__restrict__ u,
                             double *__restrict__ r, const double *__restrict__ p, const double *__restrict__ q,
                             double *__restrict__ partial)
 {
@@ -681,7 +706,7 @@ __global__ void k_cg_update(int64_t n, const double *__restrict__ sc, double *__
 }
 
 // p = z + beta p
-__global__ void k_cg_pupdate(int64_t n, const double *__restrict__ sc, const double *__restrict__ z,
+static __global__ void k_cg_pupdate(int64_t n, const double *__restrict__ sc, const double *__restrict__ z,
                              double *__restrict__ p)
 {
     const double beta = sc[S_BETA];
@@ -704,7 +729,7 @@ __global__ void k_fill(int64_t n, T v, T *__restrict__ d)
 
 // Final sum of the block partials (two dots) in index order, then the scalar
 // recurrences of CG / FCG(1) on the device.
-__global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double *__restrict__ partial, int nblk, double *sc,
+static __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double *__restrict__ partial, int nblk, double *sc,
                                                            int op, int slot)
 {
     __shared__ double lds[2 * FIN_THREADS / 64];

@@ -1,0 +1,297 @@
+// Element-wise, transfer, coarsest-level and reduction kernels of the 16-column
+// block solve (row-major N x 16 vectors; the matrix passes are in kernels_blk.h).
+#pragma once
+#include "kernels.h"
+
+namespace amgk {
+
+constexpr int NB = 16;
+
+// per-column scalar slots: sc[slot * NB + j]
+enum BSlot { B_RZ = 0, B_PQ, B_RR, B_ALPHA, B_BETA, B_PR, B_ZQ, B_FF, B_FLAG, B_DONE, B_ITERS, B_THR, B_NSLOTS };
+enum BFin { BF_FF = 0, BF_RR0, BF_RZ0, BF_PQ_CG, BF_PQ_FCG, BF_RR, BF_RZ_CG, BF_ZQ_FCG };
+
+__device__ inline bool bactive(const double *sc, int j) { return sc[B_DONE * NB + j] == 0.0 && sc[B_FLAG * NB + j] == 0.0; }
+
+// ---- elementwise block kernels (one thread per row, 16 columns) ---------------
+
+template <typename VT, typename FT>
+__global__ void k_scale_blk(int64_t n, const VT *__restrict__ invd, const FT *__restrict__ f, VT *__restrict__ u,
+                            VT coef)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const VT di = invd[i];
+#pragma unroll
+    for (int j = 0; j < NB; j++) u[i * NB + j] = coef * (di * (VT)f[i * NB + j]);
+}
+
+// coef == 1 keeps the l1 sweep's bits: 1 * (d * f) == d * f exactly.
+template <typename VT>
+__global__ void k_restrict_blk(int64_t nc, int mw, const int32_t *__restrict__ members, const VT *__restrict__ pc,
+                               const VT *__restrict__ r, VT *__restrict__ fc, const VT *__restrict__ invdc,
+                               VT *__restrict__ uc, VT coef)
+{
+#pragma clang fp contract(off)
+    int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (I >= nc) return;
+    VT s[NB];
+#pragma unroll
+    for (int j = 0; j < NB; j++) s[j] = 0;
+    for (int t = 0; t < mw; t++) {
+        int m = members[I * mw + t];
+        if (m < 0) break;
+        const VT pm = pc[m];
+#pragma unroll
+        for (int j = 0; j < NB; j++) {
+            VT prod = pm * r[(int64_t)m * NB + j];
+            s[j] = s[j] + prod;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NB; j++) fc[I * NB + j] = s[j];
+    if (uc) {
+        const VT di = invdc[I];
+#pragma unroll
+        for (int j = 0; j < NB; j++) uc[I * NB + j] = coef * (di * s[j]);
+    }
+}
+
+template <typename VT>
+__global__ void k_prolong_blk(int64_t n, const int32_t *__restrict__ agg, const VT *__restrict__ pc,
+                              const VT *__restrict__ e, VT *__restrict__ u)
+{
+#pragma clang fp contract(off)
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const VT pi = pc[i];
+    const int64_t a = (int64_t)agg[i] * NB;
+#pragma unroll
+    for (int j = 0; j < NB; j++) {
+        VT prod = pi * e[a + j];
+        u[i * NB + j] = u[i * NB + j] + prod;
+    }
+}
+
+template <typename VT, typename OT>
+__global__ void k_add_blk(int64_t n, const VT *__restrict__ x, const VT *__restrict__ c, OT *__restrict__ y)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n * NB) return;
+    y[i] = (OT)(x[i] + c[i]);
+}
+
+// Coarsest level for 16 columns, in two launches over 16-row tiles (block =
+// 16 rows x 16 columns, thread = one output element):
+//   phase 0: Y = L^{-1} F,   phase 1: E = L^{-T} Y   (Y: global scratch, n x 16).
+// Per element the single-vector kernel's order (k ascending), so each column
+// equals k_coarse_solve's result.
+template <typename VT>
+__global__ __launch_bounds__(256) void k_coarse_solve_blk(int n, int ld, const double *__restrict__ Linv,
+                                                          const double *__restrict__ LinvT, const VT *__restrict__ f,
+                                                          double *__restrict__ Y, VT *__restrict__ e, int phase)
+{
+    const int j = threadIdx.x & (NB - 1);
+    const int i = blockIdx.x * (256 / NB) + threadIdx.x / NB;
+    if (i >= n) return;
+    double s = 0.0;
+    if (phase == 0) {
+#pragma unroll 8
+        for (int k = 0; k <= i; k++) s = fma(LinvT[(int64_t)k * ld + i], (double)f[(int64_t)k * NB + j], s);
+        Y[(int64_t)i * NB + j] = s;
+    } else {
+#pragma unroll 8
+        for (int k = i; k < n; k++) s = fma(Linv[(int64_t)k * ld + i], Y[(int64_t)k * NB + j], s);
+        e[(int64_t)i * NB + j] = (VT)s;
+    }
+}
+
+// Column-major (n x k, leading dimension n) <-> row-major block (n x NB).
+static __global__ void k_pack_blk(int64_t n, int k, const double *__restrict__ cm, double *__restrict__ rm)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+#pragma unroll
+    for (int j = 0; j < NB; j++) rm[i * NB + j] = j < k ? cm[(int64_t)j * n + i] : 0.0;
+}
+
+static __global__ void k_unpack_blk(int64_t n, int k, const double *__restrict__ rm, double *__restrict__ cm)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    for (int j = 0; j < k; j++) cm[(int64_t)j * n + i] = rm[i * NB + j];
+}
+
+// ---- element-parallel block vector kernels ----------------------------------
+//
+// Thread t of the grid handles the elements e = t, t + T, ... (T = threads in
+// the grid, a multiple of 16) of the row-major N x 16 arrays, so a wave's load
+// is 64 consecutive values and every thread keeps one column j = e % 16.  Dot
+// partials per column: the thread's running sum, the 4 lanes of each column in
+// a wave (butterfly over lane bits 4 and 5), then the block's waves in order:
+// partial[(2 * blockIdx.x + d) * NB + j].
+
+__device__ inline void blk_col_partials(double s0, double s1, double *lds /* 2 * 4 * NB */, double *partial)
+{
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    s0 += __shfl_xor(s0, 16, 64);
+    s0 += __shfl_xor(s0, 32, 64);
+    s1 += __shfl_xor(s1, 16, 64);
+    s1 += __shfl_xor(s1, 32, 64);
+    if (lane < NB) {
+        lds[wid * NB + lane] = s0;
+        lds[(4 + wid) * NB + lane] = s1;
+    }
+    __syncthreads();
+    if (threadIdx.x < NB) {
+        const int j = threadIdx.x;
+        partial[(2 * blockIdx.x) * NB + j] = ((lds[j] + lds[NB + j]) + lds[2 * NB + j]) + lds[3 * NB + j];
+        partial[(2 * blockIdx.x + 1) * NB + j] =
+            ((lds[4 * NB + j] + lds[5 * NB + j]) + lds[6 * NB + j]) + lds[7 * NB + j];
+    }
+}
+
+// per-column partials of (a, b) and (a, c) (c may be NULL)
+static __global__ __launch_bounds__(256) void k_dot2_blk(int64_t n, const double *__restrict__ a, const double *__restrict__ b,
+                                                  const double *__restrict__ c, double *__restrict__ partial)
+{
+    __shared__ double lds[8 * NB];
+    double s0 = 0.0, s1 = 0.0;
+    const int64_t m = n * NB;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < m; e += (int64_t)gridDim.x * 256) {
+        s0 = fma(a[e], b[e], s0);
+        if (c) s1 = fma(a[e], c[e], s1);
+    }
+    blk_col_partials(s0, s1, lds, partial);
+}
+
+// u += alpha p ; r -= alpha q for the active columns; partials of (r, r).
+static __global__ __launch_bounds__(256) void k_bcg_update(int64_t n, const double *__restrict__ sc, double *__restrict__ u,
+                                                    double *__restrict__ r, const double *__restrict__ p,
+                                                    const double *__restrict__ q, double *__restrict__ partial)
+{
+    __shared__ double lds[8 * NB];
+    const int j = threadIdx.x & (NB - 1);
+    const bool act = bactive(sc, j);
+    const double al = sc[B_ALPHA * NB + j];
+    double s = 0.0;
+    const int64_t m = n * NB;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < m; e += (int64_t)gridDim.x * 256) {
+        double ri = r[e];
+        if (act) {
+            u[e] = fma(al, p[e], u[e]);
+            ri = fma(-al, q[e], ri);
+            r[e] = ri;
+        }
+        s = fma(ri, ri, s);
+    }
+    blk_col_partials(s, 0.0, lds, partial);
+}
+
+// p = z + beta p for the active columns
+static __global__ __launch_bounds__(256) void k_bcg_pupdate(int64_t n, const double *__restrict__ sc,
+                                                     const double *__restrict__ z, double *__restrict__ p)
+{
+    const int j = threadIdx.x & (NB - 1);
+    if (!bactive(sc, j)) return;
+    const double be = sc[B_BETA * NB + j];
+    const int64_t m = n * NB;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < m; e += (int64_t)gridDim.x * 256)
+        p[e] = fma(be, p[e], z[e]);
+}
+
+// First stage of k_bfinalize for many partials: the strided sums that its
+// thread t would form (partials t, t + FIN_THREADS, ... in ascending order),
+// one grid thread per (t, dot, column): strided[(d * NB + j) * FIN_THREADS + t].
+static __global__ __launch_bounds__(256) void k_bfin_strided(const double *__restrict__ partial, int nblk,
+                                                      double *__restrict__ strided)
+{
+    const int idx = blockIdx.x * 256 + threadIdx.x;   // < 2 * NB * FIN_THREADS
+    const int j = idx % NB, d = (idx / NB) % 2, t = idx / (2 * NB);
+    double s = 0.0;
+    for (int b = t; b < nblk; b += FIN_THREADS) s += partial[(2 * b + d) * NB + j];
+    strided[(d * NB + j) * FIN_THREADS + t] = s;
+}
+
+// Final per-column sums of the partials (index order) and the scalar
+// recurrences, masks and iteration counters of the 16 independent solves.
+// With strided != nullptr the per-thread strided sums come from
+// k_bfin_strided (the same values).
+static __global__ __launch_bounds__(FIN_THREADS) void k_bfinalize(const double *__restrict__ partial, int nblk, double *sc,
+                                                           int op, double tol, const double *__restrict__ strided)
+{
+    // per column the order of k_finalize: thread strides, butterfly, waves in order
+    constexpr int NW = FIN_THREADS / 64;
+    __shared__ double lds[2 * NW * NB];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    double s0[NB], s1[NB];
+#pragma unroll
+    for (int j = 0; j < NB; j++) { s0[j] = 0.0; s1[j] = 0.0; }
+    if (strided) {
+#pragma unroll
+        for (int j = 0; j < NB; j++) {
+            s0[j] = strided[j * FIN_THREADS + threadIdx.x];
+            s1[j] = strided[(NB + j) * FIN_THREADS + threadIdx.x];
+        }
+    } else {
+        for (int b = threadIdx.x; b < nblk; b += FIN_THREADS)
+#pragma unroll
+            for (int j = 0; j < NB; j++) { s0[j] += partial[(2 * b) * NB + j]; s1[j] += partial[(2 * b + 1) * NB + j]; }
+    }
+#pragma unroll
+    for (int j = 0; j < NB; j++) { s0[j] = wave_sum(s0[j]); s1[j] = wave_sum(s1[j]); }
+    if (lane == 0)
+#pragma unroll
+        for (int j = 0; j < NB; j++) { lds[wid * NB + j] = s0[j]; lds[(NW + wid) * NB + j] = s1[j]; }
+    __syncthreads();
+    // thread j: column j, its waves summed in order (the columns are independent)
+    if (threadIdx.x >= NB) return;
+    {
+        const int j = threadIdx.x;
+        double a = 0.0, b = 0.0;
+        for (int w = 0; w < NW; w++) { a += lds[w * NB + j]; b += lds[(NW + w) * NB + j]; }
+        double *F = sc + B_FLAG * NB + j, *D = sc + B_DONE * NB + j;
+        switch (op) {
+        case BF_FF:
+            sc[B_FF * NB + j] = a;
+            sc[B_THR * NB + j] = tol * sqrt(a);
+            break;
+        case BF_RR0:   // initial residual: converged columns are done before any update
+            sc[B_RR * NB + j] = a;
+            if (sc[B_FF * NB + j] == 0.0 || sqrt(a) <= sc[B_THR * NB + j]) *D = 1.0;
+            break;
+        case BF_RZ0:
+            if (*D != 0.0) break;
+            sc[B_RZ * NB + j] = a;
+            if (!(a > 0.0) || !isfinite(a)) *F = 2.0;
+            break;
+        case BF_PQ_CG:
+        case BF_PQ_FCG:
+            if (*D != 0.0 || *F != 0.0) break;
+            sc[B_PQ * NB + j] = a;
+            if (op == BF_PQ_FCG) sc[B_PR * NB + j] = b;
+            if (!(a > 0.0) || !isfinite(a)) *F = 1.0;
+            else sc[B_ALPHA * NB + j] = (op == BF_PQ_FCG ? b : sc[B_RZ * NB + j]) / a;
+            break;
+        case BF_RR:   // one more completed update of this column
+            if (*D != 0.0 || *F != 0.0) break;
+            sc[B_RR * NB + j] = a;
+            sc[B_ITERS * NB + j] += 1.0;
+            if (sqrt(a) <= sc[B_THR * NB + j]) *D = 1.0;
+            break;
+        case BF_RZ_CG:
+            if (*D != 0.0 || *F != 0.0) break;
+            if (!(a > 0.0) || !isfinite(a)) *F = 2.0;
+            else { sc[B_BETA * NB + j] = a / sc[B_RZ * NB + j]; sc[B_RZ * NB + j] = a; }
+            break;
+        case BF_ZQ_FCG:
+            if (*D != 0.0 || *F != 0.0) break;
+            sc[B_ZQ * NB + j] = a;
+            if (!isfinite(a)) *F = 2.0;
+            else sc[B_BETA * NB + j] = -a / sc[B_PQ * NB + j];
+            break;
+        }
+    }
+}
+
+}  // namespace amgk

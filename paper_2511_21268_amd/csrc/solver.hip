@@ -5,13 +5,16 @@
 #include "amg.h"
 #include "cheb.h"
 #include "coarse.h"
+#include "devmat.h"
 #include "host.h"
 #include "kernels.h"
-#include "kernels_blk.h"
+#include "blk_launch.h"
+#include "kernels_blk_vec.h"
 #include "blockcg.h"
 #include "mlp.h"
 #include "post_res.h"
 #include "setup_dev.h"
+#include "split_launch.h"
 #include "tail.h"
 
 #include <hip/hip_runtime.h>
@@ -89,41 +92,6 @@ template <typename T> T *dupload(const T *h, size_t n)
 
 inline unsigned nblocks(int64_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
 inline unsigned vgrid(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (n + 255) / 256)); }
-
-// Host-side sliced-ELL image of one level (layout described in kernels.h).
-struct DevMat {
-    int64_t n = 0, ncols = 0, nnz = 0, nslices = 0, stored = 0, nshared = 0;
-    double index_bytes = 0.0;
-    int idx16 = 1, C = SLICE, sorted = 0;
-    int64_t *soff = nullptr, *ibase = nullptr;
-    int32_t *col0 = nullptr, *c32 = nullptr, *shoff = nullptr, *perm = nullptr, *shrun = nullptr;
-    // windows shared by the four slices of a block (batched stencil images)
-    int32_t *wgtab = nullptr, *wgst = nullptr;
-    int wg_sigma = 0;
-    int xwin = 0;   // single-vector K passes through x windows (shared-offset images with run tables)
-    double wg_ratio = 0.0;   // rows the shared windows copy / rows per-wave windows copy
-    uint16_t *d16 = nullptr;
-    double *v64 = nullptr;
-    float *v32 = nullptr;
-    // CSR image with `lpr` lanes per row (lpr > 0; FP64, int32 columns) instead
-    // of SELL: long or few rows of the smoothed hierarchy
-    int lpr = 0;
-    int64_t *crp = nullptr;
-    int32_t *cci = nullptr;
-    double *cv = nullptr;
-    bool built() const { return soff || crp; }
-    template <typename VT> const VT *val() const;
-    template <typename IT> const IT *idx() const;
-    template <typename VT, typename IT> Sell<VT, IT> sv() const
-    {
-        return Sell<VT, IT>{n,     ncols, nslices, soff,  ibase, val<VT>(), idx<IT>(), col0,
-                            shoff, perm,  shrun,   wgtab, wgst,  xwin};
-    }
-};
-template <> const double *DevMat::val<double>() const { return v64; }
-template <> const float *DevMat::val<float>() const { return v32; }
-template <> const uint16_t *DevMat::idx<uint16_t>() const { return d16; }
-template <> const int32_t *DevMat::idx<int32_t>() const { return c32; }
 
 struct Level {
     int64_t n = 0, nnz = 0;
@@ -287,7 +255,7 @@ struct amg_ctx {
     }
     void release(DevMat &M)
     {
-        release(M.soff); release(M.ibase); release(M.shoff); release(M.shrun); release(M.perm); release(M.col0);
+        release(M.soff); release(M.ibase); release(M.shoff); release(M.shrun); release(M.perm); release(M.gcol); release(M.col0);
         release(M.wgtab); release(M.wgst);
         release(M.c32);
         release(M.d16);
@@ -355,6 +323,24 @@ struct amg_ctx {
         A.n = K.n; A.ncols = square ? K.n : ncols; A.sorted = S.sorted;
         A.nnz = K.nnz(); A.nslices = S.nslices; A.stored = S.stored; A.idx16 = S.idx16; A.C = C;
         A.nshared = S.nshared; A.index_bytes = S.index_bytes;
+        if (C == SLICE) A.split = split_waves(S.nslices, S.stored);
+        if (A.split > 1 && !S.d16.empty()) {
+            // running column before each group of 8 deltas
+            std::vector<int32_t> gcol(S.d16.size() / 8);
+            for (int64_t sl = 0; sl < S.nslices; sl++) {
+                if (S.ibase[sl] < 0) continue;
+                const int64_t ng = (S.soff[sl + 1] - S.soff[sl]) / (8 * C);
+                for (int r = 0; r < C; r++) {
+                    int32_t col = S.col0[sl * C + r];
+                    for (int64_t g = 0; g < ng; g++) {
+                        gcol[S.ibase[sl] / 8 + g * C + r] = col;
+                        const uint16_t *d = &S.d16[S.ibase[sl] + (g * C + r) * 8];
+                        for (int k = 0; k < 8; k++) col += d[k];
+                    }
+                }
+            }
+            A.gcol = upload(gcol);
+        }
         A.soff = upload(S.soff);
         A.ibase = upload(S.ibase);
         if (!S.shoff.empty()) {
@@ -381,6 +367,21 @@ struct amg_ctx {
         if (!S.col0.empty()) A.col0 = upload(S.col0);
         if (!S.c32.empty()) A.c32 = upload(S.c32);
         return A;
+    }
+    // Wavefronts per slice of the single-vector passes.  One wave per slice
+    // keeps the GPU's loads going from about 1,200 slices (4-5 per CU) on:
+    // measured, 3D p = 3 SpMV in us, one wave / four: 792 slices 39 / 27, 1,077
+    // slices 40 / 39, 1,839 slices 54 / 59; an FP64 V-cycle at 1,839 slices
+    // on level 0 221 / 230.  Eight waves below 256 slices: a V-cycle of
+    // 145, 37, .. slices 100 / 90 with four / eight, one of 562, 141, ..
+    // slices 119 / 130 with eight on its finest level.  A row of few groups
+    // of 8 entries gives more waves nothing to do.
+    static int split_waves(int64_t nslices, int64_t stored)
+    {
+        const double groups = (double)stored / (8.0 * SLICE * (double)std::max<int64_t>(nslices, 1));
+        if (nslices >= 1200) return 1;
+        if (nslices >= 256) return groups >= 8.0 ? 4 : 1;
+        return groups >= 16.0 ? 8 : 4;
     }
     // Device time of body(), best of two after one warm-up run.
     template <class Body> float time_passes(Body body)
@@ -409,7 +410,7 @@ struct amg_ctx {
     void tune_xwin()
     {
         DevMat &A = lev[0].A;
-        if (!A.xwin || !A.v64) return;
+        if (!A.xwin || !A.v64 || A.split > 1) return;   // the passes of a split image gather
         for (double *v : {p, r})
             hipLaunchKernelGGL((k_fill<double>), dim3(vgrid(n)), dim3(256), 0, stream, n, 1.0, v);
         HIPCHK(hipGetLastError());
@@ -709,13 +710,21 @@ struct amg_ctx {
     void launch_sell(const DevMat &A, unsigned nb, const VT *x, const FT *f, const VT *invd, OT *y,
                      const double *g0, const double *g1, VT coef)
     {
-        if (A.idx16)
+        if (A.split > 1)
+            split_pass<VT, FT, OT, EPI, NDOT>(stream, A, {x, f, invd, y, g0, g1, coef}, partial);
+        else if (A.idx16)
             hipLaunchKernelGGL((k_sell<VT, FT, OT, uint16_t, EPI, NDOT>), dim3(nb), dim3(256), 0, stream,
                                A.sv<VT, uint16_t>(), x, f, invd, y, g0, g1, partial, coef);
         else
             hipLaunchKernelGGL((k_sell<VT, FT, OT, int32_t, EPI, NDOT>), dim3(nb), dim3(256), 0, stream,
                                A.sv<VT, int32_t>(), x, f, invd, y, g0, g1, partial, coef);
         HIPCHK(hipGetLastError());
+    }
+    // dot partials of a single-vector pass over the level's matrix: one per
+    // wavefront of whole blocks, or one per slice
+    unsigned dot_blocks(const DevMat &A) const
+    {
+        return A.split > 1 ? (unsigned)A.nslices : (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES) * SELL_WAVES;
     }
     unsigned sell_blocks(int l) const { return (unsigned)((lev[l].A.nslices + SELL_WAVES - 1) / SELL_WAVES); }
     // Fused prolongation + first post-smoothing sweep on level l (needs K P).
@@ -726,17 +735,23 @@ struct amg_ctx {
         const DevMat &A = L.KP;
         unsigned nb = (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES);
         if (l == 0) prof_begin();
-#define POST_LAUNCH(IT, IDX, ND)                                                                              \
+#define POST_LAUNCH(IT, ND)                                                                                   \
     hipLaunchKernelGGL((k_sell_post<VT, OT, IT, ND>), dim3(nb), dim3(256), 0, stream, A.sv<VT, IT>(), e, u,     \
                        (const VT *)L.r, L.invd<VT>(), L.agg, L.pc<VT>(), y, g0, g1, partial)
-        if (A.idx16) {
-            if (ndot == 2) POST_LAUNCH(uint16_t, A.d16, 2);
-            else if (ndot == 1) POST_LAUNCH(uint16_t, A.d16, 1);
-            else POST_LAUNCH(uint16_t, A.d16, 0);
+        if (A.split > 1) {
+            const PostVecs<VT, OT> v{e, u, (const VT *)L.r, L.invd<VT>(), L.agg, L.pc<VT>(), y, g0};
+            if constexpr (std::is_same_v<OT, double>) {
+                if (ndot) split_post<VT, OT, 1>(stream, A, v, partial);
+                else split_post<VT, OT, 0>(stream, A, v, partial);
+            } else {
+                split_post<VT, OT, 0>(stream, A, v, partial);
+            }
+        } else if (A.idx16) {
+            if (ndot) POST_LAUNCH(uint16_t, 1);
+            else POST_LAUNCH(uint16_t, 0);
         } else {
-            if (ndot == 2) POST_LAUNCH(int32_t, A.c32, 2);
-            else if (ndot == 1) POST_LAUNCH(int32_t, A.c32, 1);
-            else POST_LAUNCH(int32_t, A.c32, 0);
+            if (ndot) POST_LAUNCH(int32_t, 1);
+            else POST_LAUNCH(int32_t, 0);
         }
 #undef POST_LAUNCH
         HIPCHK(hipGetLastError());
@@ -747,7 +762,7 @@ struct amg_ctx {
                            (double)sizeof(OT) * A.n + 8.0 * A.n * ndot;              // y, dot partners
             prof_end(bytes, AMG_PASS_KP);
         }
-        return nb * SELL_WAVES;   // one dot partial per wavefront
+        return dot_blocks(A);
     }
     // Fused prolongation + residual of the polynomial post-smoothing on level l:
     // y = u + P e, L.r <- L.r - (K P) e (needs K P and the pre-smoothing residual in L.r).
@@ -757,7 +772,9 @@ struct amg_ctx {
         const DevMat &A = L.KP;
         unsigned nb = (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES);
         if (l == 0) prof_begin();
-        if (A.idx16)
+        if (A.split > 1)
+            split_post_res<VT>(stream, A, e, u, (VT *)L.r, L.agg, L.pc<VT>(), y);
+        else if (A.idx16)
             hipLaunchKernelGGL((k_sell_post_res<VT, uint16_t>), dim3(nb), dim3(256), 0, stream, A.sv<VT, uint16_t>(),
                                e, u, (VT *)L.r, L.agg, L.pc<VT>(), y);
         else
@@ -802,10 +819,14 @@ struct amg_ctx {
     {
         Level &L = lev[l];
         if (!L.poly_on) {
-            if (ndot == 2) sell<VT, FT, OT, EPI_SMOOTH, 2>(l, uin, f, L.invd<VT>(), uout, g0, g1);
-            else if (ndot == 1) sell<VT, FT, OT, EPI_SMOOTH, 1>(l, uin, f, L.invd<VT>(), uout, g0, g1);
-            else sell<VT, FT, OT, EPI_SMOOTH, 0>(l, uin, f, L.invd<VT>(), uout, g0, g1);
-            if (ndot) vc_nb = sell_blocks(l) * SELL_WAVES;
+            // dots at level 0 only (FP64 right-hand side and output)
+            if constexpr (std::is_same_v<FT, double> && std::is_same_v<OT, double>) {
+                if (ndot) sell<VT, FT, OT, EPI_SMOOTH, 1>(l, uin, f, L.invd<VT>(), uout, g0, g1);
+                else sell<VT, FT, OT, EPI_SMOOTH, 0>(l, uin, f, L.invd<VT>(), uout, g0, g1);
+            } else {
+                sell<VT, FT, OT, EPI_SMOOTH, 0>(l, uin, f, L.invd<VT>(), uout, g0, g1);
+            }
+            if (ndot) vc_nb = dot_blocks(L.A);
             return;
         }
         VT *res = (VT *)L.r, *c = (VT *)L.c, *c2 = (VT *)L.c2;
@@ -919,10 +940,11 @@ struct amg_ctx {
             HIPCHK(hipGetLastError());
         }
         for (int s = s0; s <= prm.nu_post; s++) {
-            if (zout && s == prm.nu_post) {
-                sweep<VT, FT, double>(l, f, u, zout, ndot, g0, g1);
-                return nullptr;
-            }
+            if constexpr (std::is_same_v<FT, double>)
+                if (zout && s == prm.nu_post) {
+                    sweep<VT, FT, double>(l, f, u, zout, ndot, g0, g1);
+                    return nullptr;
+                }
             sweep<VT, FT, VT>(l, f, u, u2, 0, nullptr, nullptr);
             std::swap(u, u2);
         }
@@ -972,7 +994,9 @@ struct amg_ctx {
         }
         unsigned nb = (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES);
         if (l == 0) prof_begin();
-        if (A.idx16)
+        if (A.split > 1)
+            split_cheb<MODE>(stream, A, x, f, r, L.invd64, u, dn, a, b, first);
+        else if (A.idx16)
             hipLaunchKernelGGL((k_sell_cheb<uint16_t, MODE>), dim3(nb), dim3(256), 0, stream,
                                A.sv<double, uint16_t>(), x, f, r, L.invd64, u, dn, a, b, first);
         else
@@ -1127,74 +1151,15 @@ struct amg_ctx {
         if (tail_start > 0) tail_dev_blk = fp32() ? tail_descriptors<float>(true) : tail_descriptors<double>(true);
         HIPCHK(hipHostMalloc((void **)&hbsc, B_NSLOTS * NB * sizeof(double), hipHostMallocDefault));
     }
-    unsigned blk_grid(const DevMat &B) const
-    {
-        int64_t wpb = blk_threads / 64;
-        int64_t g = (B.nslices + wpb - 1) / wpb;
-        return (unsigned)std::max<int64_t>(1, std::min<int64_t>(g, blk_threads == 512 ? 2048 : 4096));
-    }
-    template <typename VT, typename FT, typename OT, int EPI, int NDOT, int LPR>
-    unsigned launch_sellb(const DevMat &B, const VT *x, const FT *f, const VT *invd, OT *y, const double *g0,
-                          const double *g1, VT coef)
-    {
-        unsigned g = blk_grid(B);
-        if (B.idx16)
-            hipLaunchKernelGGL((k_sellb<VT, FT, OT, uint16_t, EPI, NDOT, LPR>), dim3(g), dim3(blk_threads), 0, stream,
-                               B.sv<VT, uint16_t>(), x, f, invd, y, g0, g1, bpartial, coef);
-        else
-            hipLaunchKernelGGL((k_sellb<VT, FT, OT, int32_t, EPI, NDOT, LPR>), dim3(g), dim3(blk_threads), 0, stream,
-                               B.sv<VT, int32_t>(), x, f, invd, y, g0, g1, bpartial, coef);
-        return g;
-    }
+    BlkCfg blk_cfg() const { return {stream, blk_win, blk_share, blk_lpr, blk_threads, bpartial}; }
     // Block matrix pass on level l; returns the number of dot-partial blocks.
     template <typename VT, typename FT, typename OT, int EPI, int NDOT>
     unsigned sell_blk(int l, const VT *x, const FT *f, const VT *invd, OT *y, const double *g0, const double *g1,
                       VT coef = 1)
     {
-        const DevMat &A = lev[l].A;
-        const DevMat &B = lev[l].Ab;
-        unsigned nb;
         if (l == 0) prof_begin();
-        if (blk_win > 0 && A.nshared > 0 && A.shrun && A.val<VT>()) {
-            // stencil image: staged x windows, blk_win rows per lane; the grid
-            // is padded to a multiple of the XCD count (XCD-aware slice order)
-            const unsigned lgrid = sell_blocks(l);
-            const unsigned grid = xcd_grid(lgrid);
-            nb = lgrid * SELL_WAVES;   // dot partials: one per wavefront of a logical block
-#define BLKW(IT, R) hipLaunchKernelGGL((k_sellw_blk<VT, FT, OT, IT, EPI, NDOT, R>), dim3(grid), dim3(256), 0, stream, \
-                                       A.sv<VT, IT>(), x, f, invd, y, g0, g1, bpartial, coef)
-#define BLKWS(IT, R) hipLaunchKernelGGL((k_sellws_blk<VT, FT, OT, IT, EPI, NDOT, R>), dim3(grid), dim3(256), 0, \
-                                        stream, A.sv<VT, IT>(), x, f, invd, y, g0, g1, bpartial, coef)
-            if ((blk_share & (sizeof(VT) == 8 ? 1 : 2)) && A.wgtab) {
-                if (A.idx16) {
-                    if (blk_win == 2) BLKWS(uint16_t, 2);
-                    else BLKWS(uint16_t, 4);
-                } else {
-                    if (blk_win == 2) BLKWS(int32_t, 2);
-                    else BLKWS(int32_t, 4);
-                }
-            } else if (A.idx16) {
-                if (blk_win == 2) BLKW(uint16_t, 2);
-                else BLKW(uint16_t, 4);
-            } else {
-                if (blk_win == 2) BLKW(int32_t, 2);
-                else BLKW(int32_t, 4);
-            }
-#undef BLKW
-#undef BLKWS
-        } else if (blk_lpr > 1 && B.soff && B.val<VT>()) {
-            nb = blk_lpr == 4   ? launch_sellb<VT, FT, OT, EPI, NDOT, 4>(B, x, f, invd, y, g0, g1, coef)
-                 : blk_lpr == 8 ? launch_sellb<VT, FT, OT, EPI, NDOT, 8>(B, x, f, invd, y, g0, g1, coef)
-                                : launch_sellb<VT, FT, OT, EPI, NDOT, 16>(B, x, f, invd, y, g0, g1, coef);
-        } else {
-            const unsigned grid = sell_blocks(l);
-            nb = grid * SELL_WAVES;   // dot partials: one per wavefront
-#define BLK1(KER, IT) hipLaunchKernelGGL((KER<VT, FT, OT, IT, EPI, NDOT>), dim3(grid), dim3(256), 0, stream, \
-                                         A.sv<VT, IT>(), x, f, invd, y, g0, g1, bpartial, coef)
-            if (A.idx16) BLK1(k_sell_blk, uint16_t);
-            else BLK1(k_sell_blk, int32_t);
-#undef BLK1
-        }
+        const unsigned nb = 
+            blk_pass<VT, FT, OT, EPI, NDOT>(blk_cfg(), lev[l].A, lev[l].Ab, {x, f, invd, y, g0, g1, coef});
         HIPCHK(hipGetLastError());
         if (l == 0) {
             // 16 columns: matrix once, 16 vectors of each kind
@@ -1250,30 +1215,12 @@ struct amg_ctx {
         Level &L = lev[l];
         const bool multi = blk_lpr > 1 && L.KPb.soff;
         const DevMat &A = multi ? L.KPb : L.KP;
-        unsigned nb = multi ? blk_grid(A) : (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES);
-        unsigned thr = multi ? (unsigned)blk_threads : 256u;
         if (l == 0) prof_begin();
-#define BPOST(KERN, IT, IDX)                                                                                    \
-    hipLaunchKernelGGL(KERN, dim3(nb), dim3(thr), 0, stream, A.sv<VT, IT>(), E, U, (const VT *)L.br, L.invd<VT>(), \
-                       L.agg, L.pc<VT>(), Y, g0, g1, bpartial)
-#define BPOST_ND(IT, IDX, ND)                                                                                   \
-    do {                                                                                                        \
-        if (!multi) BPOST((k_sell_blk_post<VT, OT, IT, ND>), IT, IDX);                                          \
-        else if (blk_lpr == 4) BPOST((k_sellb_post<VT, OT, IT, ND, 4>), IT, IDX);                               \
-        else if (blk_lpr == 8) BPOST((k_sellb_post<VT, OT, IT, ND, 8>), IT, IDX);                               \
-        else BPOST((k_sellb_post<VT, OT, IT, ND, 16>), IT, IDX);                                                \
-    } while (0)
-        if (A.idx16) {
-            if (ndot == 2) BPOST_ND(uint16_t, A.d16, 2);
-            else if (ndot == 1) BPOST_ND(uint16_t, A.d16, 1);
-            else BPOST_ND(uint16_t, A.d16, 0);
-        } else {
-            if (ndot == 2) BPOST_ND(int32_t, A.c32, 2);
-            else if (ndot == 1) BPOST_ND(int32_t, A.c32, 1);
-            else BPOST_ND(int32_t, A.c32, 0);
-        }
-#undef BPOST_ND
-#undef BPOST
+        const PostVecs<VT, OT> v{E, U, (const VT *)L.br, L.invd<VT>(), L.agg, L.pc<VT>(), Y, g0};
+        unsigned nb;
+        if constexpr (std::is_same_v<OT, double>)
+            nb = ndot ? blk_post<VT, OT, 1>(blk_cfg(), A, multi, v) : blk_post<VT, OT, 0>(blk_cfg(), A, multi, v);
+        else nb = blk_post<VT, OT, 0>(blk_cfg(), A, multi, v);   // dots at level 0 only (FP64 output)
         HIPCHK(hipGetLastError());
         if (l == 0) {
             double bytes = (double)A.nnz * sizeof(VT) + A.index_bytes + (double)NB * sizeof(VT) * lev[1].n + (double)NB * sizeof(VT) * A.n * 2 +
@@ -1281,7 +1228,7 @@ struct amg_ctx {
                            8.0 * NB * A.n * ndot;
             prof_end(bytes, AMG_PASS_KP);
         }
-        return multi ? nb : nb * SELL_WAVES;   // one-lane kernel: a dot partial per wavefront
+        return nb;
     }
     template <typename VT, typename FT> VT *bpoly_apply(int l, const FT *rr, VT *&c, VT *&c2)
     {
@@ -1301,8 +1248,10 @@ struct amg_ctx {
         Level &L = lev[l];
         if (!L.poly_on) {
             unsigned nb;
-            if (ndot == 2) nb = sell_blk<VT, FT, OT, EPI_SMOOTH, 2>(l, uin, f, L.invd<VT>(), uout, g0, g1);
-            else if (ndot == 1) nb = sell_blk<VT, FT, OT, EPI_SMOOTH, 1>(l, uin, f, L.invd<VT>(), uout, g0, g1);
+            // dots at level 0 only (FP64 right-hand side and output)
+            if constexpr (std::is_same_v<FT, double> && std::is_same_v<OT, double>)
+                nb = ndot ? sell_blk<VT, FT, OT, EPI_SMOOTH, 1>(l, uin, f, L.invd<VT>(), uout, g0, g1)
+                          : sell_blk<VT, FT, OT, EPI_SMOOTH, 0>(l, uin, f, L.invd<VT>(), uout, g0, g1);
             else nb = sell_blk<VT, FT, OT, EPI_SMOOTH, 0>(l, uin, f, L.invd<VT>(), uout, g0, g1);
             if (ndot) vc_nb = nb;
             return;
@@ -1375,10 +1324,11 @@ struct amg_ctx {
             HIPCHK(hipGetLastError());
         }
         for (int s = s0; s <= prm.nu_post; s++) {
-            if (zout && s == prm.nu_post) {
-                bsweep<VT, FT, double>(l, f, u, zout, ndot, g0, g1);
-                return nullptr;
-            }
+            if constexpr (std::is_same_v<FT, double>)
+                if (zout && s == prm.nu_post) {
+                    bsweep<VT, FT, double>(l, f, u, zout, ndot, g0, g1);
+                    return nullptr;
+                }
             bsweep<VT, FT, VT>(l, f, u, u2, 0, nullptr, nullptr);
             std::swap(u, u2);
         }
@@ -1745,7 +1695,7 @@ static amg_status solve_impl(amg_ctx *c, const double *F, double *u_user, double
     auto partA = [&]() {
         if (flex) c->sell<double, double, double, EPI_SPMV, 2>(0, c->p, nullptr, nullptr, c->q, nullptr, c->r);
         else c->sell<double, double, double, EPI_SPMV, 1>(0, c->p, nullptr, nullptr, c->q, nullptr, nullptr);
-        c->finalize(c->sell_blocks(0) * SELL_WAVES, flex ? FIN_PQ_FCG : FIN_PQ_CG);
+        c->finalize(c->dot_blocks(c->lev[0].A), flex ? FIN_PQ_FCG : FIN_PQ_CG);
         unsigned g = vgrid(n);
         hipLaunchKernelGGL(k_cg_update, dim3(g), dim3(256), 0, c->stream, n, c->sc, u, c->r, c->p, c->q, c->partial);
         HIPCHK(hipGetLastError());
