@@ -2271,7 +2271,7 @@ amg_status amg_level_features(const amg_ctx *c, int level, float *feat)
 amg_status amg_mlp_forward(const uint16_t *w, const float *X, int B, float *Y, float *act, void *hip_stream)
 {
     if (!w || !X || !Y || B < 1) { set_err("NULL argument or B < 1"); return AMG_ERR_ARG; }
-    hipLaunchKernelGGL(k_mlp_fwd, dim3((B + 63) / 64), dim3(64), 0, (hipStream_t)hip_stream, w, X, B, Y, act);
+    mlp_forward(w, X, B, Y, act, (hipStream_t)hip_stream);
     if (hipGetLastError() != hipSuccess) { set_err("launch failed"); return AMG_ERR_HIP; }
     return AMG_OK;
 }
@@ -2280,16 +2280,14 @@ amg_status amg_mlp_backward(const uint16_t *w, const float *X, const float *act,
                             int B, float *del, float *grad, float *loss, void *hip_stream)
 {
     if (!w || !X || !act || !Y || !T || !del || !grad || B < 1) { set_err("NULL argument or B < 1"); return AMG_ERR_ARG; }
-    hipStream_t st = (hipStream_t)hip_stream;
-    hipLaunchKernelGGL(k_mlp_delta, dim3((B + 63) / 64), dim3(64), 0, st, w, act, Y, T, B, del);
-    hipLaunchKernelGGL(k_mlp_grad, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, st, X, act, del, Y, T, B, grad, loss);
+    mlp_gradient(w, X, act, Y, T, B, del, grad, loss, (hipStream_t)hip_stream);
     if (hipGetLastError() != hipSuccess) { set_err("launch failed"); return AMG_ERR_HIP; }
     return AMG_OK;
 }
 
 // ---- the MLP gradient without allocation ----------------------------------
 //
-// Per-sample deltas of the backward pass in a file-scope device array instead
+// Workspace of the backward pass in a file-scope device array instead
 // of a caller workspace, for callers that cannot allocate device memory.  Each
 // device holds its own copy of the array (until the process ends); host code
 // reaches it only through the address hipGetSymbolAddress returns on that
@@ -2336,11 +2334,9 @@ amg_status amg_mlp_backward_noalloc(const uint16_t *w, const float *X, const flo
     }
     float *del = scratch_on_current_device();
     if (!del) return AMG_ERR_HIP;
-    hipStream_t st = (hipStream_t)hip_stream;
-    // k_mlp_delta writes every delta of samples 0..B-1 before k_mlp_grad reads
-    // them (stream order), so nothing left by an earlier call is read
-    hipLaunchKernelGGL(k_mlp_delta, dim3((B + 63) / 64), dim3(64), 0, st, w, act, Y, T, B, del);
-    hipLaunchKernelGGL(k_mlp_grad, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, st, X, act, del, Y, T, B, grad, loss);
+    // k_mlp_back writes every partial sum before k_mlp_reduce reads it (stream
+    // order), so nothing left by an earlier call is read
+    mlp_gradient(w, X, act, Y, T, B, del, grad, loss, (hipStream_t)hip_stream);
     if (hipGetLastError() != hipSuccess) { set_err("launch failed"); return AMG_ERR_HIP; }
     return AMG_OK;
 }
@@ -2398,7 +2394,7 @@ amg_status amg_set_learned_poly(amg_ctx *c, const uint16_t *w_host, int *accepte
         float *dX = dalloc<float>(X.size()), *dY = dalloc<float>(Y.size());
         HIPCHK(hipMemcpy(dw, w_host, MLP_NPARAM * sizeof(uint16_t), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(dX, X.data(), X.size() * sizeof(float), hipMemcpyHostToDevice));
-        hipLaunchKernelGGL(k_mlp_fwd, dim3((nl + 63) / 64), dim3(64), 0, c->stream, dw, dX, nl, dY, (float *)nullptr);
+        mlp_forward(dw, dX, nl, dY, nullptr, c->stream);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(Y.data(), dY, Y.size() * sizeof(float), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));

@@ -159,6 +159,7 @@ class Trainer:
         self.grad = torch.zeros_like(self.master)
         self.loss = torch.zeros(1, dtype=torch.float32, device=dev)
         self.step_no = 0
+        self.work = None
         self._adam(0, 0.0)
 
     def _st(self):
@@ -170,31 +171,39 @@ class Trainer:
                                           C.c_void_p(self.v.data_ptr()), step, lr, self._st()))
 
     def forward(self, X, act=None):
-        B = X.shape[0]
-        Y = self.t.empty(B, 4, dtype=self.t.float32, device="cuda")
-        amg._check(amg.lib().amg_mlp_forward(C.c_void_p(self.w.data_ptr()), C.c_void_p(X.data_ptr()), B,
-                                             C.c_void_p(Y.data_ptr()),
-                                             C.c_void_p(act.data_ptr()) if act is not None else None, self._st()))
+        Y = self.t.empty(X.shape[0], 4, dtype=self.t.float32, device="cuda")
+        self._forward(X, Y, act)
         return Y
 
+    def _forward(self, X, Y, act):
+        amg._check(amg.lib().amg_mlp_forward(C.c_void_p(self.w.data_ptr()), C.c_void_p(X.data_ptr()), X.shape[0],
+                                             C.c_void_p(Y.data_ptr()),
+                                             C.c_void_p(act.data_ptr()) if act is not None else None, self._st()))
+
     def backward(self, X, act, Y, T):
-        B = X.shape[0]
-        dl = self.t.empty(B, amg.MLP_NDEL, dtype=self.t.float32, device="cuda")
+        self._backward(X, act, Y, T, self.t.empty(X.shape[0], amg.MLP_NDEL, dtype=self.t.float32, device="cuda"))
+        return float(self.loss.item())
+
+    def _backward(self, X, act, Y, T, work):
         amg._check(amg.lib().amg_mlp_backward(C.c_void_p(self.w.data_ptr()), C.c_void_p(X.data_ptr()),
                                               C.c_void_p(act.data_ptr()), C.c_void_p(Y.data_ptr()),
-                                              C.c_void_p(T.data_ptr()), B, C.c_void_p(dl.data_ptr()),
+                                              C.c_void_p(T.data_ptr()), X.shape[0], C.c_void_p(work.data_ptr()),
                                               C.c_void_p(self.grad.data_ptr()), C.c_void_p(self.loss.data_ptr()),
                                               self._st()))
-        return float(self.loss.item())
 
     def step(self, X, T, lr):
         B = X.shape[0]
-        act = self.t.empty(B, amg.MLP_NACT, dtype=self.t.float32, device="cuda")
-        Y = self.forward(X, act)
-        loss = self.backward(X, act, Y, T)
+        if self.work is None or self.work[0].shape[0] != B:
+            # activations, outputs and workspace of this batch size
+            self.work = [self.t.empty(B, k, dtype=self.t.float32, device="cuda")
+                         for k in (amg.MLP_NACT, 4, amg.MLP_NDEL)]
+        act, Y, work = self.work
+        self._forward(X, Y, act)
+        self._backward(X, act, Y, T, work)
         self.step_no += 1
         self._adam(self.step_no, lr)
-        return loss
+        # read last: the update is queued before the host waits for the loss
+        return float(self.loss.item())
 
     def weights_bf16(self):
         return self.w.cpu().numpy().view(np.uint16).copy()
