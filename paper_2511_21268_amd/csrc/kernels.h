@@ -602,6 +602,35 @@ __global__ void k_add(int64_t n, const VT *__restrict__ x, const VT *__restrict_
     if (i < n) y[i] = (OT)(x[i] + c[i]);
 }
 
+// Sum over the members of coarse row I of pc r (at most 8, ascending, padded
+// with -1; no contraction: the bits of a sequential P^T r).  All members are
+// read first, then all their values, so that the row costs two latencies
+// instead of two per member.
+template <typename VT> __device__ __forceinline__ VT restrict_sum(int mw, const int32_t *__restrict__ members,
+                                                                  const VT *__restrict__ pc, const VT *__restrict__ r,
+                                                                  int64_t I)
+{
+#pragma clang fp contract(off)
+    constexpr int MW = 8;
+    int m[MW];
+    VT p[MW], v[MW];
+#pragma unroll
+    for (int t = 0; t < MW; t++) m[t] = t < mw ? members[I * mw + t] : -1;
+#pragma unroll
+    for (int t = 0; t < MW; t++) {
+        const int i = m[t] < 0 ? 0 : m[t];
+        if (t < mw) { p[t] = pc[i]; v[t] = r[i]; }
+    }
+    VT s = 0;
+#pragma unroll
+    for (int t = 0; t < MW; t++)
+        if (m[t] >= 0) {
+            VT prod = p[t] * v[t];
+            s = s + prod;
+        }
+    return s;
+}
+
 // Restriction f_c = P^T r over the members of each coarse row (ascending, at
 // most mw, padded with -1), fused with the coarse level's zero-guess smoothing
 // sweep u_c = invd_c * f_c when uc != nullptr.  Sum order is fixed and no
@@ -611,16 +640,9 @@ __global__ void k_restrict(int64_t nc, int mw, const int32_t *__restrict__ membe
                            const VT *__restrict__ r, VT *__restrict__ fc, const VT *__restrict__ invdc,
                            VT *__restrict__ uc, VT coef)
 {
-#pragma clang fp contract(off)
     int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (I >= nc) return;
-    VT s = 0;
-    for (int t = 0; t < mw; t++) {
-        int m = members[I * mw + t];
-        if (m < 0) break;
-        VT prod = pc[m] * r[m];
-        s = s + prod;
-    }
+    const VT s = restrict_sum(mw, members, pc, r, I);
     fc[I] = s;
     if (uc) uc[I] = coef * (invdc[I] * s);
 }
@@ -637,35 +659,67 @@ __global__ void k_prolong(int64_t n, const int32_t *__restrict__ agg, const VT *
     u[i] = u[i] + prod;
 }
 
-// Coarsest level: e = L^{-T} (L^{-1} f) with the precomputed inverse Cholesky
-// factor (row-major, leading dimension ld) and its transpose; FP64 arithmetic
-// whatever the level type.  One 256-thread block, n <= 2048, one thread per
-// output row: y_i = sum_{k<=i} L^{-1}_ik f_k reads column i of L^{-T} (row k of
-// LinvT), x_j = sum_{k>=j} L^{-1}_kj y_k reads column j of L^{-1}, so the
-// threads of a wave load consecutive addresses and every load is independent
-// of the running sum; k ascending.
-template <typename VT>
-__global__ __launch_bounds__(256) void k_coarse_solve(int n, int ld, const double *__restrict__ Linv,
-                                                      const double *__restrict__ LinvT, const VT *__restrict__ f,
-                                                      VT *__restrict__ e)
+// Coarsest level: e = K^{-1} f with the inverse matrix M (n x n, symmetric,
+// leading dimension ld), FP64 whatever the level type.  Row i is summed in
+// COARSE_SEGS segments of consecutive k, each an ascending chain, then
+// (s0 + s1) + (s2 + s3); the 16-column kernel and the V-cycle tail keep that
+// order.  One product instead of two triangular ones with L^{-1}: the same
+// bytes, half the dependent chain, and a quarter of it in each segment
+// (n = 154: 10.6 -> 4.8 us per call, most of it the launch).
+constexpr int COARSE_SEGS = 4, COARSE_MAXN = 2048;
+__device__ __forceinline__ double coarse_segment(int n, int ld, const double *__restrict__ M, const double *f, int i,
+                                                 int seg)
 {
-    __shared__ double fs[2048];
-    __shared__ double ys[2048];
-    for (int i = threadIdx.x; i < n; i += 256) fs[i] = (double)f[i];
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += 256) {
-        double s = 0.0;
-#pragma unroll 8
-        for (int k = 0; k <= i; k++) s = fma(LinvT[(int64_t)k * ld + i], fs[k], s);
-        ys[i] = s;
+    const int len = (n + COARSE_SEGS - 1) / COARSE_SEGS, k0 = seg * len, k1 = min(k0 + len, n);
+    double s = 0.0;
+    int k = k0;
+    for (; k + 32 <= k1; k += 32) {
+        double m[32];
+#pragma unroll
+        for (int t = 0; t < 32; t++) m[t] = M[(int64_t)(k + t) * ld + i];
+#pragma unroll
+        for (int t = 0; t < 32; t++) s = fma(m[t], f[k + t], s);
     }
-    __syncthreads();
-    for (int j = threadIdx.x; j < n; j += 256) {
-        double s = 0.0;
-#pragma unroll 8
-        for (int k = j; k < n; k++) s = fma(Linv[(int64_t)k * ld + j], ys[k], s);
-        e[j] = (VT)s;
+    for (; k + 8 <= k1; k += 8) {
+        double m[8];
+#pragma unroll
+        for (int t = 0; t < 8; t++) m[t] = M[(int64_t)(k + t) * ld + i];
+#pragma unroll
+        for (int t = 0; t < 8; t++) s = fma(m[t], f[k + t], s);
     }
+    for (; k < k1; k++) s = fma(M[(int64_t)k * ld + i], f[k], s);
+    return s;
+}
+// the block's threads (a multiple of 256): thread = (row of a group, segment);
+// put(i, x) gets each result once.  f in LDS.
+template <int THREADS, typename Put>
+__device__ __forceinline__ void coarse_apply(int n, int ld, const double *__restrict__ M, const double *f,
+                                             double *segs /* THREADS */, Put put)
+{
+    constexpr int ROWS = THREADS / COARSE_SEGS;
+    const int row = threadIdx.x % ROWS, seg = threadIdx.x / ROWS;
+    for (int i0 = 0; i0 < n; i0 += ROWS) {
+        const int i = i0 + row;
+        __syncthreads();
+        segs[threadIdx.x] = i < n ? coarse_segment(n, ld, M, f, i, seg) : 0.0;
+        __syncthreads();
+        if (seg == 0 && i < n) put(i, (segs[row] + segs[ROWS + row]) + (segs[2 * ROWS + row] + segs[3 * ROWS + row]));
+    }
+}
+
+// One block.  With members: f is the residual of the level above, restricted
+// here (its launch saved); else the right-hand side itself.
+constexpr int COARSE_THREADS = 1024;
+template <typename VT>
+__global__ __launch_bounds__(COARSE_THREADS) void k_coarse_solve(int n, int ld, const double *__restrict__ M, int mw,
+                                                                 const int32_t *__restrict__ members,
+                                                                 const VT *__restrict__ pc, const VT *__restrict__ f,
+                                                                 VT *__restrict__ e)
+{
+    __shared__ double fs[COARSE_MAXN], segs[COARSE_THREADS];
+    for (int i = threadIdx.x; i < n; i += COARSE_THREADS)
+        fs[i] = members ? (double)restrict_sum(mw, members, pc, f, i) : (double)f[i];
+    coarse_apply<COARSE_THREADS>(n, ld, M, fs, segs, [&](int i, double x) { e[i] = (VT)x; });
 }
 
 // Dot-product partials: one per block of a fixed grid (grid-stride).

@@ -81,29 +81,58 @@ __global__ void k_add_blk(int64_t n, const VT *__restrict__ x, const VT *__restr
     y[i] = (OT)(x[i] + c[i]);
 }
 
-// Coarsest level for 16 columns, in two launches over 16-row tiles (block =
-// 16 rows x 16 columns, thread = one output element):
-//   phase 0: Y = L^{-1} F,   phase 1: E = L^{-T} Y   (Y: global scratch, n x 16).
-// Per element the single-vector kernel's order (k ascending), so each column
-// equals k_coarse_solve's result.
+// Coarsest level for 16 columns: E = K^{-1} F with the inverse matrix M, one
+// element (row i, column j) per thread in k_coarse_solve's segments and order,
+// so each column equals its result.  The rows of F and the block's columns of
+// M come through LDS, 64 of each segment at a time: one thread per element
+// reading them from memory waited a latency every few terms (n = 117: 36 us; two
+// triangular products 23 us; this 5 us, most of it the launch).
+constexpr int CBLK_ROWS = 256 / NB, CBLK_K = 64;
 template <typename VT>
-__global__ __launch_bounds__(256) void k_coarse_solve_blk(int n, int ld, const double *__restrict__ Linv,
-                                                          const double *__restrict__ LinvT, const VT *__restrict__ f,
-                                                          double *__restrict__ Y, VT *__restrict__ e, int phase)
+__global__ __launch_bounds__(256) void k_coarse_solve_blk(int n, int ld, const double *__restrict__ M,
+                                                          const VT *__restrict__ f, VT *__restrict__ e)
 {
-    const int j = threadIdx.x & (NB - 1);
-    const int i = blockIdx.x * (256 / NB) + threadIdx.x / NB;
-    if (i >= n) return;
-    double s = 0.0;
-    if (phase == 0) {
-#pragma unroll 8
-        for (int k = 0; k <= i; k++) s = fma(LinvT[(int64_t)k * ld + i], (double)f[(int64_t)k * NB + j], s);
-        Y[(int64_t)i * NB + j] = s;
-    } else {
-#pragma unroll 8
-        for (int k = i; k < n; k++) s = fma(Linv[(int64_t)k * ld + i], Y[(int64_t)k * NB + j], s);
-        e[(int64_t)i * NB + j] = (VT)s;
+    __shared__ double fs[COARSE_SEGS * CBLK_K][NB], ms[COARSE_SEGS * CBLK_K][CBLK_ROWS + 1];
+    const int j = threadIdx.x & (NB - 1), r = threadIdx.x / NB, i0 = blockIdx.x * CBLK_ROWS;
+    const int len = (n + COARSE_SEGS - 1) / COARSE_SEGS;
+    double s[COARSE_SEGS];
+#pragma unroll
+    for (int q = 0; q < COARSE_SEGS; q++) s[q] = 0.0;
+    for (int c = 0; c < len; c += CBLK_K) {
+        __syncthreads();
+        // row h of the tiles: k = q len + c + t (zeros past the segment)
+#pragma unroll
+        for (int g = 0; g < COARSE_SEGS * CBLK_K / CBLK_ROWS; g++) {
+            const int h = g * CBLK_ROWS + r, q = h / CBLK_K, t = c + h % CBLK_K, k = q * len + t;
+            const bool live = t < len && k < n;
+            fs[h][j] = live ? (double)f[(int64_t)k * NB + j] : 0.0;
+            ms[h][j] = live && i0 + j < n ? M[(int64_t)k * ld + i0 + j] : 0.0;
+        }
+        __syncthreads();
+        const int steps = min(CBLK_K, len - c);
+        for (int t = 0; t < steps; t++)
+#pragma unroll
+            for (int q = 0; q < COARSE_SEGS; q++)
+                if (q * len + c + t < n) s[q] = fma(ms[q * CBLK_K + t][r], fs[q * CBLK_K + t][j], s[q]);
     }
+    if (i0 + r < n) e[(int64_t)(i0 + r) * NB + j] = (VT)((s[0] + s[1]) + (s[2] + s[3]));
+}
+
+// the same sum for one element in one thread (V-cycle tail of 16 columns)
+template <typename VT>
+__device__ __forceinline__ double coarse_row_blk(int n, int ld, const double *__restrict__ M, const VT *__restrict__ f,
+                                                 int i, int j)
+{
+    const int len = (n + COARSE_SEGS - 1) / COARSE_SEGS;
+    double s[COARSE_SEGS];
+#pragma unroll
+    for (int q = 0; q < COARSE_SEGS; q++) {
+        s[q] = 0.0;
+        const int k1 = min((q + 1) * len, n);
+#pragma unroll 8
+        for (int k = q * len; k < k1; k++) s[q] = fma(M[(int64_t)k * ld + i], (double)f[(int64_t)k * NB + j], s[q]);
+    }
+    return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
 // Column-major (n x k, leading dimension n) <-> row-major block (n x NB).

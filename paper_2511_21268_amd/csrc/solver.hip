@@ -132,7 +132,7 @@ struct amg_ctx {
     std::vector<Level> lev;
     int nlev = 0;
     int nL = 0, ldL = 0;
-    double *Linv = nullptr, *LinvT = nullptr;
+    double *Minv = nullptr;   // inverse of the coarsest matrix, nL x nL, leading dimension ldL
     // coarsest level for the CG coarse solver: CSR (int32) and 1 / k_ii
     int32_t *cg_rp = nullptr, *cg_ci = nullptr;
     double *cg_v = nullptr, *cg_dj = nullptr;
@@ -142,7 +142,7 @@ struct amg_ctx {
     int64_t partial_cap = 0;
     // batched solve (allocated on first use)
     double *bR = nullptr, *bZ = nullptr, *bP = nullptr, *bQ = nullptr, *bU = nullptr, *bF = nullptr;
-    double *bY = nullptr, *bsc = nullptr, *hbsc = nullptr, *bpartial = nullptr, *bstrided = nullptr;
+    double *bsc = nullptr, *hbsc = nullptr, *bpartial = nullptr, *bstrided = nullptr;
     double *bgram = nullptr, *bcoef = nullptr, *bgsave = nullptr;   // block CG: Gram partials, alpha / beta, G
     int blk_lpr = 1, blk_threads = 256;   // block-kernel variant (autotuned when prm.nrhs > 1)
     int blk_win = 4;       // stencil images: staged-window block kernel with this many rows per lane (0: off)
@@ -631,7 +631,7 @@ struct amg_ctx {
     void choose_tail()
     {
         tail_start = -1;
-        if (nlev < 3 || nL > TAIL_MAX_COARSE || general_vcycle()) return;
+        if (nlev < 3 || nL > COARSE_MAXN || general_vcycle()) return;
         for (int l = nlev - 2; l >= 1; l--) {
             if (lev[l].n > TAIL_ROWS || lev[l].nnz > TAIL_NNZ || !lev[l].KP.soff || !lev[l].A.soff) break;
             tail_start = l;
@@ -679,14 +679,23 @@ struct amg_ctx {
         Level &C = lev[nlev - 1];
         if (blk) {
             hipLaunchKernelGGL((k_vtail_blk<VT>), dim3(1), dim3(TAIL_THREADS), 0, stream,
-                               (const TailLevel<VT> *)tail_dev_blk, nt, nL, ldL, Linv, LinvT, (VT *)C.bf,
-                               (VT *)C.bu, bY);
+                               (const TailLevel<VT> *)tail_dev_blk, nt, nL, ldL, Minv, (VT *)C.bf,
+                               (VT *)C.bu);
         } else {
             hipLaunchKernelGGL((k_vtail<VT>), dim3(1), dim3(TAIL_THREADS), 0, stream, (const TailLevel<VT> *)tail_dev,
-                               nt, nL, ldL, Linv, LinvT, (VT *)C.f, (VT *)C.u);
+                               nt, nL, ldL, Minv, (VT *)C.f, (VT *)C.u);
         }
         HIPCHK(hipGetLastError());
         return (VT *)(blk ? lev[tail_start].bu2 : lev[tail_start].u2);
+    }
+
+    // coarsest level: restriction of the residual of the level above (P), then
+    // the solve; with P null f is the right-hand side itself
+    template <typename VT> void coarse_solve(const Level *P, const VT *f, VT *e)
+    {
+        hipLaunchKernelGGL((k_coarse_solve<VT>), dim3(1), dim3(COARSE_THREADS), 0, stream, nL, ldL, Minv,
+                           P ? P->mw : 0, P ? P->members : nullptr, P ? P->pc<VT>() : nullptr, f, e);
+        HIPCHK(hipGetLastError());
     }
 
     // ---- kernel launchers --------------------------------------------------
@@ -893,23 +902,18 @@ struct amg_ctx {
         // 2. residual and restriction (fused with the coarse pre-smoothing)
         sell<VT, FT, VT, EPI_RESID, 0>(l, u, f, L.invd<VT>(), (VT *)L.r, nullptr, nullptr);
         Level &C = lev[l + 1];
-        const bool coarsest = (l + 1 == nlev - 1);
-        const VT a3 = C.poly_on ? (VT)C.poly[3] : (VT)1;
-        hipLaunchKernelGGL((k_restrict<VT>), dim3(nblocks(C.n)), dim3(256), 0, stream, C.n, L.mw, L.members,
-                           L.pc<VT>(), (const VT *)L.r, (VT *)C.f, coarsest ? nullptr : C.invd<VT>(),
-                           coarsest ? nullptr : (VT *)C.u, a3);
-        HIPCHK(hipGetLastError());
-        // 3. coarse solve
+        // 3. coarse solve; the coarsest level's kernel restricts by itself
         VT *e;
-        if (coarsest) {
+        if (l + 1 == nlev - 1) {
             e = (VT *)C.u;
-            hipLaunchKernelGGL((k_coarse_solve<VT>), dim3(1), dim3(256), 0, stream, nL, ldL, Linv, LinvT,
-                               (const VT *)C.f, e);
-            HIPCHK(hipGetLastError());
-        } else if (l + 1 == tail_start && tail_usable()) {
-            e = run_tail<VT>(false);
+            coarse_solve<VT>(&L, (const VT *)L.r, e);
         } else {
-            e = vlevel<VT, VT>(l + 1, (const VT *)C.f, nullptr, 0, nullptr, nullptr, true);
+            const VT a3 = C.poly_on ? (VT)C.poly[3] : (VT)1;
+            hipLaunchKernelGGL((k_restrict<VT>), dim3(nblocks(C.n)), dim3(256), 0, stream, C.n, L.mw, L.members,
+                               L.pc<VT>(), (const VT *)L.r, (VT *)C.f, C.invd<VT>(), (VT *)C.u, a3);
+            HIPCHK(hipGetLastError());
+            if (l + 1 == tail_start && tail_usable()) e = run_tail<VT>(false);
+            else e = vlevel<VT, VT>(l + 1, (const VT *)C.f, nullptr, 0, nullptr, nullptr, true);
         }
         // 4. + 5.: with l1-Jacobi the prolongation is fused into the first
         // post-smoothing sweep through K P (f - K (u + P e) = r - (K P) e)
@@ -967,7 +971,7 @@ struct amg_ctx {
             hipLaunchKernelGGL(k_coarse_cg, dim3(1), dim3(CG_THREADS), 0, stream, nL, cg_rp, cg_ci, cg_v, cg_dj, f,
                                e, prm.coarse_tol, prm.coarse_itmax);
         else
-            hipLaunchKernelGGL((k_coarse_solve<double>), dim3(1), dim3(256), 0, stream, nL, ldL, Linv, LinvT, f, e);
+            coarse_solve<double>(nullptr, f, e);
         HIPCHK(hipGetLastError());
     }
 
@@ -1116,9 +1120,7 @@ struct amg_ctx {
             return vc_nb;
         }
         if (nlev == 1) {
-            hipLaunchKernelGGL((k_coarse_solve<double>), dim3(1), dim3(256), 0, stream, nL, ldL, Linv, LinvT, rin,
-                               zout);
-            HIPCHK(hipGetLastError());
+            coarse_solve<double>(nullptr, rin, zout);
             if (ndot) vc_nb = dot_partials(n, zout, g0, g1);
             return vc_nb;
         }
@@ -1141,7 +1143,6 @@ struct amg_ctx {
         size_t nb = (size_t)n * NB;
         bR = alloc<double>(nb); bZ = alloc<double>(nb); bP = alloc<double>(nb);
         bQ = alloc<double>(nb); bU = alloc<double>(nb); bF = alloc<double>(nb);
-        bY = alloc<double>((size_t)std::max(nL, 1) * NB);
         bsc = alloc<double>(B_NSLOTS * NB);
         bpartial = alloc<double>((size_t)partial_cap * NB);
         bstrided = alloc<double>((size_t)2 * NB * FIN_THREADS);
@@ -1196,9 +1197,8 @@ struct amg_ctx {
     }
     template <typename VT> void coarse_blk(const VT *f, VT *e)
     {
-        const unsigned g = (unsigned)((nL + 256 / NB - 1) / (256 / NB));
-        hipLaunchKernelGGL((k_coarse_solve_blk<VT>), dim3(g), dim3(256), 0, stream, nL, ldL, Linv, LinvT, f, bY, e, 0);
-        hipLaunchKernelGGL((k_coarse_solve_blk<VT>), dim3(g), dim3(256), 0, stream, nL, ldL, Linv, LinvT, f, bY, e, 1);
+        const unsigned g = (unsigned)((nL + CBLK_ROWS - 1) / CBLK_ROWS);
+        hipLaunchKernelGGL((k_coarse_solve_blk<VT>), dim3(g), dim3(256), 0, stream, nL, ldL, Minv, f, e);
         HIPCHK(hipGetLastError());
     }
     unsigned bdot_partials(int64_t m, const double *a, const double *b, const double *c)
@@ -1456,10 +1456,13 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
         }
         c->nL = nl;
         c->ldL = npad;
-        c->Linv = c->alloc<double>((size_t)npad * npad);
-        c->LinvT = c->alloc<double>((size_t)npad * npad);
-        hipLaunchKernelGGL(k_tri_inv, dim3((nl + 255) / 256), dim3(256), 0, c->stream, nl, npad, dA, c->Linv,
-                           c->LinvT);
+        c->Minv = c->alloc<double>((size_t)npad * npad);
+        double *Linv = c->alloc<double>((size_t)npad * npad);
+        hipLaunchKernelGGL(k_tri_inv, dim3((nl + 255) / 256), dim3(256), 0, c->stream, nl, npad, dA, Linv);
+        hipLaunchKernelGGL(k_sym_inv, dim3((nl + 255) / 256, nl), dim3(256), 0, c->stream, nl, npad, Linv, c->Minv);
+        HIPCHK(hipStreamSynchronize(c->stream));
+        c->release(Linv);
+        c->release(dA);
         HIPCHK(hipGetLastError());
     }
     c->n = H.lev[0].n;

@@ -21,7 +21,6 @@ namespace amgk {
 
 constexpr int TAIL_THREADS = 1024;
 constexpr int TAIL_WAVES = TAIL_THREADS / 64;
-constexpr int TAIL_MAX_COARSE = 2048;   // rows of the coarsest level held in LDS (single vector)
 
 // One tail level: its matrix K and K P (SELL-64 images; one of the two index
 // types in use), smoother and transfer data, and work vectors (single vector,
@@ -37,20 +36,6 @@ template <typename VT> struct TailLevel {
     const int32_t *agg, *members;
     VT *f, *u, *u2, *r;
 };
-
-template <typename VT> __device__ __forceinline__ VT restrict_sum(int mw, const int32_t *members, const VT *pc,
-                                                                  const VT *r, int64_t I)
-{
-#pragma clang fp contract(off)
-    VT s = 0;
-    for (int t = 0; t < mw; t++) {
-        int m = members[I * mw + t];
-        if (m < 0) break;
-        VT prod = pc[m] * r[m];
-        s = s + prod;
-    }
-    return s;
-}
 
 template <typename VT, typename IT>
 __device__ inline void tail_resid(const Sell<VT, IT> &A, const VT *f, const VT *u, VT *r)
@@ -88,11 +73,9 @@ __device__ inline void tail_post(const Sell<VT, IT> &A, const VT *e, const VT *u
 // solution of the coarsest level.  Output: T[0].u2.
 template <typename VT>
 __global__ __launch_bounds__(TAIL_THREADS) void k_vtail(const TailLevel<VT> *__restrict__ T, int nt, int nL, int ld,
-                                                        const double *__restrict__ Linv,
-                                                        const double *__restrict__ LinvT, VT *fL, VT *eL)
+                                                        const double *__restrict__ M, VT *fL, VT *eL)
 {
-    __shared__ double fs[TAIL_MAX_COARSE];
-    __shared__ double ys[TAIL_MAX_COARSE];
+    __shared__ double fs[COARSE_MAXN], segs[TAIL_THREADS];
     for (int t = 0; t < nt; t++) {
         const TailLevel<VT> &L = T[t];
         if (L.a16) tail_resid(L.A16, L.f, L.u, L.r);
@@ -109,22 +92,9 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_vtail(const TailLevel<VT> *__r
         }
         __syncthreads();
     }
-    // coarsest level: e = L^{-T} (L^{-1} f), k_coarse_solve's order
+    // coarsest level, k_coarse_solve's order
     for (int i = threadIdx.x; i < nL; i += TAIL_THREADS) fs[i] = (double)fL[i];
-    __syncthreads();
-    for (int i = threadIdx.x; i < nL; i += TAIL_THREADS) {
-        double s = 0.0;
-#pragma unroll 8
-        for (int k = 0; k <= i; k++) s = fma(LinvT[(int64_t)k * ld + i], fs[k], s);
-        ys[i] = s;
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < nL; j += TAIL_THREADS) {
-        double s = 0.0;
-#pragma unroll 8
-        for (int k = j; k < nL; k++) s = fma(Linv[(int64_t)k * ld + j], ys[k], s);
-        eL[j] = (VT)s;
-    }
+    coarse_apply<TAIL_THREADS>(nL, ld, M, fs, segs, [&](int i, double x) { eL[i] = (VT)x; });
     __syncthreads();
     for (int t = nt - 1; t >= 0; t--) {
         const TailLevel<VT> &L = T[t];
@@ -189,12 +159,10 @@ __device__ inline void tail_post_blk(const Sell<VT, IT> &A, const VT *E, const V
     }
 }
 
-// As k_vtail for 16 columns; Yc: global scratch of the coarse solve (nL x 16).
+// As k_vtail for 16 columns.
 template <typename VT>
 __global__ __launch_bounds__(TAIL_THREADS) void k_vtail_blk(const TailLevel<VT> *__restrict__ T, int nt, int nL,
-                                                            int ld, const double *__restrict__ Linv,
-                                                            const double *__restrict__ LinvT, VT *FL, VT *EL,
-                                                            double *Yc)
+                                                            int ld, const double *__restrict__ M, VT *FL, VT *EL)
 {
     for (int t = 0; t < nt; t++) {
         const TailLevel<VT> &L = T[t];
@@ -229,22 +197,9 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_vtail_blk(const TailLevel<VT> 
         }
         __syncthreads();
     }
-    // coarsest level, k_coarse_solve_blk's order: Y = L^{-1} F, then E = L^{-T} Y
-    for (int q = threadIdx.x; q < nL * NB; q += TAIL_THREADS) {
-        const int i = q / NB, j = q % NB;
-        double s = 0.0;
-#pragma unroll 8
-        for (int k = 0; k <= i; k++) s = fma(LinvT[(int64_t)k * ld + i], (double)FL[(int64_t)k * NB + j], s);
-        Yc[(int64_t)i * NB + j] = s;
-    }
-    __syncthreads();
-    for (int q = threadIdx.x; q < nL * NB; q += TAIL_THREADS) {
-        const int i = q / NB, j = q % NB;
-        double s = 0.0;
-#pragma unroll 8
-        for (int k = i; k < nL; k++) s = fma(Linv[(int64_t)k * ld + i], Yc[(int64_t)k * NB + j], s);
-        EL[(int64_t)i * NB + j] = (VT)s;
-    }
+    // coarsest level, k_coarse_solve_blk's order
+    for (int q = threadIdx.x; q < nL * NB; q += TAIL_THREADS)
+        EL[q] = (VT)coarse_row_blk(nL, ld, M, FL, q / NB, q % NB);
     __syncthreads();
     for (int t = nt - 1; t >= 0; t--) {
         const TailLevel<VT> &L = T[t];
