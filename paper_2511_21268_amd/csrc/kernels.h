@@ -67,7 +67,9 @@ constexpr int RED_THREADS = 256;
 enum Epi { EPI_SPMV = 0, EPI_RESID = 1, EPI_SMOOTH = 2, EPI_POLY = 3, EPI_ADD = 4 };
 
 // scalar slots of the solver's device scalar array
-enum Slot { S_RZ = 0, S_PQ, S_RR, S_ALPHA, S_BETA, S_PR, S_ZQ, S_FF, S_FLAG, S_TMP, S_NSLOTS = 16 };
+// (S_RZN: the newest (r, z); S_RZ follows it in the next iteration's alpha, so
+// that no kernel writes a scalar that its other blocks read)
+enum Slot { S_RZ = 0, S_PQ, S_RR, S_ALPHA, S_BETA, S_PR, S_ZQ, S_FF, S_FLAG, S_TMP, S_TMP1, S_RZN, S_NSLOTS = 16 };
 enum FinOp { FIN_STORE = 0, FIN_PQ_CG, FIN_PQ_FCG, FIN_RZ_CG, FIN_ZQ_FCG, FIN_RZ0 };
 
 __device__ inline double wave_sum(double v)
@@ -736,15 +738,62 @@ static __global__ void k_dot2(int64_t n, const double *__restrict__ a, const dou
     if (threadIdx.x == 0) { partial[2 * blockIdx.x] = t0; partial[2 * blockIdx.x + 1] = t1; }
 }
 
-// u += alpha p ; r -= alpha q ; partials of (r, r).  Skipped once a breakdown
-// flag is set (so u keeps the last valid iterate).
-static __global__ void k_cg_update(int64_t n, const double *__restrict__ sc, double *__restrict__ u,
-                            double *__restrict__ r, const double *__restrict__ p, const double *__restrict__ q,
-                            double *__restrict__ partial)
+// Final sums of at most FIN_THREADS partials (two dots) in the order of
+// k_finalize, formed by every 256-thread block that needs the scalars itself:
+// each partial is one of its threads' sums, the butterflies and the order of the
+// waves are its own.  Valid in all threads.
+__device__ __forceinline__ void sum_partials(const double *__restrict__ partial, int nblk, double &t0, double &t1,
+                                             double *lds /* 2 * FIN_THREADS / 64 */)
 {
-    __shared__ double lds[8];
-    const bool skip = sc[S_FLAG] != 0.0;
-    const double alpha = sc[S_ALPHA];
+    constexpr int NW = FIN_THREADS / 64;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int g = 0; g < NW / 4; g++) {
+        const int w = 4 * g + wid, b = w * 64 + lane;
+        const double s0 = wave_sum(b < nblk ? partial[2 * b] : 0.0), s1 = wave_sum(b < nblk ? partial[2 * b + 1] : 0.0);
+        if (lane == 0) { lds[w] = s0; lds[NW + w] = s1; }
+    }
+    __syncthreads();
+    t0 = t1 = 0.0;
+    for (int w = 0; w < NW; w++) { t0 += lds[w]; t1 += lds[NW + w]; }
+}
+
+// The scalar recurrences of CG / FCG(1) from the final sums (breakdown: the
+// flag set, the scalar left).
+__device__ __forceinline__ bool cg_bad(double t) { return !(t > 0.0) || !isfinite(t); }
+
+// u += alpha p ; r -= alpha q ; partials of (r, r); with u0 the first smoothing
+// step of the next V-cycle from zero, u0 = coef D^{-1} r, whose kernel it
+// saves.  Skipped once a breakdown flag is set (so u keeps the last valid
+// iterate).  pq != NULL: npq partials of (p, q) and (p, r), from which every
+// block forms alpha itself and block 0 stores the scalars (no launch between
+// the product and this kernel; a 1,024-row solve 58 -> 38 us per iteration with
+// all of these); else alpha was stored by k_finalize.
+template <typename VT>
+__global__ __launch_bounds__(256) void k_cg_update(int64_t n, double *__restrict__ sc, const double *__restrict__ pq,
+                                                   int npq, int op, double *__restrict__ u, double *__restrict__ r,
+                                                   const double *__restrict__ p, const double *__restrict__ q,
+                                                   double *__restrict__ partial, const VT *__restrict__ invd,
+                                                   VT *__restrict__ u0, VT coef)
+{
+    __shared__ double lds[2 * FIN_THREADS / 64];
+    bool skip = sc[S_FLAG] != 0.0;
+    double alpha = sc[S_ALPHA];
+    if (pq) {
+        double t0, t1;
+        sum_partials(pq, npq, t0, t1, lds);
+        const double rz = sc[S_RZN];
+        const bool bad = cg_bad(t0);
+        if (bad) skip = true;
+        else alpha = (op == FIN_PQ_FCG ? t1 : rz) / t0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            sc[S_PQ] = t0;
+            if (op == FIN_PQ_FCG) sc[S_PR] = t1;
+            else sc[S_RZ] = rz;
+            if (bad) { if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 1.0; }
+            else sc[S_ALPHA] = alpha;
+        }
+    }
     double s = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         double ri = r[i];
@@ -753,17 +802,37 @@ static __global__ void k_cg_update(int64_t n, const double *__restrict__ sc, dou
             ri = fma(-alpha, q[i], ri);
             r[i] = ri;
         }
+        if (u0) u0[i] = coef * (invd[i] * (VT)ri);
         s = fma(ri, ri, s);
     }
+    __syncthreads();
     double t = block_sum(s, lds);
     if (threadIdx.x == 0) { partial[2 * blockIdx.x] = t; partial[2 * blockIdx.x + 1] = 0.0; }
 }
 
-// p = z + beta p
-static __global__ void k_cg_pupdate(int64_t n, const double *__restrict__ sc, const double *__restrict__ z,
-                             double *__restrict__ p)
+// p = z + beta p.  rz != NULL: nrz partials of the V-cycle's dot, from which
+// every block forms beta itself and block 0 stores the scalars; else beta was
+// stored by k_finalize.
+static __global__ __launch_bounds__(256) void k_cg_pupdate(int64_t n, double *__restrict__ sc,
+                                                           const double *__restrict__ rz, int nrz, int op,
+                                                           const double *__restrict__ z, double *__restrict__ p)
 {
-    const double beta = sc[S_BETA];
+    __shared__ double lds[2 * FIN_THREADS / 64];
+    double beta = sc[S_BETA];
+    if (rz) {
+        double t0, t1;
+        sum_partials(rz, nrz, t0, t1, lds);
+        const bool bad = op == FIN_ZQ_FCG ? !isfinite(t0) : cg_bad(t0);
+        if (!bad) beta = op == FIN_ZQ_FCG ? -t0 / sc[S_PQ] : t0 / sc[S_RZ];
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if (op == FIN_ZQ_FCG) sc[S_ZQ] = t0;
+            if (bad) { if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 2.0; }
+            else {
+                sc[S_BETA] = beta;
+                if (op != FIN_ZQ_FCG) sc[S_RZN] = t0;
+            }
+        }
+    }
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         p[i] = fma(beta, p[i], z[i]);
 }
@@ -782,9 +851,10 @@ __global__ void k_fill(int64_t n, T v, T *__restrict__ d)
 }
 
 // Final sum of the block partials (two dots) in index order, then the scalar
-// recurrences of CG / FCG(1) on the device.
-static __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double *__restrict__ partial, int nblk, double *sc,
-                                                           int op, int slot)
+// recurrences of CG / FCG(1) on the device.  host (mapped, may be NULL): the
+// scalars that the host's stopping test reads, written there directly.
+static __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double *__restrict__ partial, int nblk,
+                                                                 double *sc, int op, int slot, double *host)
 {
     __shared__ double lds[2 * FIN_THREADS / 64];
     double s0 = 0.0, s1 = 0.0;
@@ -794,24 +864,26 @@ static __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double *_
     switch (op) {
     case FIN_STORE:
         sc[slot] = t0;
-        if (slot + 1 < S_NSLOTS && slot == S_TMP) sc[slot + 1] = t1;
+        if (slot == S_TMP) sc[S_TMP1] = t1;
+        if (host) { host[slot] = t0; host[S_FLAG] = sc[S_FLAG]; }
         break;
     case FIN_PQ_CG:
     case FIN_PQ_FCG: {
         sc[S_PQ] = t0;
         if (op == FIN_PQ_FCG) sc[S_PR] = t1;
-        double num = op == FIN_PQ_FCG ? t1 : sc[S_RZ];
-        if (!(t0 > 0.0) || !isfinite(t0)) { if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 1.0; }
-        else sc[S_ALPHA] = num / t0;
+        const double rz = sc[S_RZN];
+        sc[S_RZ] = rz;
+        if (cg_bad(t0)) { if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 1.0; }
+        else sc[S_ALPHA] = (op == FIN_PQ_FCG ? t1 : rz) / t0;
         break;
     }
     case FIN_RZ0:
-        sc[S_RZ] = t0;
-        if (!(t0 > 0.0) || !isfinite(t0)) { if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 2.0; }
+        sc[S_RZ] = sc[S_RZN] = t0;
+        if (cg_bad(t0)) { if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 2.0; }
         break;
     case FIN_RZ_CG:
-        if (!(t0 > 0.0) || !isfinite(t0)) { if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 2.0; }
-        else { sc[S_BETA] = t0 / sc[S_RZ]; sc[S_RZ] = t0; }
+        if (cg_bad(t0)) { if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 2.0; }
+        else { sc[S_BETA] = t0 / sc[S_RZ]; sc[S_RZN] = t0; }
         break;
     case FIN_ZQ_FCG:
         sc[S_ZQ] = t0;

@@ -26,35 +26,38 @@ __global__ void k_scale_blk(int64_t n, const VT *__restrict__ invd, const FT *__
     for (int j = 0; j < NB; j++) u[i * NB + j] = coef * (di * (VT)f[i * NB + j]);
 }
 
+// Restriction of 16 columns, one element (coarse row I, column j) per thread:
+// consecutive threads on consecutive addresses, the members read together.
 // coef == 1 keeps the l1 sweep's bits: 1 * (d * f) == d * f exactly.
 template <typename VT>
-__global__ void k_restrict_blk(int64_t nc, int mw, const int32_t *__restrict__ members, const VT *__restrict__ pc,
-                               const VT *__restrict__ r, VT *__restrict__ fc, const VT *__restrict__ invdc,
-                               VT *__restrict__ uc, VT coef)
+__global__ __launch_bounds__(256) void k_restrict_blk(int64_t nc, int mw, const int32_t *__restrict__ members,
+                                                      const VT *__restrict__ pc, const VT *__restrict__ r,
+                                                      VT *__restrict__ fc, const VT *__restrict__ invdc,
+                                                      VT *__restrict__ uc, VT coef)
 {
 #pragma clang fp contract(off)
-    int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, I = e / NB;
+    const int j = (int)(e % NB);
     if (I >= nc) return;
-    VT s[NB];
+    constexpr int MW = 8;
+    int m[MW];
+    VT p[MW], v[MW];
 #pragma unroll
-    for (int j = 0; j < NB; j++) s[j] = 0;
-    for (int t = 0; t < mw; t++) {
-        int m = members[I * mw + t];
-        if (m < 0) break;
-        const VT pm = pc[m];
+    for (int t = 0; t < MW; t++) m[t] = t < mw ? members[I * mw + t] : -1;
 #pragma unroll
-        for (int j = 0; j < NB; j++) {
-            VT prod = pm * r[(int64_t)m * NB + j];
-            s[j] = s[j] + prod;
+    for (int t = 0; t < MW; t++) {
+        const int64_t i = m[t] < 0 ? 0 : m[t];
+        if (t < mw) { p[t] = pc[i]; v[t] = r[i * NB + j]; }
+    }
+    VT s = 0;
+#pragma unroll
+    for (int t = 0; t < MW; t++)
+        if (m[t] >= 0) {
+            VT prod = p[t] * v[t];
+            s = s + prod;
         }
-    }
-#pragma unroll
-    for (int j = 0; j < NB; j++) fc[I * NB + j] = s[j];
-    if (uc) {
-        const VT di = invdc[I];
-#pragma unroll
-        for (int j = 0; j < NB; j++) uc[I * NB + j] = coef * (di * s[j]);
-    }
+    fc[e] = s;
+    if (uc) uc[e] = coef * (invdc[I] * s);
 }
 
 template <typename VT>
@@ -194,10 +197,14 @@ static __global__ __launch_bounds__(256) void k_dot2_blk(int64_t n, const double
     blk_col_partials(s0, s1, lds, partial);
 }
 
-// u += alpha p ; r -= alpha q for the active columns; partials of (r, r).
-static __global__ __launch_bounds__(256) void k_bcg_update(int64_t n, const double *__restrict__ sc, double *__restrict__ u,
+// u += alpha p ; r -= alpha q for the active columns; partials of (r, r); with
+// u0 the first smoothing step of the next V-cycle from zero, coef D^{-1} r (every
+// column), whose kernel it saves.
+template <typename VT>
+__global__ __launch_bounds__(256) void k_bcg_update(int64_t n, const double *__restrict__ sc, double *__restrict__ u,
                                                     double *__restrict__ r, const double *__restrict__ p,
-                                                    const double *__restrict__ q, double *__restrict__ partial)
+                                                    const double *__restrict__ q, double *__restrict__ partial,
+                                                    const VT *__restrict__ invd, VT *__restrict__ u0, VT coef)
 {
     __shared__ double lds[8 * NB];
     const int j = threadIdx.x & (NB - 1);
@@ -212,6 +219,7 @@ static __global__ __launch_bounds__(256) void k_bcg_update(int64_t n, const doub
             ri = fma(-al, q[e], ri);
             r[e] = ri;
         }
+        if (u0) u0[e] = coef * (invd[e / NB] * (VT)ri);
         s = fma(ri, ri, s);
     }
     blk_col_partials(s, 0.0, lds, partial);
@@ -243,42 +251,34 @@ static __global__ __launch_bounds__(256) void k_bfin_strided(const double *__res
 }
 
 // Final per-column sums of the partials (index order) and the scalar
-// recurrences, masks and iteration counters of the 16 independent solves.
-// With strided != nullptr the per-thread strided sums come from
-// k_bfin_strided (the same values).
-static __global__ __launch_bounds__(FIN_THREADS) void k_bfinalize(const double *__restrict__ partial, int nblk, double *sc,
-                                                           int op, double tol, const double *__restrict__ strided)
+// recurrences, masks and iteration counters of the 16 independent solves: block
+// j takes column j (one block for all columns spent 28 us in 32 butterflies
+// per wave; this 5 us, most of it the launch).  With strided != nullptr the
+// per-thread strided sums come from k_bfin_strided (the same values).  host
+// (mapped, may be NULL): the column's flags, which the host's stopping test
+// reads, written there directly.
+static __global__ __launch_bounds__(FIN_THREADS) void k_bfinalize(const double *__restrict__ partial, int nblk,
+                                                                  double *sc, int op, double tol,
+                                                                  const double *__restrict__ strided, double *host)
 {
-    // per column the order of k_finalize: thread strides, butterfly, waves in order
+    // the order of k_finalize: thread strides, butterfly, waves in order
     constexpr int NW = FIN_THREADS / 64;
-    __shared__ double lds[2 * NW * NB];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    double s0[NB], s1[NB];
-#pragma unroll
-    for (int j = 0; j < NB; j++) { s0[j] = 0.0; s1[j] = 0.0; }
+    __shared__ double lds[2 * NW];
+    const int j = blockIdx.x, t = threadIdx.x;
+    double s0 = 0.0, s1 = 0.0;
     if (strided) {
-#pragma unroll
-        for (int j = 0; j < NB; j++) {
-            s0[j] = strided[j * FIN_THREADS + threadIdx.x];
-            s1[j] = strided[(NB + j) * FIN_THREADS + threadIdx.x];
-        }
+        s0 = strided[j * FIN_THREADS + t];
+        s1 = strided[(NB + j) * FIN_THREADS + t];
     } else {
-        for (int b = threadIdx.x; b < nblk; b += FIN_THREADS)
-#pragma unroll
-            for (int j = 0; j < NB; j++) { s0[j] += partial[(2 * b) * NB + j]; s1[j] += partial[(2 * b + 1) * NB + j]; }
+#pragma unroll 4
+        for (int b = t; b < nblk; b += FIN_THREADS) {
+            s0 += partial[(2 * b) * NB + j];
+            s1 += partial[(2 * b + 1) * NB + j];
+        }
     }
-#pragma unroll
-    for (int j = 0; j < NB; j++) { s0[j] = wave_sum(s0[j]); s1[j] = wave_sum(s1[j]); }
-    if (lane == 0)
-#pragma unroll
-        for (int j = 0; j < NB; j++) { lds[wid * NB + j] = s0[j]; lds[(NW + wid) * NB + j] = s1[j]; }
-    __syncthreads();
-    // thread j: column j, its waves summed in order (the columns are independent)
-    if (threadIdx.x >= NB) return;
+    const double a = block_sum_n<NW>(s0, lds), b = block_sum_n<NW>(s1, lds + NW);
+    if (t != 0) return;
     {
-        const int j = threadIdx.x;
-        double a = 0.0, b = 0.0;
-        for (int w = 0; w < NW; w++) { a += lds[w * NB + j]; b += lds[(NW + w) * NB + j]; }
         double *F = sc + B_FLAG * NB + j, *D = sc + B_DONE * NB + j;
         switch (op) {
         case BF_FF:
@@ -319,6 +319,10 @@ static __global__ __launch_bounds__(FIN_THREADS) void k_bfinalize(const double *
             if (!isfinite(a)) *F = 2.0;
             else sc[B_BETA * NB + j] = -a / sc[B_PQ * NB + j];
             break;
+        }
+        if (host) {
+            host[B_DONE * NB + j] = *D;
+            host[B_FLAG * NB + j] = *F;
         }
     }
 }

@@ -142,7 +142,7 @@ struct amg_ctx {
     int64_t partial_cap = 0;
     // batched solve (allocated on first use)
     double *bR = nullptr, *bZ = nullptr, *bP = nullptr, *bQ = nullptr, *bU = nullptr, *bF = nullptr;
-    double *bsc = nullptr, *hbsc = nullptr, *bpartial = nullptr, *bstrided = nullptr;
+    double *bsc = nullptr, *hbsc = nullptr, *hbsc_dev = nullptr, *bpartial = nullptr, *bstrided = nullptr;
     double *bgram = nullptr, *bcoef = nullptr, *bgsave = nullptr;   // block CG: Gram partials, alpha / beta, G
     int blk_lpr = 1, blk_threads = 256;   // block-kernel variant (autotuned when prm.nrhs > 1)
     int blk_win = 4;       // stencil images: staged-window block kernel with this many rows per lane (0: off)
@@ -220,6 +220,7 @@ struct amg_ctx {
     amgiga::DevSetupInfo setup_info;
     double *sc = nullptr;
     double *hsc = nullptr;     // pinned host copy of the scalar block
+    double *hsc_dev = nullptr; // its device address: k_finalize writes the stopping test's scalars there
     std::vector<double> hist;  // ||r_k|| / ||F|| of the last pcg_solve, k = 0 .. iterations
     hipEvent_t ev_iter = nullptr;
     std::vector<void *> allocs;
@@ -796,10 +797,35 @@ struct amg_ctx {
             prof_end(bytes, AMG_PASS_KP);
         }
     }
-    void finalize(unsigned nblk, int op, int slot = 0)
+    void finalize(unsigned nblk, int op, int slot = 0, double *host = nullptr)
     {
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FIN_THREADS), 0, stream, partial, (int)nblk, sc, op, slot);
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FIN_THREADS), 0, stream, partial, (int)nblk, sc, op, slot, host);
         HIPCHK(hipGetLastError());
+    }
+    // u += alpha p, r -= alpha q and the next V-cycle's first smoothing step,
+    // from nblk partials of (p, q): the update forms alpha itself when every
+    // block can sum them in one step, else k_finalize does
+    template <typename VT> unsigned cg_update(unsigned nblk, int op, double *u)
+    {
+        const bool own = nblk <= (unsigned)FIN_THREADS;
+        if (!own) finalize(nblk, op);
+        const unsigned g = vgrid(n);
+        VT *u0 = nullptr;
+        VT coef = 1;
+        if (nlev > 1) {
+            Level &L = lev[0];
+            const bool ch = prm.smoother == 2;
+            u0 = (VT *)(ch ? L.c : L.u);
+            coef = ch ? (VT)(4.0 / 3.0) : L.poly_on ? (VT)L.poly[3] : (VT)1;
+        }
+        // the partials of (r, r) go behind those of (p, q), which other blocks may still read
+        double *rr = partial + (own ? 2 * FIN_THREADS : 0);
+        hipLaunchKernelGGL((k_cg_update<VT>), dim3(g), dim3(256), 0, stream, n, sc, own ? partial : nullptr, (int)nblk,
+                           op, u, r, p, q, rr, lev[0].invd<VT>(), u0, coef);
+        HIPCHK(hipGetLastError());
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FIN_THREADS), 0, stream, rr, (int)g, sc, FIN_STORE, S_RR, hsc_dev);
+        HIPCHK(hipGetLastError());
+        return g;
     }
     unsigned dot_partials(int64_t m, const double *a, const double *b, const double *c)
     {
@@ -887,7 +913,7 @@ struct amg_ctx {
                 HIPCHK(hipGetLastError());
             }
         } else if (L.poly_on) {
-            // the restriction wrote a3 D^{-1} f into u: finish Horner from there
+            // u holds a3 D^{-1} f already: finish Horner from there
             VT *c = u, *c2 = (VT *)L.c2;
             for (int k = 2; k >= 0; k--) {
                 sell<VT, FT, VT, EPI_POLY, 0>(l, c, f, L.invd<VT>(), c2, nullptr, nullptr, (VT)L.poly[k]);
@@ -1018,7 +1044,8 @@ struct amg_ctx {
 
     // Level l of the V-cycle in this form; returns where the result lives
     // (level 0 writes zout with the dot partials instead).
-    double *vgen(int l, const double *f, double *zout, int ndot, const double *g0, const double *g1)
+    double *vgen(int l, const double *f, double *zout, int ndot, const double *g0, const double *g1,
+                 bool first_ready = false)
     {
         Level &L = lev[l];
         double *u = (double *)L.u, *u2 = (double *)L.u2, *d = (double *)L.c, *d2 = (double *)L.c2;
@@ -1028,9 +1055,11 @@ struct amg_ctx {
         const unsigned g = nblocks(L.n);
         // 1. pre-smoothing from the zero guess, leaving r = f - K u
         if (ch) {
-            hipLaunchKernelGGL((k_scale_coef<double, double>), dim3(g), dim3(256), 0, stream, L.n, L.invd64, f, d,
-                               4.0 / 3.0);
-            HIPCHK(hipGetLastError());
+            if (!first_ready) {
+                hipLaunchKernelGGL((k_scale_coef<double, double>), dim3(g), dim3(256), 0, stream, L.n, L.invd64, f, d,
+                                   4.0 / 3.0);
+                HIPCHK(hipGetLastError());
+            }
             for (int j = 1; j < k; j++) {
                 cheb<1>(l, d, f, r, u, d2, (2.0 * j - 1.0) / (2.0 * j + 3.0), (8.0 * j + 4.0) / (2.0 * j + 3.0),
                         j == 1);
@@ -1038,8 +1067,10 @@ struct amg_ctx {
             }
             cheb<2>(l, d, f, r, u, nullptr, 0.0, 0.0, k == 1);
         } else {
-            hipLaunchKernelGGL((k_scale<double, double>), dim3(g), dim3(256), 0, stream, L.n, L.invd64, f, u);
-            HIPCHK(hipGetLastError());
+            if (!first_ready) {
+                hipLaunchKernelGGL((k_scale<double, double>), dim3(g), dim3(256), 0, stream, L.n, L.invd64, f, u);
+                HIPCHK(hipGetLastError());
+            }
             for (int s = 1; s < prm.nu_pre; s++) {
                 sweep<double, double, double>(l, f, u, u2, 0, nullptr, nullptr);
                 std::swap(u, u2);
@@ -1105,9 +1136,11 @@ struct amg_ctx {
         return u;
     }
 
-    // z = B r; when ndot > 0 the partials of (z, g0) [and (z, g1)] are left in
+    // z = B r; u0_ready: level 0's first smoothing step from zero is done (by
+    // cg_update); when ndot > 0 the partials of (z, g0) [and (z, g1)] are left in
     // `partial` and the number of blocks to finalize is returned.
-    unsigned vcycle(const double *rin, double *zout, int ndot, const double *g0, const double *g1)
+    unsigned vcycle(const double *rin, double *zout, int ndot, const double *g0, const double *g1,
+                    bool u0_ready = false)
     {
         vc_nb = 0;
         if (general_vcycle()) {
@@ -1115,7 +1148,7 @@ struct amg_ctx {
                 coarsest_solve(rin, zout);
                 if (ndot) vc_nb = dot_partials(n, zout, g0, g1);
             } else {
-                vgen(0, rin, zout, ndot, g0, g1);
+                vgen(0, rin, zout, ndot, g0, g1, u0_ready);
             }
             return vc_nb;
         }
@@ -1124,8 +1157,8 @@ struct amg_ctx {
             if (ndot) vc_nb = dot_partials(n, zout, g0, g1);
             return vc_nb;
         }
-        if (fp32()) vlevel<float, double>(0, rin, zout, ndot, g0, g1, false);
-        else vlevel<double, double>(0, rin, zout, ndot, g0, g1, false);
+        if (fp32()) vlevel<float, double>(0, rin, zout, ndot, g0, g1, u0_ready);
+        else vlevel<double, double>(0, rin, zout, ndot, g0, g1, u0_ready);
         return vc_nb;
     }
 
@@ -1151,6 +1184,7 @@ struct amg_ctx {
         bgsave = alloc<double>(256);
         if (tail_start > 0) tail_dev_blk = fp32() ? tail_descriptors<float>(true) : tail_descriptors<double>(true);
         HIPCHK(hipHostMalloc((void **)&hbsc, B_NSLOTS * NB * sizeof(double), hipHostMallocDefault));
+        HIPCHK(hipHostGetDevicePointer((void **)&hbsc_dev, hbsc, 0));
     }
     BlkCfg blk_cfg() const { return {stream, blk_win, blk_share, blk_lpr, blk_threads, bpartial}; }
     // Block matrix pass on level l; returns the number of dot-partial blocks.
@@ -1177,7 +1211,7 @@ struct amg_ctx {
         }
         return nb;
     }
-    void bfinalize(unsigned nblk, int op, double tol = 0.0)
+    void bfinalize(unsigned nblk, int op, double tol = 0.0, double *host = nullptr)
     {
         // many partials (one per wavefront of a level-0 pass): the strided sums
         // of the single final block over a wide grid first
@@ -1187,13 +1221,25 @@ struct amg_ctx {
                                (int)nblk, bstrided);
             st = bstrided;
         }
-        hipLaunchKernelGGL(k_bfinalize, dim3(1), dim3(FIN_THREADS), 0, stream, bpartial, (int)nblk, bsc, op, tol, st);
+        hipLaunchKernelGGL(k_bfinalize, dim3(NB), dim3(FIN_THREADS), 0, stream, bpartial, (int)nblk, bsc, op, tol, st,
+                           host);
         HIPCHK(hipGetLastError());
     }
     // grid of the element-parallel block vector kernels (a multiple of 16 threads)
     unsigned bgrid(int64_t rows) const
     {
         return (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (rows * NB + 255) / 256));
+    }
+    // u += alpha p, r -= alpha q and the next V-cycle's first smoothing step;
+    // the stopping test's flags go to the host
+    template <typename VT> void bcg_update()
+    {
+        const unsigned g = bgrid(n);
+        const Level &L = lev[0];
+        hipLaunchKernelGGL((k_bcg_update<VT>), dim3(g), dim3(256), 0, stream, n, bsc, bU, bR, bP, bQ, bpartial,
+                           L.invd<VT>(), nlev > 1 ? (VT *)L.bu : nullptr, L.poly_on ? (VT)L.poly[3] : (VT)1);
+        HIPCHK(hipGetLastError());
+        bfinalize(g, BF_RR, 0.0, hbsc_dev);
     }
     template <typename VT> void coarse_blk(const VT *f, VT *e)
     {
@@ -1296,7 +1342,7 @@ struct amg_ctx {
         Level &C = lev[l + 1];
         const bool coarsest = (l + 1 == nlev - 1);
         const VT a3 = C.poly_on ? (VT)C.poly[3] : (VT)1;
-        hipLaunchKernelGGL((k_restrict_blk<VT>), dim3(nblocks(C.n)), dim3(256), 0, stream, C.n, L.mw, L.members,
+        hipLaunchKernelGGL((k_restrict_blk<VT>), dim3(nblocks(C.n * NB)), dim3(256), 0, stream, C.n, L.mw, L.members,
                            L.pc<VT>(), (const VT *)L.br, (VT *)C.bf, coarsest ? nullptr : C.invd<VT>(),
                            coarsest ? nullptr : (VT *)C.bu, a3);
         HIPCHK(hipGetLastError());
@@ -1339,7 +1385,8 @@ struct amg_ctx {
         }
         return u;
     }
-    unsigned vcycle_blk(const double *rin, double *zout, int ndot, const double *g0, const double *g1)
+    unsigned vcycle_blk(const double *rin, double *zout, int ndot, const double *g0, const double *g1,
+                        bool u0_ready = false)
     {
         vc_nb = 0;
         if (nlev == 1) {
@@ -1347,8 +1394,8 @@ struct amg_ctx {
             if (ndot) vc_nb = bdot_partials(n, zout, g0, g1);
             return vc_nb;
         }
-        if (fp32()) vlevel_blk<float, double>(0, rin, zout, ndot, g0, g1, false);
-        else vlevel_blk<double, double>(0, rin, zout, ndot, g0, g1, false);
+        if (fp32()) vlevel_blk<float, double>(0, rin, zout, ndot, g0, g1, u0_ready);
+        else vlevel_blk<double, double>(0, rin, zout, ndot, g0, g1, u0_ready);
         return vc_nb;
     }
 };
@@ -1470,10 +1517,12 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
     c->z = c->alloc<double>(c->n);
     c->p = c->alloc<double>(c->n);
     c->q = c->alloc<double>(c->n);
+    // at least the FIN_THREADS partials of (p, q) and vgrid's of (r, r) behind them
     c->partial_cap = 2 * std::max<int64_t>(4096, SELL_WAVES * c->sell_blocks(0));
     c->partial = c->alloc<double>(c->partial_cap);
     c->sc = c->alloc<double>(S_NSLOTS);
     HIPCHK(hipHostMalloc((void **)&c->hsc, S_NSLOTS * sizeof(double), hipHostMallocDefault));
+    HIPCHK(hipHostGetDevicePointer((void **)&c->hsc_dev, c->hsc, 0));
     HIPCHK(hipEventCreateWithFlags(&c->ev_iter, hipEventDisableTiming));
     c->choose_tail();
     c->tune_xwin();
@@ -1698,18 +1747,18 @@ static amg_status solve_impl(amg_ctx *c, const double *F, double *u_user, double
     auto partA = [&]() {
         if (flex) c->sell<double, double, double, EPI_SPMV, 2>(0, c->p, nullptr, nullptr, c->q, nullptr, c->r);
         else c->sell<double, double, double, EPI_SPMV, 1>(0, c->p, nullptr, nullptr, c->q, nullptr, nullptr);
-        c->finalize(c->dot_blocks(c->lev[0].A), flex ? FIN_PQ_FCG : FIN_PQ_CG);
-        unsigned g = vgrid(n);
-        hipLaunchKernelGGL(k_cg_update, dim3(g), dim3(256), 0, c->stream, n, c->sc, u, c->r, c->p, c->q, c->partial);
-        HIPCHK(hipGetLastError());
-        c->finalize(g, FIN_STORE, S_RR);
-        HIPCHK(hipMemcpyAsync(c->hsc, c->sc, S_NSLOTS * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        const unsigned nb = c->dot_blocks(c->lev[0].A);
+        if (c->fp32()) c->cg_update<float>(nb, flex ? FIN_PQ_FCG : FIN_PQ_CG, u);
+        else c->cg_update<double>(nb, flex ? FIN_PQ_FCG : FIN_PQ_CG, u);
     };
     // part B: z = B r, beta, p = z + beta p
     auto partB = [&]() {
-        unsigned nb2 = c->vcycle(c->r, c->z, 1, flex ? c->q : c->r, nullptr);
-        c->finalize(nb2, flex ? FIN_ZQ_FCG : FIN_RZ_CG);
-        hipLaunchKernelGGL(k_cg_pupdate, dim3(vgrid(n)), dim3(256), 0, c->stream, n, c->sc, c->z, c->p);
+        const unsigned nb = c->vcycle(c->r, c->z, 1, flex ? c->q : c->r, nullptr, true);
+        const int op = flex ? FIN_ZQ_FCG : FIN_RZ_CG;
+        const bool own = nb <= (unsigned)FIN_THREADS;
+        if (!own) c->finalize(nb, op);
+        hipLaunchKernelGGL(k_cg_pupdate, dim3(vgrid(n)), dim3(256), 0, c->stream, n, c->sc,
+                           own ? c->partial : nullptr, (int)nb, op, c->z, c->p);
         HIPCHK(hipGetLastError());
     };
     if (std::sqrt(rr) <= tol * nF) {
@@ -1905,15 +1954,11 @@ static amg_status solve_batched_impl(amg_ctx *c, int nrhs, const double *F, doub
             if (flex) nbq = c->sell_blk<double, double, double, EPI_SPMV, 2>(0, c->bP, nullptr, nullptr, c->bQ, nullptr, c->bR);
             else nbq = c->sell_blk<double, double, double, EPI_SPMV, 1>(0, c->bP, nullptr, nullptr, c->bQ, nullptr, nullptr);
             c->bfinalize(nbq, flex ? BF_PQ_FCG : BF_PQ_CG);
-            unsigned g = c->bgrid(n);
-            hipLaunchKernelGGL(k_bcg_update, dim3(g), dim3(256), 0, c->stream, n, c->bsc, c->bU, c->bR, c->bP, c->bQ,
-                               c->bpartial);
-            HIPCHK(hipGetLastError());
-            c->bfinalize(g, BF_RR);
-            HIPCHK(hipMemcpyAsync(c->hbsc, c->bsc, B_NSLOTS * NB * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+            if (c->fp32()) c->bcg_update<float>();
+            else c->bcg_update<double>();
         };
         auto partB = [&]() {
-            unsigned nb2 = c->vcycle_blk(c->bR, c->bZ, 1, flex ? c->bQ : c->bR, nullptr);
+            unsigned nb2 = c->vcycle_blk(c->bR, c->bZ, 1, flex ? c->bQ : c->bR, nullptr, true);
             c->bfinalize(nb2, flex ? BF_ZQ_FCG : BF_RZ_CG);
             hipLaunchKernelGGL(k_bcg_pupdate, dim3(c->bgrid(n)), dim3(256), 0, c->stream, n, c->bsc, c->bZ, c->bP);
             HIPCHK(hipGetLastError());
