@@ -9,6 +9,24 @@ namespace amgk {
 template <typename VT, typename OT, int NDOT>
 unsigned blk_post(const BlkCfg &c, const DevMat &A, bool multi, const PostVecs<VT, OT> &v)
 {
+    if constexpr (NDOT == 0) {
+        if (multi && A.split > 1) {
+#define LAUNCH(IT, LPR)                                                                                           \
+    hipLaunchKernelGGL((k_splitb_post<VT, OT, IT, LPR>), dim3((unsigned)A.nslices), dim3(64 * SPLITB_WAVES), 0,   \
+                       c.stream, A.sv<VT, IT>(), v.e, v.u, v.r, v.invd, v.agg, v.pc, v.y)
+#define LAUNCH_IT(LPR)                   \
+    do {                                 \
+        if (A.idx16) LAUNCH(uint16_t, LPR); \
+        else LAUNCH(int32_t, LPR);       \
+    } while (0)
+            if (c.lpr == 4) LAUNCH_IT(4);
+            else if (c.lpr == 8) LAUNCH_IT(8);
+            else LAUNCH_IT(16);
+#undef LAUNCH_IT
+#undef LAUNCH
+            return (unsigned)A.nslices;
+        }
+    }
     const unsigned g = multi ? blk_grid(c, A) : sell_grid(A);
 #define LAUNCH(IT, ...)                                                                                            \
     hipLaunchKernelGGL((__VA_ARGS__), dim3(g), dim3(multi ? c.threads : 256), 0, c.stream, A.sv<VT, IT>(), v.e, v.u, \

@@ -266,6 +266,15 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// barrier that orders the block's LDS accesses and leaves the waves' global
+// loads in flight
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Direct global-to-LDS load of 16 bytes per lane (global_load_lds_dwordx4):
 // lane l's 16 bytes from src go to lds + 16 l (lds wave-uniform).  The host
 // pass of the compiler does not take the builtin, hence the guard.

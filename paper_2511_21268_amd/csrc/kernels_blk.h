@@ -737,6 +737,140 @@ template <> struct RowLoad<double> {
     }
 };
 
+// Index data and columns of T consecutive entries (T / 8 groups) of a lane's
+// row, the columns made a step after the loads: shared offsets (scalar cache),
+// 16-bit deltas or int32 columns.  Groups past the row's last one (ng) are read
+// from it; their columns stay in range and nobody sums them.
+template <int C, int T, typename IT> struct ColsAhead {
+    static constexpr int TG = T / 8;
+    const int32_t *so;       // shared offsets, or nullptr
+    int row, hi, clamp, ng;
+    vu4 d[TG];
+    vi4 c[2 * TG];
+    int col;
+    template <typename VT> __device__ __forceinline__ void start(const Sell<VT, IT> &A, int64_t s, int r, int groups)
+    {
+        const int64_t ib = A.ibase[s];
+        ng = groups;
+        so = nullptr;
+        if (ib < 0) {
+            const int64_t e = -1 - ib;
+            so = A.shoff + (e >> 1);
+            clamp = !(e & 1);
+            row = (int)(s * C) + r;
+            hi = (int)A.ncols - 1;
+        } else if (sizeof(IT) == 2) {
+            col = A.col0[s * C + r];
+        }
+    }
+    // ask for the entries from group g0 on; restart: their running column too
+    template <typename VT>
+    __device__ __forceinline__ void fetch(const Sell<VT, IT> &A, int64_t s, int r, int g0, bool restart = false)
+    {
+        if (so) return;
+        const int64_t ib = A.ibase[s];
+        if constexpr (sizeof(IT) == 2) {
+            if (restart) col = A.gcol[ib / 8 + (int64_t)min(g0, ng - 1) * C + r];
+#pragma unroll
+            for (int g = 0; g < TG; g++)
+                d[g] = __builtin_nontemporal_load(reinterpret_cast<const vu4 *>(A.idx + ib) +
+                                                  (int64_t)min(g0 + g, ng - 1) * C + r);
+        } else {
+#pragma unroll
+            for (int g = 0; g < 2 * TG; g++)
+                c[g] = __builtin_nontemporal_load(reinterpret_cast<const vi4 *>(A.idx + ib) +
+                                                  (int64_t)min(2 * g0 + g, 2 * ng - 1) * C + r);
+        }
+    }
+    __device__ __forceinline__ void columns(int g0, int (&o)[T])
+    {
+        if (so) {
+#pragma unroll
+            for (int k = 0; k < T; k++) {
+                o[k] = row + so[8 * min(g0 + k / 8, ng - 1) + k % 8];
+                if (clamp) o[k] = min(max(o[k], 0), hi);
+            }
+        } else if constexpr (sizeof(IT) == 2) {
+#pragma unroll
+            for (int g = 0; g < TG; g++) {
+                const bool live = g0 + g < ng;
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    const unsigned w = d[g][k / 2];
+                    if (live) col += (int)(k % 2 ? w >> 16 : w & 0xffffu);
+                    o[8 * g + k] = col;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < T; k++) o[k] = c[k / 4][k % 4];
+        }
+    }
+};
+
+// values and X rows of T entries of a lane's row, and their ascending chains
+template <int C, int T, int RPL, typename VT> struct EntryBlock {
+    VT v[T], x[T][RPL];
+    template <typename IT>
+    __device__ __forceinline__ void values(const Sell<VT, IT> &A, int64_t base, int ng, int g0, int r)
+    {
+#pragma unroll
+        for (int g = 0; g < T / 8; g++) {
+            VT o[8];
+            load8c<C>(A.val, base, 8 * min(g0 + g, ng - 1), r, o);
+#pragma unroll
+            for (int k = 0; k < 8; k++) v[8 * g + k] = o[k];
+        }
+    }
+    __device__ __forceinline__ void rows(const VT *__restrict__ X, const int (&c)[T])
+    {
+#pragma unroll
+        for (int k = 0; k < T; k++) RowLoad<VT>::template load<RPL>(X + (int64_t)c[k] * NB, x[k]);
+    }
+    __device__ __forceinline__ void add(VT (&acc)[RPL], const VT (&w)[T], int left) const
+    {
+#pragma unroll
+        for (int g = 0; g < T / 8; g++)
+            if (g < left)
+#pragma unroll
+                for (int k = 8 * g; k < 8 * g + 8; k++)
+#pragma unroll
+                    for (int j = 0; j < RPL; j++) acc[j] = fma(w[k], x[k][j], acc[j]);
+    }
+};
+
+// Row sums of RPL columns (Xq: X at the lane's first column) by one wave: the
+// values and index data of the next T entries are in flight while the X rows of
+// this T are gathered and summed, so a step waits for one latency, not two
+// (T = 16 in FP32, 8 in FP64: within 128 VGPRs).  With 8 entries a step and no
+// load ahead, the coarse levels and K P of 16 columns at 3D p = 3 n = 48 took 260
+// of 735 us an iteration; this and k_splitb take 70.
+template <int C, int RPL, typename VT, typename IT>
+__device__ __forceinline__ void blk_row(const Sell<VT, IT> &A, int64_t s, int r, const VT *__restrict__ Xq,
+                                        VT (&acc)[RPL])
+{
+    constexpr int T = sizeof(VT) == 4 ? 16 : 8, TG = T / 8;
+    const int64_t base = A.soff[s];
+    const int ng = (int)((A.soff[s + 1] - base) / (8 * C));
+    if (ng == 0) return;
+    ColsAhead<C, T, IT> cols;
+    EntryBlock<C, T, RPL, VT> e;
+    cols.start(A, s, r, ng);
+    cols.fetch(A, s, r, 0);
+    e.values(A, base, ng, 0, r);
+    for (int g = 0; g < ng; g += TG) {
+        int c[T];
+        VT w[T];
+        cols.columns(g, c);
+        e.rows(Xq, c);
+#pragma unroll
+        for (int k = 0; k < T; k++) w[k] = e.v[k];
+        cols.fetch(A, s, r, g + TG);
+        e.values(A, base, ng, g + TG, r);
+        e.add(acc, w, ng - g);
+    }
+}
+
 template <typename VT, typename FT, typename OT, typename IT, int EPI, int NDOT, int LPR>
 __global__ __launch_bounds__(512) void k_sellb(const Sell<VT, IT> A, const VT *__restrict__ X,
                                                const FT *__restrict__ F, const VT *__restrict__ invd,
@@ -756,15 +890,7 @@ __global__ __launch_bounds__(512) void k_sellb(const Sell<VT, IT> A, const VT *_
         VT acc[RPL];
 #pragma unroll
         for (int j = 0; j < RPL; j++) acc[j] = 0;
-        sell_row<C>(A, s, r, [&](const VT *v, const int *c) {
-#pragma unroll
-            for (int t = 0; t < 8; t++) {
-                VT xv[RPL];
-                RowLoad<VT>::template load<RPL>(X + (int64_t)c[t] * NB + q * RPL, xv);
-#pragma unroll
-                for (int j = 0; j < RPL; j++) acc[j] = fma(v[t], xv[j], acc[j]);
-            }
-        });
+        blk_row<C, RPL>(A, s, r, X + q * RPL, acc);
         if (row >= 0) {
             const int64_t o = row * NB + q * RPL;
             if (EPI == EPI_SPMV) {
@@ -895,15 +1021,7 @@ __global__ __launch_bounds__(512) void k_sellb_post(const Sell<VT, IT> A, const 
         VT acc[RPL];
 #pragma unroll
         for (int j = 0; j < RPL; j++) acc[j] = 0;
-        sell_row<C>(A, s, r, [&](const VT *v, const int *c) {
-#pragma unroll
-            for (int t = 0; t < 8; t++) {
-                VT xv[RPL];
-                RowLoad<VT>::template load<RPL>(E + (int64_t)c[t] * NB + q * RPL, xv);
-#pragma unroll
-                for (int j = 0; j < RPL; j++) acc[j] = fma(v[t], xv[j], acc[j]);
-            }
-        });
+        blk_row<C, RPL>(A, s, r, E + q * RPL, acc);
         if (row >= 0) {
             const int64_t o = row * NB + q * RPL, a = (int64_t)agg[row] * NB + q * RPL;
             const VT di = invd[row], pi = pc[row];
@@ -937,6 +1055,102 @@ __global__ __launch_bounds__(512) void k_sellb_post(const Sell<VT, IT> A, const 
             partial[(2 * blockIdx.x + d) * NB + j] = (d == 1 && NDOT < 2) ? 0.0 : t;
         }
     }
+}
+
+// ---- several waves per slice ---------------------------------------------------
+//
+// Block images of few slices (coarse levels): a block of SPLITB_WAVES waves takes
+// one slice of 64 / LPR rows in turns of T entries, as split.h does for the
+// single-vector passes: each wave has its next turn's values and X rows in
+// flight, the sums go from wave to wave through LDS, in ascending entry order.
+constexpr int SPLITB_WAVES = 4, SPLITB_T = 16;
+
+// acc of the slice's rows and columns after the last turn, in wave 0
+template <int C, int RPL, typename VT, typename IT>
+__device__ __forceinline__ void splitb_rows(const Sell<VT, IT> &A, int64_t s, int r, int lane, int wid,
+                                            const VT *__restrict__ Xq, VT (&acc)[RPL], VT (*sums)[64] /* RPL */)
+{
+    constexpr int W = SPLITB_WAVES, T = SPLITB_T, TG = T / 8;
+    const int64_t base = A.soff[s];
+    const int ng = (int)((A.soff[s + 1] - base) / (8 * C)), nt = (ng + TG - 1) / TG;
+    if (nt == 0) return;
+    ColsAhead<C, T, IT> cols;
+    EntryBlock<C, T, RPL, VT> e;
+    cols.start(A, s, r, ng);
+    auto load = [&](int t) {
+        int c[T];
+        cols.columns(t * TG, c);
+        e.values(A, base, ng, t * TG, r);
+        e.rows(Xq, c);
+        cols.fetch(A, s, r, (t + W) * TG, true);
+    };
+    cols.fetch(A, s, r, wid * TG, true);
+    if (wid < nt) load(wid);
+    for (int t = 0; t < nt; t++) {
+        const bool mine = t % W == wid;
+        if (mine) {
+            if (t > 0)
+#pragma unroll
+                for (int j = 0; j < RPL; j++) acc[j] = sums[j][lane];
+            e.add(acc, e.v, ng - t * TG);
+#pragma unroll
+            for (int j = 0; j < RPL; j++) sums[j][lane] = acc[j];
+        }
+        lds_barrier();
+        if (mine && t + W < nt) load(t + W);
+    }
+    if (wid == 0)
+#pragma unroll
+        for (int j = 0; j < RPL; j++) acc[j] = sums[j][lane];
+}
+
+// k_sellb without dots, SPLITB_WAVES waves per slice: block s takes slice s.
+template <typename VT, typename FT, typename OT, typename IT, int EPI, int LPR>
+__global__ __launch_bounds__(64 * SPLITB_WAVES) void k_splitb(const Sell<VT, IT> A, const VT *__restrict__ X,
+                                                              const FT *__restrict__ F, const VT *__restrict__ invd,
+                                                              OT *__restrict__ Y, VT coef)
+{
+    constexpr int C = 64 / LPR, RPL = NB / LPR;
+    __shared__ VT sums[RPL][64];
+    const int lane = threadIdx.x & 63, wid = wave_id(), r = lane / LPR, q = lane % LPR;
+    const int64_t s = blockIdx.x, row = A.row_of(s * C + r);
+    VT acc[RPL];
+#pragma unroll
+    for (int j = 0; j < RPL; j++) acc[j] = 0;
+    splitb_rows<C, RPL>(A, s, r, lane, wid, X + q * RPL, acc, sums);
+    if (wid != 0 || row < 0) return;
+    const int64_t o = row * NB + q * RPL;
+    const VT di = (EPI == EPI_SMOOTH || EPI == EPI_POLY) ? invd[row] : (VT)0;
+#pragma unroll
+    for (int j = 0; j < RPL; j++) {
+        if (EPI == EPI_SPMV) Y[o + j] = (OT)acc[j];
+        else if (EPI == EPI_RESID) Y[o + j] = (OT)((VT)F[o + j] - acc[j]);
+        else if (EPI == EPI_SMOOTH) Y[o + j] = (OT)(X[o + j] + di * ((VT)F[o + j] - acc[j]));
+        else Y[o + j] = (OT)(coef * (di * (VT)F[o + j]) + di * acc[j]);
+    }
+}
+
+// k_sellb_post without dots, SPLITB_WAVES waves per slice.
+template <typename VT, typename OT, typename IT, int LPR>
+__global__ __launch_bounds__(64 * SPLITB_WAVES) void k_splitb_post(const Sell<VT, IT> A, const VT *__restrict__ E,
+                                                                   const VT *__restrict__ U, const VT *__restrict__ R,
+                                                                   const VT *__restrict__ invd,
+                                                                   const int32_t *__restrict__ agg,
+                                                                   const VT *__restrict__ pc, OT *__restrict__ Y)
+{
+    constexpr int C = 64 / LPR, RPL = NB / LPR;
+    __shared__ VT sums[RPL][64];
+    const int lane = threadIdx.x & 63, wid = wave_id(), r = lane / LPR, q = lane % LPR;
+    const int64_t s = blockIdx.x, row = A.row_of(s * C + r);
+    VT acc[RPL];
+#pragma unroll
+    for (int j = 0; j < RPL; j++) acc[j] = 0;
+    splitb_rows<C, RPL>(A, s, r, lane, wid, E + q * RPL, acc, sums);
+    if (wid != 0 || row < 0) return;
+    const int64_t o = row * NB + q * RPL, a = (int64_t)agg[row] * NB + q * RPL;
+    const VT di = invd[row], pi = pc[row];
+#pragma unroll
+    for (int j = 0; j < RPL; j++) Y[o + j] = (OT)post_update(U[o + j], pi, E[a + j], di, R[o + j], acc[j]);
 }
 
 }  // namespace amgk

@@ -9,7 +9,7 @@
 #include "host.h"
 #include "kernels.h"
 #include "blk_launch.h"
-#include "kernels_blk_vec.h"
+#include "kernels_blk.h"
 #include "blockcg.h"
 #include "mlp.h"
 #include "post_res.h"
@@ -324,7 +324,7 @@ struct amg_ctx {
         A.n = K.n; A.ncols = square ? K.n : ncols; A.sorted = S.sorted;
         A.nnz = K.nnz(); A.nslices = S.nslices; A.stored = S.stored; A.idx16 = S.idx16; A.C = C;
         A.nshared = S.nshared; A.index_bytes = S.index_bytes;
-        if (C == SLICE) A.split = split_waves(S.nslices, S.stored);
+        A.split = C == SLICE ? split_waves(S.nslices, S.stored) : split_waves_blk(S.nslices);
         if (A.split > 1 && !S.d16.empty()) {
             // running column before each group of 8 deltas
             std::vector<int32_t> gcol(S.d16.size() / 8);
@@ -384,6 +384,11 @@ struct amg_ctx {
         if (nslices >= 256) return groups >= 8.0 ? 4 : 1;
         return groups >= 16.0 ? 8 : 4;
     }
+    // Several waves per slice of a block image (SELL-(64/lanes), k_splitb)
+    // below 1,024 slices: 16 columns, 3D p = 3 n = 48 (coarse levels of 466, 118,
+    // .. slices) 552 us an iteration without, 534 below 1,024, 543 below 2,048;
+    // n = 32: 375, 355, 355
+    static int split_waves_blk(int64_t nslices) { return nslices < 1024 ? SPLITB_WAVES : 1; }
     // Device time of body(), best of two after one warm-up run.
     template <class Body> float time_passes(Body body)
     {

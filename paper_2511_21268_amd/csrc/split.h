@@ -29,15 +29,6 @@
 
 namespace amgk {
 
-// barrier that orders the block's LDS accesses and leaves the waves' global
-// loads in flight
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 constexpr int TURN = 32;   // entries per row and turn (values and x in registers: 128 VGPRs in FP64)
 
 // sums[r] = (K x)_{row r of slice s}; all W waves of the block call it.

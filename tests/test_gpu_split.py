@@ -100,3 +100,23 @@ def test_split_rule_lines(amg, n):
     ctx = amg.Context(*_arrays(K))
     y = ctx.spmv(torch.from_numpy(x).cuda()).cpu().numpy()
     assert np.array_equal(y, K @ x)
+
+
+@pytest.mark.parametrize("d,p,n", [(3, 3, 14), (3, 2, 33), (2, 3, 61), (3, 5, 9), (3, 3, 40)])
+@pytest.mark.parametrize("fp32", [0, 1])
+def test_block_split_equals_one_lane(amg, d, p, n, fp32):
+    """The block V-cycle on the lanes-per-row images (one wave or several per
+    slice, loads ahead) against the one-lane-per-row kernels: the V-cycle has the
+    same bits, so the first iterate u = alpha z differs by alpha's dots only."""
+    print(f"case block split d={d} p={p} n={n} fp32={fp32}", flush=True)
+    rp, ci, v, _ = amg.iga_poisson(d, p, n, want_F=False)
+    ctx = amg.Context(rp, ci, v, nrhs=16, itmax=1, **(dict(vcycle_fp32=1, krylov=1) if fp32 else {}))
+    lpr, threads = ctx.batched_variant()
+    F = torch.from_numpy(np.random.default_rng(n).standard_normal((16, len(rp) - 1))).cuda().t()
+    got = ctx.solve_batched(F)["U"]
+    ctx.set_batched_variant(1, 256)
+    ref = ctx.solve_batched(F)["U"]
+    print(f"  lanes per row {lpr}", flush=True)
+    # two sums of N products each: 2 N u on sums of absolute terms at most about
+    # ten times their value
+    assert torch.linalg.norm(got - ref) <= 20 * len(rp) * 2.0 ** -53 * torch.linalg.norm(ref)
