@@ -134,6 +134,8 @@ struct SellHost {
     std::vector<float> v32;
     std::vector<uint16_t> d16;
     std::vector<int32_t> c32, col0, shoff, shrun;
+    int64_t indices = 0;            // entries of the per-row index stream
+    std::vector<int32_t> ulen;      // offsets of each slice's shared list (0: per-row indices)
 };
 // Windows shared by the four waves (slices) of a workgroup in the block
 // kernels: logical workgroup b holds slices tab[8b .. 8b+3] (ids past the last
@@ -156,6 +158,10 @@ void choose_wg_stages(const SellHost &S, int C, int64_t nwg, WgStages &W);
 std::vector<int32_t> slice_offsets(const CsrView &K, int64_t s, int C, int64_t limit);
 int64_t count_shared(const CsrView &K, int C);
 void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, int sigma, SellHost &S);
+// Its layout alone (soff, ibase, perm, offset lists and run tables, sizes): what
+// a device fill of the entries needs.  max_gap: the widest column gap of a row
+// if known (K.ci may then be NULL unless shared), else -1.
+void sell_layout(const CsrView &K, int C, bool shared, int sigma, int64_t max_gap, SellHost &S);
 // y = K x walked through the image as the kernels walk it (layouts of
 // amg_sell_spmv_host); 0, or -6 with err set when a read would leave its array.
 int sell_spmv_walk(const CsrView &K, int64_t ncols, int C, int layout, const double *x, double *y,

@@ -1100,6 +1100,12 @@ int64_t count_shared(const CsrView &K, int C)
     return cnt.load();
 }
 
+// rows of the slots, and the shared offset list of each slice (empty: none)
+struct SellRows {
+    std::vector<int32_t> rowof;
+    std::vector<std::vector<int32_t>> U;
+};
+
 // SELL-C image of a CSR matrix (slice height C rows; group layout of kernels.h).
 // With `shared`, a slice whose offset union is no wider than its longest row
 // (both rounded up to 8) stores the union once; the others keep per-row indices.
@@ -1107,13 +1113,14 @@ int64_t count_shared(const CsrView &K, int C)
 // consecutive rows are placed in the window's slots by decreasing length (ties
 // by index), so the slices of a window pad to similar lengths; perm[slot]
 // gives the row of each slot (-1 for the slots past the last row).
-void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, int sigma, SellHost &S)
+static void layout_rows(const CsrView &K, int C, bool shared, int sigma, int64_t max_gap, SellHost &S, SellRows &R)
 {
     const int64_t n = K.n;
     S.nslices = (n + C - 1) / C;
     const int64_t nslot = S.nslices * C;
     if (sigma > 0) shared = false;
-    std::vector<int32_t> rowof(nslot, -1);
+    std::vector<int32_t> &rowof = R.rowof;
+    rowof.assign(nslot, -1);
     auto len = [&](int64_t r) { return K.rp[r + 1] - K.rp[r]; };
     parallel_for((n + std::max(sigma, 1) - 1) / std::max(sigma, 1), [&](int64_t wb, int64_t we) {
         for (int64_t w = wb; w < we; w++) {
@@ -1127,7 +1134,8 @@ void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, 
     S.sorted = sigma > 0 ? 1 : 0;
     if (S.sorted) S.perm = rowof;
     std::vector<int64_t> wd(S.nslices);
-    std::vector<std::vector<int32_t>> U(S.nslices);
+    std::vector<std::vector<int32_t>> &U = R.U;
+    U.assign(S.nslices, {});
     parallel_for(S.nslices, [&](int64_t sb, int64_t se) {
         for (int64_t s = sb; s < se; s++) {
             int64_t w = 0;
@@ -1169,7 +1177,7 @@ void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, 
         }
     }
     S.stored = S.soff[S.nslices];
-    int maxd = 0;
+    int maxd = max_gap >= 0 ? (int)max_gap : 0;
     int64_t dnnz = 0, drows = 0;
     {
         std::mutex mx;
@@ -1181,7 +1189,8 @@ void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, 
                 for (int64_t q = s * C; q < (s + 1) * C; q++) {
                     const int64_t r = rowof[q];
                     if (r < 0) continue;
-                    for (int64_t k = K.rp[r] + 1; k < K.rp[r + 1]; k++) m = std::max(m, K.ci[k] - K.ci[k - 1]);
+                    if (max_gap < 0)
+                        for (int64_t k = K.rp[r] + 1; k < K.rp[r + 1]; k++) m = std::max(m, K.ci[k] - K.ci[k - 1]);
                     z += K.rp[r + 1] - K.rp[r];
                     nr++;
                 }
@@ -1193,17 +1202,10 @@ void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, 
         }, 1);
     }
     S.idx16 = maxd <= 65535 ? 1 : 0;
+    S.indices = ib;
+    S.ulen.resize(S.nslices);
+    for (int64_t s = 0; s < S.nslices; s++) S.ulen[s] = (int32_t)U[s].size();
     S.index_bytes += S.idx16 ? 2.0 * (double)dnnz + 4.0 * (double)drows : 4.0 * (double)dnnz;
-    if (want64) S.v64.assign(S.stored, 0.0);
-    if (want32) S.v32.assign(S.stored, 0.0f);
-    if (ib > 0) {
-        if (S.idx16) {
-            S.d16.assign(ib, 0);
-            S.col0.assign(S.nslices * C, 0);
-        } else {
-            S.c32.assign(ib, 0);
-        }
-    }
     S.shoff.assign(sh, 0);
     for (const auto &kv : lists) std::copy(kv.first.begin(), kv.first.end(), S.shoff.begin() + kv.second);
     // run table of each list for the block kernels' staged x windows: its
@@ -1222,6 +1224,30 @@ void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, 
             while (L < (size_t)amgk::WIN_LMAX && k + L < u.size() && u[k + L] == u[k] + (int32_t)L) L++;
             S.shrun[kv.second + rho++] = u[k] * 16 + (int32_t)L;
             k += L;
+        }
+    }
+}
+
+void sell_layout(const CsrView &K, int C, bool shared, int sigma, int64_t max_gap, SellHost &S)
+{
+    SellRows R;
+    layout_rows(K, C, shared, sigma, max_gap, S, R);
+}
+
+void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, int sigma, SellHost &S)
+{
+    SellRows R;
+    layout_rows(K, C, shared, sigma, -1, S, R);
+    const std::vector<int32_t> &rowof = R.rowof;
+    const std::vector<std::vector<int32_t>> &U = R.U;
+    if (want64) S.v64.assign(S.stored, 0.0);
+    if (want32) S.v32.assign(S.stored, 0.0f);
+    if (S.indices > 0) {
+        if (S.idx16) {
+            S.d16.assign(S.indices, 0);
+            S.col0.assign(S.nslices * C, 0);
+        } else {
+            S.c32.assign(S.indices, 0);
         }
     }
     parallel_for(S.nslices, [&](int64_t sb, int64_t se) {

@@ -300,13 +300,128 @@ __global__ void k_compose(int64_t n, int32_t *__restrict__ agg, double *__restri
     agg[i] = ag[a];
 }
 
+// K P: positions (row, aggregate of the column), entry indices, products
+__global__ void k_kp_keys(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                          const double *__restrict__ v, const int32_t *__restrict__ agg, const double *__restrict__ pc,
+                          uint64_t *__restrict__ keys, int32_t *__restrict__ vals, double *__restrict__ t)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    for (int64_t k = rp[i]; k < rp[i + 1]; k++) {
+        const int32_t j = ci[k];
+        keys[k] = ((uint64_t)i << 32) | (uint64_t)(uint32_t)agg[j];
+        vals[k] = (int32_t)k;
+        t[k] = v[k] * pc[j];
+    }
+}
+
+// widest column gap within a row
+__global__ void k_max_gap(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                          unsigned int *__restrict__ gap)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    int m = 0;
+    for (int64_t k = rp[i] + 1; k < rp[i + 1]; k++) m = max(m, ci[k] - ci[k - 1]);
+    if (m > 0) atomicMax(gap, (unsigned int)m);
+}
+
+// One block per slice of a SELL-C image, a thread per row and group of 8
+// entries: it reads the group's entries from the row (consecutive addresses)
+// and writes them as the image's 16-byte pieces, consecutive across the rows.
+// Bound by the loads of a row by few lanes: 10.5M entries (0.23 GB in and out)
+// 258 us; the host's fill of the same image and its upload took about 25 ms.
+// Slices s0 on; ci and v hold the entries from e0 on.
+__global__ __launch_bounds__(256) void k_fill_sell(int64_t n, int64_t row0, int64_t e0, const int64_t *__restrict__ rp,
+                                                   const int32_t *__restrict__ ci, const double *__restrict__ v, int C,
+                                                   int64_t s0, SellFill F)
+{
+    const int64_t s = s0 + blockIdx.x;
+    const int r = threadIdx.x % C;
+    const int64_t q = s * C + r, base = F.soff[s], ib = F.ibase[s];
+    const int64_t row = F.perm ? (int64_t)F.perm[q] : (q < n ? q : -1);
+    const int ng = (int)((F.soff[s + 1] - base) / (8 * C));
+    const int64_t r0 = row >= 0 ? rp[row - row0] - e0 : 0;
+    const int len = row >= 0 ? (int)(rp[row - row0 + 1] - e0 - r0) : 0;
+    const int32_t *so = ib < 0 ? F.shoff + ((-1 - ib) >> 1) : nullptr;
+    const int nu = ib < 0 ? F.ulen[s] : 0;
+    if (threadIdx.x < C && F.col0) F.col0[q] = ib >= 0 && len > 0 ? ci[r0] : 0;
+    for (int g = threadIdx.x / C; g < ng; g += 256 / C) {
+        double o[8];
+        if (so) {
+            // entry of each shared offset, 0 where the row has none
+#pragma unroll
+            for (int t = 0; t < 8; t++) {
+                const int k = 8 * g + t;
+                o[t] = 0.0;
+                if (k >= nu || len == 0) continue;
+                if (len == nu) {   // the row has them all
+                    o[t] = v[r0 + k];
+                    continue;
+                }
+                const int32_t col = (int32_t)(row + so[k]);
+                int lo = 0, hi = len - 1;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (ci[r0 + mid] < col) lo = mid + 1;
+                    else hi = mid;
+                }
+                if (ci[r0 + lo] == col) o[t] = v[r0 + lo];
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < 8; t++) o[t] = 8 * g + t < len ? v[r0 + 8 * g + t] : 0.0;
+        }
+        if (F.v64) {
+            double2 *d = reinterpret_cast<double2 *>(F.v64 + base) + (int64_t)(4 * g) * C + r;
+#pragma unroll
+            for (int t = 0; t < 4; t++) d[t * C] = make_double2(o[2 * t], o[2 * t + 1]);
+        }
+        if (F.v32) {
+            float4 *d = reinterpret_cast<float4 *>(F.v32 + base) + (int64_t)(2 * g) * C + r;
+#pragma unroll
+            for (int t = 0; t < 2; t++)
+                d[t * C] = make_float4((float)o[4 * t], (float)o[4 * t + 1], (float)o[4 * t + 2], (float)o[4 * t + 3]);
+        }
+        if (ib < 0) continue;
+        // columns of the group and the one before it; past the row its last one
+        int c[9];
+#pragma unroll
+        for (int t = 0; t < 9; t++) {
+            const int k = min(8 * g + t - 1, len - 1);
+            c[t] = len > 0 ? ci[r0 + max(k, 0)] : 0;
+        }
+        if (F.d16) {
+            uint32_t w[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++)
+                w[t] = (uint32_t)(c[2 * t + 1] - c[2 * t]) | (uint32_t)(c[2 * t + 2] - c[2 * t + 1]) << 16;
+            reinterpret_cast<uint4 *>(F.d16 + ib)[(int64_t)g * C + r] = make_uint4(w[0], w[1], w[2], w[3]);
+            if (F.gcol) F.gcol[ib / 8 + (int64_t)g * C + r] = c[0];
+        }
+        if (F.c32) {
+            int4 *d = reinterpret_cast<int4 *>(F.c32 + ib) + (int64_t)(2 * g) * C + r;
+            d[0] = make_int4(c[1], c[2], c[3], c[4]);
+            d[C] = make_int4(c[5], c[6], c[7], c[8]);
+        }
+    }
+}
+
 // ---- host driver ----------------------------------------------------------
 
-struct DevCsr {
+struct BufCsr {
     int64_t n = 0, nnz = 0;
     DBuf<int64_t> rp;
     DBuf<int32_t> ci;
     DBuf<double> v;
+    DevCsr give()
+    {
+        DevCsr d;
+        d.n = n; d.nnz = nnz;
+        d.rp = rp.p; d.ci = ci.p; d.v = v.p;
+        rp.p = nullptr; ci.p = nullptr; v.p = nullptr;
+        return d;
+    }
 };
 
 template <typename T> void up(DBuf<T> &d, const T *h, size_t k, hipStream_t s)
@@ -320,13 +435,75 @@ template <typename T> void down(std::vector<T> &h, const DBuf<T> &d, size_t k, h
     if (k) DCHK(hipMemcpyAsync(h.data(), d.p, k * sizeof(T), hipMemcpyDeviceToHost, s));
 }
 
+template <typename TI, typename TO> void scan(const TI *in, TO *out, int64_t n, hipStream_t s)
+{
+    size_t b = 0;
+    DCHK(hipcub::DeviceScan::ExclusiveSum(nullptr, b, in, out, (int)n, s));
+    DBuf<char> tmp(b ? b : 1);
+    DCHK(hipcub::DeviceScan::ExclusiveSum(tmp.p, b, in, out, (int)n, s));
+}
+
+// CSR (rows x cols) of sums of products: make_keys writes each of the m
+// products' position (row << 32 | column), its index (ascending order of the
+// sum) and its value; equal positions are summed in index order from +0.0.
+template <typename Keys>
+BufCsr sum_products(int64_t m, int64_t rows, hipStream_t s_, Keys make_keys)
+{
+    DBuf<uint64_t> keys(m), keys2(m);
+    DBuf<int32_t> vals(m), vals2(m), head(m);
+    DBuf<double> t(m);
+    make_keys(keys.p, vals.p, t.p);
+    DCHK(hipGetLastError());
+    int bits = 1;
+    while ((int64_t(1) << bits) < rows) bits++;
+    const int end_bit = 32 + bits;
+    {
+        size_t b = 0;
+        DCHK(hipcub::DeviceRadixSort::SortPairs(nullptr, b, keys.p, keys2.p, vals.p, vals2.p, (int)m, 0, end_bit,
+                                                s_));
+        DBuf<char> tmp(b ? b : 1);
+        DCHK(hipcub::DeviceRadixSort::SortPairs(tmp.p, b, keys.p, keys2.p, vals.p, vals2.p, (int)m, 0, end_bit,
+                                                s_));
+    }
+    keys.release();
+    vals.release();
+    hipLaunchKernelGGL(k_run_heads, dim3(grid(m)), dim3(256), 0, s_, m, keys2.p, head.p);
+    DCHK(hipGetLastError());
+    DBuf<int64_t> runid(m);
+    scan(head.p, runid.p, m, s_);
+    int64_t last_run = 0;
+    int32_t last_head = 0;
+    DCHK(hipMemcpyAsync(&last_run, runid.p + (m - 1), sizeof(int64_t), hipMemcpyDeviceToHost, s_));
+    DCHK(hipMemcpyAsync(&last_head, head.p + (m - 1), sizeof(int32_t), hipMemcpyDeviceToHost, s_));
+    DCHK(hipStreamSynchronize(s_));
+    const int64_t nrun = last_run + last_head;
+    DBuf<int64_t> start(nrun + 1);
+    hipLaunchKernelGGL(k_run_starts, dim3(grid(m)), dim3(256), 0, s_, m, head.p, runid.p, start.p);
+    DCHK(hipMemcpyAsync(start.p + nrun, &m, sizeof(int64_t), hipMemcpyHostToDevice, s_));
+    DCHK(hipGetLastError());
+    BufCsr C;
+    C.n = rows;
+    C.nnz = nrun;
+    C.ci.alloc(nrun);
+    C.v.alloc(nrun);
+    C.rp.alloc(rows + 1);
+    DBuf<int64_t> cnt(rows + 1);
+    DCHK(hipMemsetAsync(cnt.p, 0, (rows + 1) * sizeof(int64_t), s_));
+    hipLaunchKernelGGL(k_run_sums, dim3(grid(nrun)), dim3(256), 0, s_, nrun, start.p, keys2.p, vals2.p, t.p,
+                       C.ci.p, C.v.p, cnt.p);
+    DCHK(hipGetLastError());
+    scan(cnt.p, C.rp.p, rows + 1, s_);
+    DCHK(hipStreamSynchronize(s_));
+    return C;
+}
+
 class DeviceCoarsener : public Coarsener {
   public:
     DeviceCoarsener(hipStream_t s, DevSetupInfo *info) : s_(s), info_(info) {}
 
     void bootstrap(const CsrView &K0, const double *w0, int sweeps, std::vector<double> &w) override
     {
-        DevCsr &K = level0(K0);
+        BufCsr &K = level0(K0);
         DBuf<double> invd(K.n), a(K.n), b(K.n);
         hipLaunchKernelGGL(k_l1_invdiag, dim3(grid(K.n)), dim3(256), 0, s_, K.n, K.rp.p, K.ci.p, K.v.p, invd.p);
         DCHK(hipMemcpyAsync(a.p, w0, K.n * sizeof(double), hipMemcpyHostToDevice, s_));
@@ -342,15 +519,15 @@ class DeviceCoarsener : public Coarsener {
 
     void coarsen(int level, const CsrView &Kh, const double *w, const SetupParams &prm, CoarsenResult &out) override
     {
-        DevCsr &K0 = level == 0 ? level0(Kh) : cur_;
+        BufCsr &K0 = level == 0 ? level0(Kh) : cur_;
         if (K0.n != Kh.n || K0.nnz != Kh.nnz()) throw HipError("device set-up: level matrix out of step");
         const int64_t nl = K0.n;
         DBuf<int32_t> agg(nl);
         DBuf<double> pc(nl);
         DBuf<double> wv;
         up(wv, w, nl, s_);
-        DevCsr C;
-        const DevCsr *K = &K0;
+        BufCsr C;
+        const BufCsr *K = &K0;
         DBuf<double> wcur = std::move(wv);
         int64_t nc = nl;
         for (int sw = 0; sw < prm.sweeps; sw++) {
@@ -358,7 +535,7 @@ class DeviceCoarsener : public Coarsener {
             DBuf<double> pcs(K->n), wc;
             match(*K, wcur.p, prm.positive_only, mate.p);
             nc = pairwise(*K, mate.p, wcur.p, ag, pcs, wc);
-            DevCsr Cn = galerkin(*K, nc, ag.p, pcs.p);
+            BufCsr Cn = galerkin(*K, nc, ag.p, pcs.p);
             if (sw == 0) {
                 DCHK(hipMemcpyAsync(agg.p, ag.p, nl * sizeof(int32_t), hipMemcpyDeviceToDevice, s_));
                 DCHK(hipMemcpyAsync(pc.p, pcs.p, nl * sizeof(double), hipMemcpyDeviceToDevice, s_));
@@ -379,16 +556,33 @@ class DeviceCoarsener : public Coarsener {
         down(out.C.ci, C.ci, C.nnz, s_);
         down(out.C.v, C.v, C.nnz, s_);
         DCHK(hipStreamSynchronize(s_));
+        // a level's matrix is done with: the image set-up takes it over
+        keep(level, level == 0 ? l0_ : cur_);
         cur_ = std::move(C);
+        have_l0_ = have_l0_ && level > 0;
+        last_ = level + 1;
+    }
+    // the coarsest level's
+    void finish()
+    {
+        if (last_ > 0) keep(last_, cur_);
     }
 
   private:
     hipStream_t s_;
     DevSetupInfo *info_;
-    DevCsr l0_, cur_;
+    BufCsr l0_, cur_;
     bool have_l0_ = false;
+    int last_ = 0;
 
-    DevCsr &level0(const CsrView &K)
+    void keep(int level, BufCsr &K)
+    {
+        if (!info_) return;
+        if ((int)info_->levels.size() <= level) info_->levels.resize(level + 1);
+        info_->levels[level] = K.give();
+    }
+
+    BufCsr &level0(const CsrView &K)
     {
         if (!have_l0_) {
             l0_.n = K.n;
@@ -401,36 +595,7 @@ class DeviceCoarsener : public Coarsener {
         return l0_;
     }
 
-    template <typename F> size_t cub_bytes(F f)
-    {
-        size_t b = 0;
-        DCHK(f(nullptr, b));
-        return b;
-    }
-
-    void scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t n)
-    {
-        size_t b = 0;
-        DCHK(hipcub::DeviceScan::ExclusiveSum(nullptr, b, in, out, (int)n, s_));
-        DBuf<char> tmp(b ? b : 1);
-        DCHK(hipcub::DeviceScan::ExclusiveSum(tmp.p, b, in, out, (int)n, s_));
-    }
-    void scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n)
-    {
-        size_t b = 0;
-        DCHK(hipcub::DeviceScan::ExclusiveSum(nullptr, b, in, out, (int)n, s_));
-        DBuf<char> tmp(b ? b : 1);
-        DCHK(hipcub::DeviceScan::ExclusiveSum(tmp.p, b, in, out, (int)n, s_));
-    }
-    void scan_i64(const int64_t *in, int64_t *out, int64_t n)
-    {
-        size_t b = 0;
-        DCHK(hipcub::DeviceScan::ExclusiveSum(nullptr, b, in, out, (int)n, s_));
-        DBuf<char> tmp(b ? b : 1);
-        DCHK(hipcub::DeviceScan::ExclusiveSum(tmp.p, b, in, out, (int)n, s_));
-    }
-
-    void match(const DevCsr &K, const double *w, int positive_only, int32_t *mate)
+    void match(const BufCsr &K, const double *w, int positive_only, int32_t *mate)
     {
         DBuf<double> diag(K.n), cw(K.nnz ? K.nnz : 1);
         DBuf<unsigned long long> cnt(1);
@@ -467,14 +632,14 @@ class DeviceCoarsener : public Coarsener {
         }
     }
 
-    int64_t pairwise(const DevCsr &K, const int32_t *mate, const double *w, DBuf<int32_t> &ag, DBuf<double> &pcs,
+    int64_t pairwise(const BufCsr &K, const int32_t *mate, const double *w, DBuf<int32_t> &ag, DBuf<double> &pcs,
                      DBuf<double> &wc)
     {
         const int64_t n = K.n;
         DBuf<int32_t> flag(n), idx(n);
         hipLaunchKernelGGL(k_open, dim3(grid(n)), dim3(256), 0, s_, n, mate, flag.p);
         DCHK(hipGetLastError());
-        scan_i32_to_i32(flag.p, idx.p, n);
+        scan(flag.p, idx.p, n, s_);
         int32_t last_idx = 0, last_flag = 0;
         DCHK(hipMemcpyAsync(&last_idx, idx.p + (n - 1), sizeof(int32_t), hipMemcpyDeviceToHost, s_));
         DCHK(hipMemcpyAsync(&last_flag, flag.p + (n - 1), sizeof(int32_t), hipMemcpyDeviceToHost, s_));
@@ -486,60 +651,106 @@ class DeviceCoarsener : public Coarsener {
         return nc;
     }
 
-    DevCsr galerkin(const DevCsr &K, int64_t nc, const int32_t *agg, const double *pc)
+    BufCsr galerkin(const BufCsr &K, int64_t nc, const int32_t *agg, const double *pc)
     {
-        const int64_t m = K.nnz;
-        DBuf<uint64_t> keys(m), keys2(m);
-        DBuf<int32_t> vals(m), vals2(m), head(m);
-        DBuf<double> t(m);
-        hipLaunchKernelGGL(k_gal_keys, dim3(grid(K.n)), dim3(256), 0, s_, K.n, K.rp.p, K.ci.p, K.v.p, agg, pc,
-                           keys.p, vals.p, t.p);
-        DCHK(hipGetLastError());
-        int bits = 1;
-        while ((int64_t(1) << bits) < nc) bits++;
-        const int end_bit = 32 + bits;
-        {
-            size_t b = 0;
-            DCHK(hipcub::DeviceRadixSort::SortPairs(nullptr, b, keys.p, keys2.p, vals.p, vals2.p, (int)m, 0, end_bit,
-                                                    s_));
-            DBuf<char> tmp(b ? b : 1);
-            DCHK(hipcub::DeviceRadixSort::SortPairs(tmp.p, b, keys.p, keys2.p, vals.p, vals2.p, (int)m, 0, end_bit,
-                                                    s_));
-        }
-        keys.release();
-        vals.release();
-        hipLaunchKernelGGL(k_run_heads, dim3(grid(m)), dim3(256), 0, s_, m, keys2.p, head.p);
-        DCHK(hipGetLastError());
-        DBuf<int64_t> runid(m);
-        scan_i32_to_i64(head.p, runid.p, m);
-        int64_t last_run = 0;
-        int32_t last_head = 0;
-        DCHK(hipMemcpyAsync(&last_run, runid.p + (m - 1), sizeof(int64_t), hipMemcpyDeviceToHost, s_));
-        DCHK(hipMemcpyAsync(&last_head, head.p + (m - 1), sizeof(int32_t), hipMemcpyDeviceToHost, s_));
-        DCHK(hipStreamSynchronize(s_));
-        const int64_t nrun = last_run + last_head;
-        DBuf<int64_t> start(nrun + 1);
-        hipLaunchKernelGGL(k_run_starts, dim3(grid(m)), dim3(256), 0, s_, m, head.p, runid.p, start.p);
-        DCHK(hipMemcpyAsync(start.p + nrun, &m, sizeof(int64_t), hipMemcpyHostToDevice, s_));
-        DCHK(hipGetLastError());
-        DevCsr C;
-        C.n = nc;
-        C.nnz = nrun;
-        C.ci.alloc(nrun);
-        C.v.alloc(nrun);
-        C.rp.alloc(nc + 1);
-        DBuf<int64_t> cnt(nc + 1);
-        DCHK(hipMemsetAsync(cnt.p, 0, (nc + 1) * sizeof(int64_t), s_));
-        hipLaunchKernelGGL(k_run_sums, dim3(grid(nrun)), dim3(256), 0, s_, nrun, start.p, keys2.p, vals2.p, t.p,
-                           C.ci.p, C.v.p, cnt.p);
-        DCHK(hipGetLastError());
-        scan_i64(cnt.p, C.rp.p, nc + 1);
-        DCHK(hipStreamSynchronize(s_));
-        return C;
+        return sum_products(K.nnz, nc, s_, [&](uint64_t *keys, int32_t *vals, double *t) {
+            hipLaunchKernelGGL(k_gal_keys, dim3(grid(K.n)), dim3(256), 0, s_, K.n, K.rp.p, K.ci.p, K.v.p, agg, pc,
+                               keys, vals, t);
+        });
     }
 };
 
 }  // namespace
+
+static constexpr int64_t FILL_PIECE = int64_t(1) << 22;   // entries uploaded at a time (50 MB)
+
+template <typename F> static int guarded(std::string &err, F f)
+{
+    try {
+        f();
+        return 0;
+    } catch (HipError &e) {
+        err = e.what();
+        return -3;
+    } catch (std::bad_alloc &) {
+        err = "host allocation failed";
+        return -4;
+    }
+}
+
+DevCsr::~DevCsr()
+{
+    for (void *p : {(void *)rp, (void *)ci, (void *)v})
+        if (p) (void)hipFree(p);
+}
+
+int csr_to_device(const CsrView &K, void *stream, DevCsr &D, std::string &err)
+{
+    return guarded(err, [&] {
+        hipStream_t s = (hipStream_t)stream;
+        BufCsr B;
+        B.n = K.n;
+        B.nnz = K.nnz();
+        up(B.rp, K.rp, K.n + 1, s);
+        up(B.ci, K.ci, K.nnz(), s);
+        up(B.v, K.v, K.nnz(), s);
+        DCHK(hipStreamSynchronize(s));
+        D = B.give();
+    });
+}
+
+int kp_on_device(const DevCsr &K, const int32_t *agg, const double *pc, void *stream, DevCsr &KP,
+                 std::vector<int64_t> &rp, int64_t &max_gap, std::string &err)
+{
+    return guarded(err, [&] {
+        hipStream_t s = (hipStream_t)stream;
+        BufCsr P = sum_products(K.nnz, K.n, s, [&](uint64_t *keys, int32_t *vals, double *t) {
+            hipLaunchKernelGGL(k_kp_keys, dim3(grid(K.n)), dim3(256), 0, s, K.n, K.rp, K.ci, K.v, agg, pc, keys, vals, t);
+        });
+        DBuf<unsigned int> gap(1);
+        unsigned int h_gap = 0;
+        DCHK(hipMemsetAsync(gap.p, 0, sizeof(unsigned int), s));
+        hipLaunchKernelGGL(k_max_gap, dim3(grid(P.n)), dim3(256), 0, s, P.n, P.rp.p, P.ci.p, gap.p);
+        DCHK(hipGetLastError());
+        down(rp, P.rp, P.n + 1, s);
+        DCHK(hipMemcpyAsync(&h_gap, gap.p, sizeof(h_gap), hipMemcpyDeviceToHost, s));
+        DCHK(hipStreamSynchronize(s));
+        max_gap = h_gap;
+        KP = P.give();
+    });
+}
+
+int fill_sell(const DevCsr &K, int C, int64_t nslices, const SellFill &F, void *stream, std::string &err)
+{
+    return guarded(err, [&] {
+        hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)nslices), dim3(256), 0, (hipStream_t)stream, K.n, (int64_t)0,
+                           (int64_t)0, K.rp, K.ci, K.v, C, (int64_t)0, F);
+        DCHK(hipGetLastError());
+    });
+}
+
+int fill_sell(const CsrView &K, int C, const SellFill &F, void *stream, std::string &err)
+{
+    return guarded(err, [&] {
+        hipStream_t s = (hipStream_t)stream;
+        const int64_t win = 4 * C;   // rows of a sorted window: the pieces end between windows
+        for (int64_t a = 0, b; a < K.n; a = b) {
+            b = std::min(K.n, a + win);
+            while (b < K.n && K.rp[std::min(K.n, b + win)] - K.rp[a] <= FILL_PIECE) b = std::min(K.n, b + win);
+            const int64_t e0 = K.rp[a], m = K.rp[b] - e0;
+            DBuf<int64_t> rp;
+            DBuf<int32_t> ci;
+            DBuf<double> v;
+            up(rp, K.rp + a, b - a + 1, s);
+            up(ci, K.ci + e0, m, s);
+            up(v, K.v + e0, m, s);
+            hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)((b - a + C - 1) / C)), dim3(256), 0, s, K.n, a, e0, rp.p, ci.p,
+                               v.p, C, a / C, F);
+            DCHK(hipGetLastError());
+            DCHK(hipStreamSynchronize(s));
+        }
+    });
+}
 
 int build_hierarchy_on_device(const CsrView &K0, const double *w, const SetupParams &prm, HostHierarchy &H,
                               std::string &err, void *stream, DevSetupInfo *info)
@@ -554,7 +765,9 @@ int build_hierarchy_on_device(const CsrView &K0, const double *w, const SetupPar
     }
     try {
         DeviceCoarsener dc((hipStream_t)stream, info);
-        return build_hierarchy(K0, w, prm, H, err, &dc);
+        const int rc = build_hierarchy(K0, w, prm, H, err, &dc);
+        if (rc == 0) dc.finish();
+        return rc;
     } catch (InputError &e) {
         err = e.what();
         return -1;

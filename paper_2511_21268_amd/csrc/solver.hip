@@ -36,7 +36,7 @@ using namespace amgk;
 using amgiga::CsrView;
 using amgiga::HostHierarchy;
 using amgiga::SellHost;
-using amgiga::build_sell;
+using amgiga::sell_layout;
 using amgiga::count_shared;
 
 static thread_local std::string g_err;
@@ -309,39 +309,26 @@ struct amg_ctx {
     // order and stores shared offsets; every other image is sorted by row
     // length within windows of 4 slices (the slices of one 4-wave block).
     // Without: row order and per-entry indices everywhere.
-    DevMat upload_sell(const CsrView &K, int C, bool want64, bool want32, int64_t ncols = 0)
+    // The layout comes from the host (K.ci is read for it unless max_gap is
+    // given, for an image without shared offsets); the entries are filled in on
+    // the device, from D, the device copy of K, if there is one.
+    DevMat upload_sell(const CsrView &K, int C, bool want64, bool want32, int64_t ncols = 0,
+                       const amgiga::DevCsr *D = nullptr, int64_t max_gap = -1)
     {
         SellHost S;
         const bool square = ncols <= 0;
         if (prm.slice_offsets == 0) {
-            build_sell(K, C, want64, want32, false, 0, S);
+            sell_layout(K, C, false, 0, max_gap, S);
         } else {
             const int64_t ns = (K.n + C - 1) / C;
             const bool stencil = square && 2 * count_shared(K, C) >= ns;
-            build_sell(K, C, want64, want32, stencil, stencil ? 0 : 4 * C, S);
+            sell_layout(K, C, stencil, stencil ? 0 : 4 * C, max_gap, S);
         }
         DevMat A;
         A.n = K.n; A.ncols = square ? K.n : ncols; A.sorted = S.sorted;
         A.nnz = K.nnz(); A.nslices = S.nslices; A.stored = S.stored; A.idx16 = S.idx16; A.C = C;
         A.nshared = S.nshared; A.index_bytes = S.index_bytes;
         A.split = C == SLICE ? split_waves(S.nslices, S.stored) : split_waves_blk(S.nslices);
-        if (A.split > 1 && !S.d16.empty()) {
-            // running column before each group of 8 deltas
-            std::vector<int32_t> gcol(S.d16.size() / 8);
-            for (int64_t sl = 0; sl < S.nslices; sl++) {
-                if (S.ibase[sl] < 0) continue;
-                const int64_t ng = (S.soff[sl + 1] - S.soff[sl]) / (8 * C);
-                for (int r = 0; r < C; r++) {
-                    int32_t col = S.col0[sl * C + r];
-                    for (int64_t g = 0; g < ng; g++) {
-                        gcol[S.ibase[sl] / 8 + g * C + r] = col;
-                        const uint16_t *d = &S.d16[S.ibase[sl] + (g * C + r) * 8];
-                        for (int k = 0; k < 8; k++) col += d[k];
-                    }
-                }
-            }
-            A.gcol = upload(gcol);
-        }
         A.soff = upload(S.soff);
         A.ibase = upload(S.ibase);
         if (!S.shoff.empty()) {
@@ -362,12 +349,56 @@ struct amg_ctx {
             }
         }
         if (S.sorted) A.perm = upload(S.perm);
-        if (want64) A.v64 = upload(S.v64);
-        if (want32) A.v32 = upload(S.v32);
-        if (!S.d16.empty()) A.d16 = upload(S.d16);
-        if (!S.col0.empty()) A.col0 = upload(S.col0);
-        if (!S.c32.empty()) A.c32 = upload(S.c32);
+        if (want64) A.v64 = alloc<double>(S.stored);
+        if (want32) A.v32 = alloc<float>(S.stored);
+        if (S.indices > 0 && S.idx16) {
+            A.d16 = alloc<uint16_t>(S.indices);
+            A.col0 = alloc<int32_t>(S.nslices * C);
+            // running column before each group of 8 deltas
+            if (A.split > 1) A.gcol = alloc<int32_t>(S.indices / 8);
+        } else if (S.indices > 0) {
+            A.c32 = alloc<int32_t>(S.indices);
+        }
+        if (S.nslices > 0) {
+            int32_t *ulen = S.nshared > 0 ? upload(S.ulen) : nullptr;
+            const amgiga::SellFill F{A.soff, A.ibase, A.perm, A.shoff, ulen, A.v64, A.v32, A.d16, A.col0, A.c32, A.gcol};
+            std::string err;
+            if (D && D->rp) check_setup(amgiga::fill_sell(*D, C, S.nslices, F, stream, err), err);
+            else check_setup(amgiga::fill_sell(K, C, F, stream, err), err);
+            HIPCHK(hipStreamSynchronize(stream));   // before ulen and D go
+            release(ulen);
+        }
         return A;
+    }
+    void check_setup(int rc, const std::string &err)
+    {
+        if (rc == 0) return;
+        set_err(err);
+        throw Fail{(amg_status)rc};
+    }
+    // K P of level l, on the device where K has a device copy, else on the host
+    // (tune_blocks makes several images of one product).
+    struct KpProduct {
+        amgiga::DevCsr dev;
+        amgiga::Csr host;           // row pointers, and the entries of a host product
+        int64_t max_gap = -1;
+    };
+    KpProduct kp_product(const CsrView &K, const amgiga::DevCsr *D, int l)
+    {
+        KpProduct p;
+        std::string err;
+        if (D->rp) {
+            check_setup(amgiga::kp_on_device(*D, lev[l].agg, lev[l].pc64, stream, p.dev, p.host.rp, p.max_gap, err),
+                        err);
+            p.host.n = K.n;
+        } else {
+            p.host = amgiga::kp_product(K, host.lev[l + 1].n, host.lev[l].agg.data(), host.lev[l].pc.data());
+        }
+        return p;
+    }
+    DevMat upload_kp(const KpProduct &p, int C, int l)
+    {
+        return upload_sell(amgiga::view(p.host), C, !fp32(), fp32(), host.lev[l + 1].n, &p.dev, p.max_gap);
     }
     // Wavefronts per slice of the single-vector passes.  One wave per slice
     // keeps the GPU's loads going from about 1,200 slices (4-5 per CU) on:
@@ -471,7 +502,7 @@ struct amg_ctx {
     // row on the SELL-64 images or 4, 8 or 16 on SELL-(64/lanes) images with
     // 256 or 512 threads per block, timed on the level-0 K P pass and a
     // level-1 pass; the fastest variant's images are then built for every level.
-    void tune_blocks(const CsrView &K0)
+    void tune_blocks(const CsrView &K0, const std::vector<amgiga::DevCsr> &dev)
     {
         blk_alloc();
         const bool f32 = fp32();
@@ -514,15 +545,15 @@ struct amg_ctx {
         best.ms = f32 ? time_passes([&] { variant_passes<float>(lvl0); }) : time_passes([&] { variant_passes<double>(lvl0); });
         tune_log.push_back({"lpr=1 threads=256", best.ms});
         // level-0 K P product, formed once for every candidate image
-        amgiga::Csr kp0;
-        if (nlev > 1) kp0 = amgiga::kp_product(K0, host.lev[1].n, host.lev[0].agg.data(), host.lev[0].pc.data());
+        KpProduct kp0;
+        if (nlev > 1) kp0 = kp_product(K0, &dev[0], 0);
         struct Imgs { DevMat a0, a1, kp0; };
         Imgs keep;
         for (int lpr : {4, 8, 16}) {
             Imgs im;
-            if (lvl0) im.a0 = upload_sell(K0, 64 / lpr, true, f32);
-            if (nlev > 2) im.a1 = upload_sell(amgiga::view(host.lev[1].K), 64 / lpr, !f32, f32);
-            if (nlev > 1) im.kp0 = upload_sell(amgiga::view(kp0), 64 / lpr, !f32, f32, host.lev[1].n);
+            if (lvl0) im.a0 = upload_sell(K0, 64 / lpr, true, f32, 0, &dev[0]);
+            if (nlev > 2) im.a1 = upload_sell(amgiga::view(host.lev[1].K), 64 / lpr, !f32, f32, 0, &dev[1]);
+            if (nlev > 1) im.kp0 = upload_kp(kp0, 64 / lpr, 0);
             lev[0].Ab = im.a0;
             if (nlev > 2) lev[1].Ab = im.a1;
             if (nlev > 1) lev[0].KPb = im.kp0;
@@ -552,11 +583,9 @@ struct amg_ctx {
             if (nlev > 2) lev[1].Ab = keep.a1;
             if (nlev > 1) lev[0].KPb = keep.kp0;
             for (int l = 2; l < nlev - 1; l++)
-                lev[l].Ab = upload_sell(amgiga::view(host.lev[l].K), 64 / best.lpr, !f32, f32);
+                lev[l].Ab = upload_sell(amgiga::view(host.lev[l].K), 64 / best.lpr, !f32, f32, 0, &dev[l]);
             for (int l = 1; l < nlev - 1; l++) {
-                amgiga::Csr kp = amgiga::kp_product(amgiga::view(host.lev[l].K), host.lev[l + 1].n,
-                                                    host.lev[l].agg.data(), host.lev[l].pc.data());
-                lev[l].KPb = upload_sell(amgiga::view(kp), 64 / best.lpr, !f32, f32, host.lev[l + 1].n);
+                lev[l].KPb = upload_kp(kp_product(amgiga::view(host.lev[l].K), &dev[l], l), 64 / best.lpr, l);
             }
             blk_img_lpr = best.lpr;
         }
@@ -1413,6 +1442,20 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
     c->lev.resize(c->nlev);
     const bool fp32 = c->fp32();
     const size_t vsz = fp32 ? sizeof(float) : sizeof(double);
+    // Device copies of the level matrices, until the images are built (a device
+    // set-up left its own): the products K P are formed from them and the
+    // images filled.  They, the products' work space and the images take up to
+    // 100 bytes an entry of K; with less memory than that, or entries past the
+    // 32-bit indices of the products, the host forms K P and the images are
+    // filled from the host's matrices piece by piece.  3D p=3 h=1/32 (10.5M
+    // entries), set-up and first V-cycle: 178 ms with the products and images
+    // made on the host, 96 ms so.
+    std::vector<amgiga::DevCsr> dev = std::move(c->setup_info.levels);
+    size_t mem_free = 0, mem_total = 0;
+    HIPCHK(hipMemGetInfo(&mem_free, &mem_total));
+    const bool copies = K0.nnz() < (int64_t(1) << 31) && (double)mem_free > 100.0 * (double)K0.nnz();
+    if (!copies) dev.clear();
+    dev.resize(c->nlev);
     for (int l = 0; l < c->nlev; l++) {
         auto &hl = H.lev[l];
         Level &L = c->lev[l];
@@ -1423,7 +1466,11 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
             CsrView K = l == 0 ? K0 : amgiga::view(hl.K);
             // the Chebyshev passes of coarse levels may take the CSR image
             if (c->prm.smoother == 2 && l > 0) L.A = c->upload_image(K);
-            else L.A = c->upload_sell(K, SLICE, (l == 0) || !fp32, fp32);
+            else {
+                std::string err;
+                if (copies && !dev[l].rp && !c->general_vcycle()) c->check_setup(amgiga::csr_to_device(K, c->stream, dev[l], err), err);
+                L.A = c->upload_sell(K, SLICE, (l == 0) || !fp32, fp32, 0, &dev[l]);
+            }
         }
         L.invd64 = c->upload(hl.invd);
         if (fp32) {
@@ -1431,6 +1478,12 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
             L.invd32 = c->upload(t);
         }
         if (!coarsest) {
+            L.agg = c->upload(hl.agg);
+            L.pc64 = c->upload(hl.pc);
+            if (fp32) {
+                std::vector<float> t(hl.pc.begin(), hl.pc.end());
+                L.pc32 = c->upload(t);
+            }
             if (c->general_vcycle()) {
                 if (!hl.P.rp.empty()) {
                     L.Pm = c->upload_image(amgiga::view(hl.P), H.lev[l + 1].n);
@@ -1438,14 +1491,7 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
                 }
             } else {
                 CsrView K = l == 0 ? K0 : amgiga::view(hl.K);
-                amgiga::Csr kp = amgiga::kp_product(K, H.lev[l + 1].n, hl.agg.data(), hl.pc.data());
-                L.KP = c->upload_sell(amgiga::view(kp), SLICE, !fp32, fp32, H.lev[l + 1].n);
-            }
-            L.agg = c->upload(hl.agg);
-            L.pc64 = c->upload(hl.pc);
-            if (fp32) {
-                std::vector<float> t(hl.pc.begin(), hl.pc.end());
-                L.pc32 = c->upload(t);
+                L.KP = c->upload_kp(c->kp_product(K, &dev[l], l), SLICE, l);
             }
             int64_t nc = H.lev[l + 1].n;
             L.mw = hl.max_members;
@@ -1531,7 +1577,8 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
     HIPCHK(hipEventCreateWithFlags(&c->ev_iter, hipEventDisableTiming));
     c->choose_tail();
     c->tune_xwin();
-    if (c->prm.nrhs > 1) c->tune_blocks(K0);
+    if (c->prm.nrhs > 1) c->tune_blocks(K0, dev);
+    dev.clear();
     HIPCHK(hipStreamSynchronize(c->stream));
     return AMG_OK;
 }

@@ -1,0 +1,60 @@
+"""GPU: the device-filled matrix images (entries from the device copy of the
+matrix, or uploaded in pieces of 4M entries) in every layout: shared offsets,
+sorted windows, 16-bit and 32-bit columns, ragged last slices.  The matrices
+and vectors hold small integers, so K x is exact in any order of the sum."""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def amg():
+    import paper_2511_21268_amd as m
+    assert torch.cuda.is_available()
+    m.lib()
+    return m
+
+
+def _matrix(kind, n):
+    if kind == "band":                       # 41 diagonals: shared offsets
+        k = np.arange(1, 41)
+        return sp.diags([np.full(n, 100.0)] + [np.full(n - s, -1.0) for s in k] * 2, [0, *k, *-k], format="csr")
+    r = np.random.default_rng(n)
+    m = n * 35
+    i, j = r.integers(0, n, m), r.integers(0, n, m)
+    i[: m // 8] //= 9                        # some rows much longer than others
+    if kind == "far":                        # a column gap of n - 1
+        i, j = np.append(i[::9], 0), np.append(j[::9], n - 1)
+    C = sp.coo_matrix((-r.integers(1, 4, len(i)).astype(np.float64), (i, j)), shape=(n, n)).tocsr()
+    C = C + C.T
+    C.setdiag(0.0)
+    C.eliminate_zeros()
+    return (C + sp.diags(np.asarray(abs(C).sum(axis=1)).ravel() + 1.0)).tocsr()
+
+
+# 70,001 rows: 5.7M (band) and about 4.8M (ragged) entries, two pieces
+@pytest.mark.parametrize("kind,n", [("band", 90), ("band", 4097), ("band", 70001), ("ragged", 130), ("ragged", 70001),
+                                    ("far", 70001)])
+@pytest.mark.parametrize("kw", [{}, {"setup_device": 1}, {"slice_offsets": 0}, {"smoother": 2}], ids=str)
+def test_images_hold_the_matrix(amg, kind, n, kw):
+    print(f"case images {kind} n={n} {kw}", flush=True)
+    K = _matrix(kind, n)
+    K.sort_indices()
+    ctx = amg.Context(K.indptr.astype(np.int64), K.indices.astype(np.int32), K.data, **kw)
+    x = np.random.default_rng(1).integers(-50, 50, n).astype(np.float64)
+    y = ctx.spmv(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.array_equal(y, K @ x)
+    if kw.get("smoother") == 2:
+        return
+    # K P inside the V-cycle against the same V-cycle without it (the coarse
+    # correction added first): a few sums of the row lengths' terms apart
+    r = torch.from_numpy(np.random.default_rng(2).standard_normal(n)).cuda()
+    z = ctx.vcycle(r)
+    ctx.set_fused_post(False)
+    ref = ctx.vcycle(r)
+    w = int(np.diff(K.indptr).max())
+    assert torch.linalg.norm(z - ref) <= 100 * (w + 10) * 2.0 ** -53 * torch.linalg.norm(ref)
