@@ -97,6 +97,7 @@ __global__ __launch_bounds__(256) void k_tri_inv(int n, int npad, const double *
         for (int i = j + 1; i < n; i++) {
             const double *row = L + (int64_t)i * npad;
             double s = 0.0;
+#pragma unroll 8
             for (int k = j; k < i; k++) s = fma(row[k], Linv[(int64_t)k * npad + j], s);
             Linv[(int64_t)i * npad + j] = -s / row[i];
         }

@@ -7,7 +7,22 @@
 
 namespace amgiga {
 
-// A CSR matrix in device memory, owned (hipMalloc / hipFree).
+// While one exists on a thread, the device memory that these functions release
+// there is kept for their next requests; the outermost gives it back.  All of
+// them then take the same stream.
+class SetupMemory {
+  public:
+    SetupMemory();
+    ~SetupMemory();
+    SetupMemory(const SetupMemory &) = delete;
+    SetupMemory &operator=(const SetupMemory &) = delete;
+    static void trim();   // give back what is idle
+
+  private:
+    void *pool_ = nullptr;
+};
+
+// A CSR matrix in device memory, owned.
 struct DevCsr {
     int64_t n = 0, nnz = 0;
     int64_t *rp = nullptr;
@@ -47,7 +62,7 @@ int csr_to_device(const CsrView &K, void *stream, DevCsr &D, std::string &err);
 // K P (kp_product's bits) from the device copies of K, the aggregates and the
 // prolongator's coefficients; rp: its row pointers on the host, max_gap: the
 // widest column gap within a row.  K has fewer than 2^31 entries.
-int kp_on_device(const DevCsr &K, const int32_t *agg, const double *pc, void *stream, DevCsr &KP,
+int kp_on_device(const DevCsr &K, int64_t nc, const int32_t *agg, const double *pc, void *stream, DevCsr &KP,
                  std::vector<int64_t> &rp, int64_t &max_gap, std::string &err);
 // The entries of a SELL-C image laid out by sell_layout, from the device copy
 // of its matrix; the arrays that are not wanted are NULL (v32 rounds v).

@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <stdexcept>
@@ -44,6 +45,73 @@ struct InputError : std::runtime_error {
         if (e_ != hipSuccess) throw HipError(std::string("HIP error in set-up: ") + hipGetErrorString(e_)); \
     } while (0)
 
+// Device memory of one set-up call: a released block serves the next request
+// of the call that fits it (all work of the call is in one stream, so the next
+// use is ordered behind the last), the rest goes back when the call ends.
+// hipMalloc and hipFree (which waits for the device) took 32 ms of the 96 ms
+// of a set-up of 10.5M entries.
+struct Block { void *p; size_t bytes; };
+struct Pool {
+    std::vector<Block> idle, used;
+    void *take(size_t bytes)
+    {
+        bytes = (bytes + 255) / 256 * 256;
+        idle.reserve(idle.size() + used.size() + 1);   // give() does not allocate
+        used.reserve(used.size() + 1);
+        // the smallest that fits, at most a quarter larger (small ones: 1 MB)
+        size_t best = idle.size();
+        for (size_t k = 0; k < idle.size(); k++)
+            if (idle[k].bytes >= bytes && idle[k].bytes <= std::max(bytes + bytes / 4, size_t(1) << 20) &&
+                (best == idle.size() || idle[k].bytes < idle[best].bytes))
+                best = k;
+        if (best < idle.size()) {
+            used.push_back(idle[best]);
+            idle.erase(idle.begin() + best);
+            return used.back().p;
+        }
+        void *p = nullptr;
+        hipError_t e = hipMalloc(&p, bytes);
+        if (e == hipErrorOutOfMemory && !idle.empty()) {
+            (void)hipGetLastError();
+            trim();
+            e = hipMalloc(&p, bytes);
+        }
+        DCHK(e);
+        used.push_back({p, bytes});
+        return p;
+    }
+    bool give(void *p)
+    {
+        for (size_t k = used.size(); k-- > 0;)
+            if (used[k].p == p) {
+                idle.push_back(used[k]);
+                used.erase(used.begin() + k);
+                return true;
+            }
+        return false;
+    }
+    void trim()
+    {
+        for (Block &b : idle) (void)hipFree(b.p);
+        idle.clear();
+    }
+};
+
+// the running set-up call of this thread
+thread_local Pool *t_pool = nullptr;
+
+void *dev_alloc(size_t bytes)
+{
+    if (t_pool) return t_pool->take(bytes);
+    void *p = nullptr;
+    DCHK(hipMalloc(&p, bytes));
+    return p;
+}
+void dev_free(void *p)
+{
+    if (p && !(t_pool && t_pool->give(p))) (void)hipFree(p);
+}
+
 template <typename T> struct DBuf {
     T *p = nullptr;
     size_t n = 0;
@@ -53,11 +121,11 @@ template <typename T> struct DBuf {
     {
         release();
         n = k;
-        if (k) DCHK(hipMalloc((void **)&p, k * sizeof(T)));
+        if (k) p = (T *)dev_alloc(k * sizeof(T));
     }
     void release()
     {
-        if (p) (void)hipFree(p);
+        dev_free(p);
         p = nullptr;
         n = 0;
     }
@@ -77,15 +145,47 @@ inline unsigned grid(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 // ---- kernels --------------------------------------------------------------
 
+__device__ inline int64_t find_col(const int64_t *rp, const int32_t *ci, int64_t row, int32_t col)
+{
+    int64_t lo = rp[row], hi = rp[row + 1] - 1;
+    while (lo <= hi) {
+        int64_t mid = (lo + hi) >> 1;
+        int32_t c = ci[mid];
+        if (c == col) return mid;
+        if (c < col) lo = mid + 1;
+        else hi = mid - 1;
+    }
+    return -1;
+}
+
+// The kernels that pass over the entries give a row L neighbouring lanes, so
+// that a wavefront reads consecutive entries: bound by memory on the first
+// levels, by the launches on the later ones.  A thread per row, which
+// strides the wavefront's reads by a row, took for the 10.5M entries of the
+// 3D p=3 h=1/32 set-up 9.8 ms in the matching rounds, 7.4 ms in the edge
+// weights, 4.0 ms in the keys of the products; 64 lanes take 0.74, 0.63 and
+// 0.28 ms.  16 lanes below 100 entries a row: matching rounds of 2D p=2
+// (25 a row) 11.8 ms against 26.8 with 64, 2D p=3 (49) 8.5 against 14.5, 3D p=2
+// (114) 1.9 against 2.3 but keys 0.44 against 0.35.
+#define FOR_ROW(L)                                                                      \
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L;             \
+    const int lane = threadIdx.x % L;                                                   \
+    if (i >= n) return;
+#define LAUNCH_ROWS(kernel, n, nnz, s, ...)                                                                      \
+    do {                                                                                                         \
+        if ((nnz) >= 100 * (n))                                                                                  \
+            hipLaunchKernelGGL((kernel<64>), dim3(grid((n) * 64)), dim3(256), 0, s, n, __VA_ARGS__);             \
+        else hipLaunchKernelGGL((kernel<16>), dim3(grid((n) * 16)), dim3(256), 0, s, n, __VA_ARGS__);            \
+        DCHK(hipGetLastError());                                                                                 \
+    } while (0)
+
 __global__ void k_diag(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                        const double *__restrict__ v, double *__restrict__ diag)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    double d = 0.0;
-    for (int64_t k = rp[i]; k < rp[i + 1]; k++)
-        if (ci[k] == i) d = v[k];
-    diag[i] = d;
+    const int64_t k = find_col(rp, ci, i, (int32_t)i);
+    diag[i] = k >= 0 ? v[k] : 0.0;
 }
 
 // 1 / (k_ii + sum_{j != i} |k_ij|), the sum in ascending j after k_ii
@@ -121,29 +221,16 @@ __device__ inline double cij_dev(double kij, double kii, double kjj, double wi, 
     return 1.0 - num / den;
 }
 
-__device__ inline int64_t find_col(const int64_t *rp, const int32_t *ci, int64_t row, int32_t col)
-{
-    int64_t lo = rp[row], hi = rp[row + 1] - 1;
-    while (lo <= hi) {
-        int64_t mid = (lo + hi) >> 1;
-        int32_t c = ci[mid];
-        if (c == col) return mid;
-        if (c < col) lo = mid + 1;
-        else hi = mid - 1;
-    }
-    return -1;
-}
-
 // c of every stored entry (value of row min(i, j)); NaN marks an ineligible
 // entry.  cnt[0] counts entries below the diagonal without a stored transpose.
+template <int L>
 __global__ void k_edge_c(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                          const double *__restrict__ v, const double *__restrict__ diag, const double *__restrict__ w,
                          int positive_only, double *__restrict__ cw, unsigned long long *cnt)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    FOR_ROW(L)
     unsigned long long missing = 0;
-    for (int64_t k = rp[i]; k < rp[i + 1]; k++) {
+    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
         const int64_t j = ci[k];
         double val = __builtin_nan("");
         if (j != i) {
@@ -168,42 +255,57 @@ __global__ void k_edge_c(int64_t n, const int64_t *__restrict__ rp, const int32_
     if (missing) atomicAdd(cnt, missing);
 }
 
-__device__ inline bool precedes(double c, int64_t a, int64_t b, double c2, int64_t a2, int64_t b2)
+// edge (u, v) of weight c before edge (u, v2) of weight c2
+__device__ inline bool edge_precedes(int64_t u, double c, int v, double c2, int v2)
 {
     if (c != c2) return c > c2;
+    const int64_t a = u < v ? u : v, b = u < v ? v : u, a2 = u < v2 ? u : v2, b2 = u < v2 ? v2 : u;
     if (a != a2) return a < a2;
     return b < b2;
 }
 
-// every free vertex points to its best eligible free neighbour (or -1)
+// every free vertex points to its best eligible free neighbour (or -1): each
+// lane the best of its entries, then the best of the lanes (the order is
+// strict, so the best does not depend on who meets it first)
+template <int L>
 __global__ void k_ld_point(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                            const double *__restrict__ cw, const int32_t *__restrict__ mate,
-                           int32_t *__restrict__ ptr, unsigned int *any)
+                           int32_t *__restrict__ ptr)
 {
-    int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= n) return;
-    if (mate[u] >= 0) { ptr[u] = -1; return; }
-    int64_t best = -1, ba = 0, bb = 0;
+    FOR_ROW(L)
+    if (mate[i] >= 0) {
+        if (lane == 0) ptr[i] = -1;
+        return;
+    }
+    int best = -1;
     double bc = 0.0;
-    for (int64_t k = rp[u]; k < rp[u + 1]; k++) {
+    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
         const double c = cw[k];
         if (c != c) continue;
-        const int64_t v = ci[k];
+        const int v = ci[k];
         if (mate[v] >= 0) continue;
-        const int64_t a = u < v ? u : v, b = u < v ? v : u;
-        if (best >= 0 && !precedes(c, a, b, bc, ba, bb)) continue;
-        best = v; bc = c; ba = a; bb = b;
+        if (best >= 0 && !edge_precedes(i, c, v, bc, best)) continue;
+        best = v; bc = c;
     }
-    ptr[u] = (int32_t)best;
-    if (best >= 0) atomicOr(any, 1u);
+#pragma unroll
+    for (int m = L / 2; m > 0; m /= 2) {
+        const int v = __shfl_xor(best, m, L);
+        const double c = __shfl_xor(bc, m, L);
+        if (v >= 0 && (best < 0 || edge_precedes(i, c, v, bc, best))) { best = v; bc = c; }
+    }
+    if (lane == 0) ptr[i] = best;
 }
 
-__global__ void k_ld_match(int64_t n, const int32_t *__restrict__ ptr, int32_t *__restrict__ mate)
+// any: set where a vertex had a candidate, by one store a block (stores of every
+// row to the one word cost 1.2 ms of a round of 36,000 rows)
+__global__ void k_ld_match(int64_t n, const int32_t *__restrict__ ptr, int32_t *__restrict__ mate,
+                           unsigned int *__restrict__ any)
 {
     int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= n) return;
-    const int32_t v = ptr[u];
+    const int32_t v = u < n ? ptr[u] : -1;
     if (v >= 0 && ptr[v] == (int32_t)u) mate[u] = v;
+    if (__syncthreads_or(v >= 0) && threadIdx.x == 0)
+        __hip_atomic_store(any, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __global__ void k_fill_i32(int64_t n, int32_t val, int32_t *__restrict__ d)
@@ -243,17 +345,17 @@ __global__ void k_pairwise(int64_t n, const int32_t *__restrict__ mate, const do
 }
 
 // sort keys (coarse row, coarse column), entry indices and contributions
+template <int L>
 __global__ void k_gal_keys(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                            const double *__restrict__ v, const int32_t *__restrict__ agg, const double *__restrict__ pc,
-                           uint64_t *__restrict__ keys, int32_t *__restrict__ vals, double *__restrict__ t)
+                           uint64_t *__restrict__ keys, int32_t *__restrict__ vals, double *__restrict__ t, int cb)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    FOR_ROW(L)
     const uint64_t I = (uint64_t)(uint32_t)agg[i];
     const double pi = pc[i];
-    for (int64_t k = rp[i]; k < rp[i + 1]; k++) {
+    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
         const int32_t j = ci[k];
-        keys[k] = (I << 32) | (uint64_t)(uint32_t)agg[j];
+        keys[k] = (I << cb) | (uint64_t)(uint32_t)agg[j];
         vals[k] = (int32_t)k;
         t[k] = (pi * v[k]) * pc[j];
     }
@@ -274,20 +376,25 @@ __global__ void k_run_starts(int64_t m, const int32_t *__restrict__ head, const 
     if (head[s]) start[runid[s]] = s;
 }
 
-// one thread per coarse position: the run's contributions in ascending entry
-// index, from +0.0; the column, and a count per coarse row
-__global__ void k_run_sums(int64_t nrun, const int64_t *__restrict__ start, const uint64_t *__restrict__ keys,
-                           const int32_t *__restrict__ vals, const double *__restrict__ t, int32_t *__restrict__ cci,
-                           double *__restrict__ cv, int64_t *__restrict__ rowcnt)
+// one thread per position: the run's contributions in ascending entry index,
+// from +0.0; the column, and the row pointers between the run before and this
+__global__ void k_run_sums(int64_t nrun, int64_t rows, int cb, const int64_t *__restrict__ start,
+                           const uint64_t *__restrict__ keys, const int32_t *__restrict__ vals,
+                           const double *__restrict__ t, int32_t *__restrict__ cci, double *__restrict__ cv,
+                           int64_t *__restrict__ crp)
 {
     int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= nrun) return;
+    const int64_t s0 = start[g], s1 = start[g + 1];
     double acc = 0.0;
-    for (int64_t s = start[g]; s < start[g + 1]; s++) acc = acc + t[vals[s]];
+    for (int64_t s = s0; s < s1; s++) acc = acc + t[vals[s]];
     cv[g] = acc;
-    const uint64_t key = keys[start[g]];
-    cci[g] = (int32_t)(uint32_t)(key & 0xffffffffull);
-    atomicAdd((unsigned long long *)&rowcnt[key >> 32], 1ull);
+    const uint64_t key = keys[s0];
+    cci[g] = (int32_t)(uint32_t)(key & ((uint64_t(1) << cb) - 1));
+    const int64_t row = (int64_t)(key >> cb);
+    for (int64_t r = g == 0 ? 0 : (int64_t)(keys[s0 - 1] >> cb) + 1; r <= row; r++) crp[r] = g;
+    if (g == nrun - 1)
+        for (int64_t r = row + 1; r <= rows; r++) crp[r] = nrun;
 }
 
 __global__ void k_compose(int64_t n, int32_t *__restrict__ agg, double *__restrict__ pc,
@@ -301,29 +408,31 @@ __global__ void k_compose(int64_t n, int32_t *__restrict__ agg, double *__restri
 }
 
 // K P: positions (row, aggregate of the column), entry indices, products
+template <int L>
 __global__ void k_kp_keys(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                           const double *__restrict__ v, const int32_t *__restrict__ agg, const double *__restrict__ pc,
-                          uint64_t *__restrict__ keys, int32_t *__restrict__ vals, double *__restrict__ t)
+                          uint64_t *__restrict__ keys, int32_t *__restrict__ vals, double *__restrict__ t, int cb)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    for (int64_t k = rp[i]; k < rp[i + 1]; k++) {
+    FOR_ROW(L)
+    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
         const int32_t j = ci[k];
-        keys[k] = ((uint64_t)i << 32) | (uint64_t)(uint32_t)agg[j];
+        keys[k] = ((uint64_t)i << cb) | (uint64_t)(uint32_t)agg[j];
         vals[k] = (int32_t)k;
         t[k] = v[k] * pc[j];
     }
 }
 
-// widest column gap within a row
+// widest column gap within a row; a wavefront's rows are gridDim.x * 256 / L apart
+template <int L>
 __global__ void k_max_gap(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                           unsigned int *__restrict__ gap)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
     int m = 0;
-    for (int64_t k = rp[i] + 1; k < rp[i + 1]; k++) m = max(m, ci[k] - ci[k - 1]);
-    if (m > 0) atomicMax(gap, (unsigned int)m);
+    for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L; i < n; i += (int64_t)gridDim.x * 256 / L)
+        for (int64_t k = rp[i] + 1 + threadIdx.x % L; k < rp[i + 1]; k += L) m = max(m, ci[k] - ci[k - 1]);
+#pragma unroll
+    for (int d = 32; d > 0; d /= 2) m = max(m, __shfl_xor(m, d));
+    if (threadIdx.x % 64 == 0 && m > 0) atomicMax(gap, (unsigned int)m);
 }
 
 // One block per slice of a SELL-C image, a thread per row and group of 8
@@ -444,19 +553,20 @@ template <typename TI, typename TO> void scan(const TI *in, TO *out, int64_t n, 
 }
 
 // CSR (rows x cols) of sums of products: make_keys writes each of the m
-// products' position (row << 32 | column), its index (ascending order of the
+// products' position (row << cb | column), its index (ascending order of the
 // sum) and its value; equal positions are summed in index order from +0.0.
 template <typename Keys>
-BufCsr sum_products(int64_t m, int64_t rows, hipStream_t s_, Keys make_keys)
+BufCsr sum_products(int64_t m, int64_t rows, int64_t cols, hipStream_t s_, Keys make_keys)
 {
     DBuf<uint64_t> keys(m), keys2(m);
     DBuf<int32_t> vals(m), vals2(m), head(m);
     DBuf<double> t(m);
-    make_keys(keys.p, vals.p, t.p);
+    int cb = 1, rb = 1;   // bits of a column and of a row: the sort's passes go by their sum
+    while ((int64_t(1) << cb) < cols) cb++;
+    while ((int64_t(1) << rb) < rows) rb++;
+    const int end_bit = cb + rb;
+    make_keys(keys.p, vals.p, t.p, cb);
     DCHK(hipGetLastError());
-    int bits = 1;
-    while ((int64_t(1) << bits) < rows) bits++;
-    const int end_bit = 32 + bits;
     {
         size_t b = 0;
         DCHK(hipcub::DeviceRadixSort::SortPairs(nullptr, b, keys.p, keys2.p, vals.p, vals2.p, (int)m, 0, end_bit,
@@ -487,12 +597,9 @@ BufCsr sum_products(int64_t m, int64_t rows, hipStream_t s_, Keys make_keys)
     C.ci.alloc(nrun);
     C.v.alloc(nrun);
     C.rp.alloc(rows + 1);
-    DBuf<int64_t> cnt(rows + 1);
-    DCHK(hipMemsetAsync(cnt.p, 0, (rows + 1) * sizeof(int64_t), s_));
-    hipLaunchKernelGGL(k_run_sums, dim3(grid(nrun)), dim3(256), 0, s_, nrun, start.p, keys2.p, vals2.p, t.p,
-                       C.ci.p, C.v.p, cnt.p);
+    hipLaunchKernelGGL(k_run_sums, dim3(grid(nrun)), dim3(256), 0, s_, nrun, rows, cb, start.p, keys2.p, vals2.p, t.p,
+                       C.ci.p, C.v.p, C.rp.p);
     DCHK(hipGetLastError());
-    scan(cnt.p, C.rp.p, rows + 1, s_);
     DCHK(hipStreamSynchronize(s_));
     return C;
 }
@@ -569,6 +676,7 @@ class DeviceCoarsener : public Coarsener {
     }
 
   private:
+    static constexpr int ROUNDS = 4;
     hipStream_t s_;
     DevSetupInfo *info_;
     BufCsr l0_, cur_;
@@ -599,31 +707,35 @@ class DeviceCoarsener : public Coarsener {
     {
         DBuf<double> diag(K.n), cw(K.nnz ? K.nnz : 1);
         DBuf<unsigned long long> cnt(1);
-        DBuf<unsigned int> any(1);
+        DBuf<unsigned int> any(ROUNDS);
         DBuf<int32_t> ptr(K.n);
         DCHK(hipMemsetAsync(cnt.p, 0, sizeof(unsigned long long), s_));
         hipLaunchKernelGGL(k_diag, dim3(grid(K.n)), dim3(256), 0, s_, K.n, K.rp.p, K.ci.p, K.v.p, diag.p);
-        hipLaunchKernelGGL(k_edge_c, dim3(grid(K.n)), dim3(256), 0, s_, K.n, K.rp.p, K.ci.p, K.v.p, diag.p, w,
-                           positive_only, cw.p, cnt.p);
+        LAUNCH_ROWS(k_edge_c, K.n, K.nnz, s_, K.rp.p, K.ci.p, K.v.p, diag.p, w, positive_only, cw.p, cnt.p);
         hipLaunchKernelGGL(k_fill_i32, dim3(grid(K.n)), dim3(256), 0, s_, K.n, -1, mate);
         DCHK(hipGetLastError());
         unsigned long long missing = 0;
         DCHK(hipMemcpyAsync(&missing, cnt.p, sizeof(missing), hipMemcpyDeviceToHost, s_));
         DCHK(hipStreamSynchronize(s_));
         if (missing) throw InputError("device set-up needs a structurally symmetric matrix");
-        // at most n/2 + 1 rounds: each round with a candidate matches a pair
+        // at most n/2 + 1 rounds: each round with a candidate matches a pair.
+        // ROUNDS at a time, one wait for them; those past the first round
+        // without a candidate change nothing and are not counted.
         int rounds = 0;
-        for (int64_t r = 0; r <= K.n / 2 + 1; r++) {
-            unsigned int h_any = 0;
-            DCHK(hipMemsetAsync(any.p, 0, sizeof(unsigned int), s_));
-            hipLaunchKernelGGL(k_ld_point, dim3(grid(K.n)), dim3(256), 0, s_, K.n, K.rp.p, K.ci.p, cw.p, mate,
-                               ptr.p, any.p);
-            hipLaunchKernelGGL(k_ld_match, dim3(grid(K.n)), dim3(256), 0, s_, K.n, ptr.p, mate);
+        for (int64_t r = 0; r <= K.n / 2 + 1; r += ROUNDS) {
+            unsigned int h_any[ROUNDS];
+            DCHK(hipMemsetAsync(any.p, 0, sizeof(h_any), s_));
+            for (int k = 0; k < ROUNDS; k++) {
+                LAUNCH_ROWS(k_ld_point, K.n, K.nnz, s_, K.rp.p, K.ci.p, cw.p, mate, ptr.p);
+                hipLaunchKernelGGL(k_ld_match, dim3(grid(K.n)), dim3(256), 0, s_, K.n, ptr.p, mate, any.p + k);
+            }
             DCHK(hipGetLastError());
-            DCHK(hipMemcpyAsync(&h_any, any.p, sizeof(h_any), hipMemcpyDeviceToHost, s_));
+            DCHK(hipMemcpyAsync(h_any, any.p, sizeof(h_any), hipMemcpyDeviceToHost, s_));
             DCHK(hipStreamSynchronize(s_));
-            rounds++;
-            if (!h_any) break;
+            int k = 0;
+            while (k < ROUNDS && h_any[k]) k++;
+            rounds += k < ROUNDS ? k + 1 : ROUNDS;
+            if (k < ROUNDS) break;
         }
         if (info_) {
             info_->rounds_total += rounds;
@@ -653,9 +765,8 @@ class DeviceCoarsener : public Coarsener {
 
     BufCsr galerkin(const BufCsr &K, int64_t nc, const int32_t *agg, const double *pc)
     {
-        return sum_products(K.nnz, nc, s_, [&](uint64_t *keys, int32_t *vals, double *t) {
-            hipLaunchKernelGGL(k_gal_keys, dim3(grid(K.n)), dim3(256), 0, s_, K.n, K.rp.p, K.ci.p, K.v.p, agg, pc,
-                               keys, vals, t);
+        return sum_products(K.nnz, nc, nc, s_, [&](uint64_t *keys, int32_t *vals, double *t, int cb) {
+            LAUNCH_ROWS(k_gal_keys, K.n, K.nnz, s_, K.rp.p, K.ci.p, K.v.p, agg, pc, keys, vals, t, cb);
         });
     }
 };
@@ -680,8 +791,24 @@ template <typename F> static int guarded(std::string &err, F f)
 
 DevCsr::~DevCsr()
 {
-    for (void *p : {(void *)rp, (void *)ci, (void *)v})
-        if (p) (void)hipFree(p);
+    for (void *p : {(void *)rp, (void *)ci, (void *)v}) dev_free(p);
+}
+
+SetupMemory::SetupMemory()
+{
+    if (!t_pool) pool_ = t_pool = new Pool();
+}
+void SetupMemory::trim()
+{
+    if (t_pool) t_pool->trim();
+}
+SetupMemory::~SetupMemory()
+{
+    if (!pool_) return;
+    t_pool->trim();
+    // what is still out (nothing, unless a call failed) is freed by its owner
+    t_pool = nullptr;
+    delete (Pool *)pool_;
 }
 
 int csr_to_device(const CsrView &K, void *stream, DevCsr &D, std::string &err)
@@ -699,18 +826,19 @@ int csr_to_device(const CsrView &K, void *stream, DevCsr &D, std::string &err)
     });
 }
 
-int kp_on_device(const DevCsr &K, const int32_t *agg, const double *pc, void *stream, DevCsr &KP,
+int kp_on_device(const DevCsr &K, int64_t nc, const int32_t *agg, const double *pc, void *stream, DevCsr &KP,
                  std::vector<int64_t> &rp, int64_t &max_gap, std::string &err)
 {
     return guarded(err, [&] {
         hipStream_t s = (hipStream_t)stream;
-        BufCsr P = sum_products(K.nnz, K.n, s, [&](uint64_t *keys, int32_t *vals, double *t) {
-            hipLaunchKernelGGL(k_kp_keys, dim3(grid(K.n)), dim3(256), 0, s, K.n, K.rp, K.ci, K.v, agg, pc, keys, vals, t);
+        BufCsr P = sum_products(K.nnz, K.n, nc, s, [&](uint64_t *keys, int32_t *vals, double *t, int cb) {
+            LAUNCH_ROWS(k_kp_keys, K.n, K.nnz, s, K.rp, K.ci, K.v, agg, pc, keys, vals, t, cb);
         });
         DBuf<unsigned int> gap(1);
         unsigned int h_gap = 0;
         DCHK(hipMemsetAsync(gap.p, 0, sizeof(unsigned int), s));
-        hipLaunchKernelGGL(k_max_gap, dim3(grid(P.n)), dim3(256), 0, s, P.n, P.rp.p, P.ci.p, gap.p);
+        hipLaunchKernelGGL((k_max_gap<16>), dim3(std::min(grid(P.n * 16), 512u)), dim3(256), 0, s, P.n, P.rp.p, P.ci.p,
+                           gap.p);
         DCHK(hipGetLastError());
         down(rp, P.rp, P.n + 1, s);
         DCHK(hipMemcpyAsync(&h_gap, gap.p, sizeof(h_gap), hipMemcpyDeviceToHost, s));

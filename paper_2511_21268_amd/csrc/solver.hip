@@ -317,13 +317,7 @@ struct amg_ctx {
     {
         SellHost S;
         const bool square = ncols <= 0;
-        if (prm.slice_offsets == 0) {
-            sell_layout(K, C, false, 0, max_gap, S);
-        } else {
-            const int64_t ns = (K.n + C - 1) / C;
-            const bool stencil = square && 2 * count_shared(K, C) >= ns;
-            sell_layout(K, C, stencil, stencil ? 0 : 4 * C, max_gap, S);
-        }
+        sell_layout(K, C, prm.slice_offsets && square, prm.slice_offsets ? 4 * C : 0, max_gap, S);
         DevMat A;
         A.n = K.n; A.ncols = square ? K.n : ncols; A.sorted = S.sorted;
         A.nnz = K.nnz(); A.nslices = S.nslices; A.stored = S.stored; A.idx16 = S.idx16; A.C = C;
@@ -388,7 +382,7 @@ struct amg_ctx {
         KpProduct p;
         std::string err;
         if (D->rp) {
-            check_setup(amgiga::kp_on_device(*D, lev[l].agg, lev[l].pc64, stream, p.dev, p.host.rp, p.max_gap, err),
+            check_setup(amgiga::kp_on_device(*D, host.lev[l + 1].n, lev[l].agg, lev[l].pc64, stream, p.dev, p.host.rp, p.max_gap, err),
                         err);
             p.host.n = K.n;
         } else {
@@ -1449,10 +1443,14 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
     // 32-bit indices of the products, the host forms K P and the images are
     // filled from the host's matrices piece by piece.  3D p=3 h=1/32 (10.5M
     // entries), set-up and first V-cycle: 178 ms with the products and images
-    // made on the host, 96 ms so.
+    // made on the host, 96 ms so (all else equal).
     std::vector<amgiga::DevCsr> dev = std::move(c->setup_info.levels);
     size_t mem_free = 0, mem_total = 0;
     HIPCHK(hipMemGetInfo(&mem_free, &mem_total));
+    if ((double)mem_free <= 100.0 * (double)K0.nnz()) {
+        amgiga::SetupMemory::trim();
+        HIPCHK(hipMemGetInfo(&mem_free, &mem_total));
+    }
     const bool copies = K0.nnz() < (int64_t(1) << 31) && (double)mem_free > 100.0 * (double)K0.nnz();
     if (!copies) dev.clear();
     dev.resize(c->nlev);
@@ -1577,7 +1575,10 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
     HIPCHK(hipEventCreateWithFlags(&c->ev_iter, hipEventDisableTiming));
     c->choose_tail();
     c->tune_xwin();
-    if (c->prm.nrhs > 1) c->tune_blocks(K0, dev);
+    if (c->prm.nrhs > 1) {
+        amgiga::SetupMemory::trim();
+        c->tune_blocks(K0, dev);
+    }
     dev.clear();
     HIPCHK(hipStreamSynchronize(c->stream));
     return AMG_OK;
@@ -1665,6 +1666,7 @@ static amg_status setup_common(int64_t n, const int64_t *row_ptr, const int32_t 
         c->prm = P;
         c->host_only = host_only;
         c->stream = (hipStream_t)hip_stream;
+        amgiga::SetupMemory memory;
         amgiga::SetupParams sp;
         sp.sweeps = P.sweeps_per_level;
         sp.max_coarse = P.max_coarse;

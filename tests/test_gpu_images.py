@@ -58,3 +58,23 @@ def test_images_hold_the_matrix(amg, kind, n, kw):
     ref = ctx.vcycle(r)
     w = int(np.diff(K.indptr).max())
     assert torch.linalg.norm(z - ref) <= 100 * (w + 10) * 2.0 ** -53 * torch.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("half", [1, 8, 49, 50, 70])
+def test_device_setup_either_side_of_the_lanes_rule(amg, half):
+    """3 to 141 entries a row, 16 or 64 lanes a row: aggregates, prolongator and
+    coarse matrix of the host set-up, bit for bit."""
+    print(f"case device set-up band {half}", flush=True)
+    n = 6000
+    r = np.random.default_rng(half)
+    off = [r.uniform(-1.0, -0.1, n - s) for s in range(1, half + 1)]
+    k = np.arange(1, half + 1)
+    K = sp.diags([np.full(n, 2.0 * half + 1.0)] + off * 2, [0, *k, *-k], format="csr")
+    K.sort_indices()
+    arrays = (K.indptr.astype(np.int64), K.indices.astype(np.int32), K.data)
+    dev, host = amg.Context(*arrays, setup_device=1), amg.Context(*arrays, host_only=True)
+    for l in range(host.nlevels - 1):
+        for a, b in zip(dev.aggregates(l), host.aggregates(l)):
+            assert np.array_equal(a, b)
+        for a, b in zip(dev.coarse_matrix(l + 1), host.coarse_matrix(l + 1)):
+            assert np.array_equal(a, b)
