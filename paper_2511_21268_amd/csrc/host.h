@@ -160,10 +160,11 @@ int64_t count_shared(const CsrView &K, int C);
 void build_sell(const CsrView &K, int C, bool want64, bool want32, bool shared, int sigma, SellHost &S);
 // Its layout alone (soff, ibase, perm, offset lists and run tables, sizes): what
 // a device fill of the entries needs.  shared: in row order with offset lists if
-// at least half of the slices have one, else without, sorted by sigma.  max_gap:
+// at least half of the slices have one, else without, sorted by sigma; wide:
+// with lists of up to twice the slice's longest row, too.  max_gap:
 // the widest column gap of a row if known (K.ci may then be NULL unless
 // shared), else -1.
-void sell_layout(const CsrView &K, int C, bool shared, int sigma, int64_t max_gap, SellHost &S);
+void sell_layout(const CsrView &K, int C, bool shared, bool wide, int sigma, int64_t max_gap, SellHost &S);
 // y = K x walked through the image as the kernels walk it (layouts of
 // amg_sell_spmv_host); 0, or -6 with err set when a read would leave its array.
 int sell_spmv_walk(const CsrView &K, int64_t ncols, int C, int layout, const double *x, double *y,

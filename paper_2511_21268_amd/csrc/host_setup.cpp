@@ -1130,19 +1130,26 @@ struct SellRows {
     std::vector<std::vector<int32_t>> U;
 };
 
-// Number of C-row slices whose offset unions would be stored once, and the unions.
-static int64_t shared_lists(const CsrView &K, int C, std::vector<std::vector<int32_t>> &U)
+// The offset unions that an image stores once per slice (empty: per-row
+// indices): those no wider than the slice's longest row (both rounded up to 8).
+// wide: those no wider than twice that and than the longest row of the matrix,
+// which admits the slices of a stencil matrix in which a plane ends and the
+// next begins, whose rows are cut on opposite sides, and leaves every slice as
+// short as the longest.  Returns the number of the former.
+static int64_t shared_lists(const CsrView &K, int C, bool wide, std::vector<std::vector<int32_t>> &U)
 {
     const int64_t ns = (K.n + C - 1) / C;
     U.assign(ns, {});
+    int64_t maxlen = 0;
+    for (int64_t r = 0; r < K.n; r++) maxlen = std::max(maxlen, K.rp[r + 1] - K.rp[r]);
     std::atomic<int64_t> cnt{0};
     parallel_for(ns, [&](int64_t sb, int64_t se) {
         int64_t c = 0;
         for (int64_t s = sb; s < se; s++) {
             int64_t w = 0;
             for (int64_t r = s * C; r < std::min(K.n, (s + 1) * C); r++) w = std::max(w, K.rp[r + 1] - K.rp[r]);
-            if (w > 0) U[s] = slice_offsets(K, s, C, (w + 7) / 8 * 8);
-            c += !U[s].empty();
+            if (w > 0) U[s] = slice_offsets(K, s, C, ((wide ? std::min(2 * w, maxlen) : w) + 7) / 8 * 8);
+            c += !U[s].empty() && (int64_t)U[s].size() <= (w + 7) / 8 * 8;
         }
         cnt += c;
     }, 1);
@@ -1151,12 +1158,12 @@ static int64_t shared_lists(const CsrView &K, int C, std::vector<std::vector<int
 int64_t count_shared(const CsrView &K, int C)
 {
     std::vector<std::vector<int32_t>> U;
-    return shared_lists(K, C, U);
+    return shared_lists(K, C, false, U);
 }
 
 // SELL-C image of a CSR matrix (slice height C rows; group layout of kernels.h).
-// With `shared`, a slice whose offset union is no wider than its longest row
-// (both rounded up to 8) stores the union once; the others keep per-row indices.
+// With `shared`, the slices of shared_lists store their offset union once; the
+// others keep per-row indices.
 // With sigma > 0 (no shared offsets then), the rows of every window of sigma
 // consecutive rows are placed in the window's slots by decreasing length (ties
 // by index), so the slices of a window pad to similar lengths; perm[slot]
@@ -1183,15 +1190,14 @@ static void layout_rows(const CsrView &K, int C, bool shared, int sigma, int64_t
     if (S.sorted) S.perm = rowof;
     std::vector<int64_t> wd(S.nslices);
     std::vector<std::vector<int32_t>> &U = R.U;
-    const bool known = shared && (int64_t)U.size() == S.nslices;
-    if (!known) U.assign(S.nslices, {});
+    if (!shared) U.assign(S.nslices, {});
+    else if ((int64_t)U.size() != S.nslices) shared_lists(K, C, false, U);
     parallel_for(S.nslices, [&](int64_t sb, int64_t se) {
         for (int64_t s = sb; s < se; s++) {
             int64_t w = 0;
             for (int64_t q = s * C; q < (s + 1) * C; q++)
                 if (rowof[q] >= 0) w = std::max(w, len(rowof[q]));
             wd[s] = (w + 7) / 8 * 8;
-            if (shared && !known && w > 0) U[s] = slice_offsets(K, s, C, wd[s]);
         }
     }, 1);
     S.soff.assign(S.nslices + 1, 0);
@@ -1277,10 +1283,10 @@ static void layout_rows(const CsrView &K, int C, bool shared, int sigma, int64_t
     }
 }
 
-void sell_layout(const CsrView &K, int C, bool shared, int sigma, int64_t max_gap, SellHost &S)
+void sell_layout(const CsrView &K, int C, bool shared, bool wide, int sigma, int64_t max_gap, SellHost &S)
 {
     SellRows R;
-    if (shared) shared = 2 * shared_lists(K, C, R.U) >= (int64_t)((K.n + C - 1) / C);
+    if (shared) shared = 2 * shared_lists(K, C, wide, R.U) >= (int64_t)((K.n + C - 1) / C);
     if (!shared) R.U.clear();
     layout_rows(K, C, shared, shared ? 0 : sigma, max_gap, S, R);
 }

@@ -317,7 +317,13 @@ struct amg_ctx {
     {
         SellHost S;
         const bool square = ncols <= 0;
-        sell_layout(K, C, prm.slice_offsets && square, prm.slice_offsets ? 4 * C : 0, max_gap, S);
+        // The block windows need offset lists: 57 of the 1,839 slices of 3D p=3
+        // h=1/48 had none by the narrow rule (a plane ends in them), and their
+        // gathers went on long after the other slices had ended (pass of 16
+        // columns, FP64 201 us, FP32 residual 74; with wide lists, which store
+        // 1% more, 124 and 55).  The single-vector passes gain nothing by them.
+        const bool wide = prm.nrhs > 1 && C == SLICE;
+        sell_layout(K, C, prm.slice_offsets && square, wide, prm.slice_offsets ? 4 * C : 0, max_gap, S);
         DevMat A;
         A.n = K.n; A.ncols = square ? K.n : ncols; A.sorted = S.sorted;
         A.nnz = K.nnz(); A.nslices = S.nslices; A.stored = S.stored; A.idx16 = S.idx16; A.C = C;

@@ -20,6 +20,11 @@ def amg():
 
 
 def _matrix(kind, n):
+    if kind == "planes":                     # box stencil of m^3 points: slices across lines and planes
+        D = sp.diags([np.ones(n - abs(k)) for k in range(-2, 3)], range(-2, 3))
+        A = -sp.kron(sp.kron(D, D), D).tocsr()
+        A.setdiag(200.0)
+        return A
     if kind == "band":                       # 41 diagonals: shared offsets
         k = np.arange(1, 41)
         return sp.diags([np.full(n, 100.0)] + [np.full(n - s, -1.0) for s in k] * 2, [0, *k, *-k], format="csr")
@@ -38,13 +43,17 @@ def _matrix(kind, n):
 
 # 70,001 rows: 5.7M (band) and about 4.8M (ragged) entries, two pieces
 @pytest.mark.parametrize("kind,n", [("band", 90), ("band", 4097), ("band", 70001), ("ragged", 130), ("ragged", 70001),
-                                    ("far", 70001)])
-@pytest.mark.parametrize("kw", [{}, {"setup_device": 1}, {"slice_offsets": 0}, {"smoother": 2}], ids=str)
+                                    ("far", 70001), ("planes", 13), ("planes", 17)])
+@pytest.mark.parametrize("kw", [{}, {"setup_device": 1}, {"slice_offsets": 0}, {"smoother": 2},
+                                {"nrhs": 16}], ids=str)
 def test_images_hold_the_matrix(amg, kind, n, kw):
     print(f"case images {kind} n={n} {kw}", flush=True)
     K = _matrix(kind, n)
     K.sort_indices()
     ctx = amg.Context(K.indptr.astype(np.int64), K.indices.astype(np.int32), K.data, **kw)
+    n = K.shape[0]
+    if kind == "planes" and "nrhs" in kw:    # every slice has an offset list, across the planes too
+        assert ctx.format(0)["shared_slices"] == (n + 63) // 64
     x = np.random.default_rng(1).integers(-50, 50, n).astype(np.float64)
     y = ctx.spmv(torch.from_numpy(x).cuda()).cpu().numpy()
     assert np.array_equal(y, K @ x)
