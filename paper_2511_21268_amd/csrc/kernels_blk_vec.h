@@ -253,7 +253,9 @@ static __global__ __launch_bounds__(256) void k_bfin_strided(const double *__res
 // Final per-column sums of the partials (index order) and the scalar
 // recurrences, masks and iteration counters of the 16 independent solves: block
 // j takes column j (one block for all columns spent 28 us in 32 butterflies
-// per wave; this 5 us, most of it the launch).  With strided != nullptr the
+// per wave).  A partial's 16 columns share a cache line, so a block reads every
+// line of the dots it takes: 4,096 partials 6 us with the first dot's lines
+// alone, the loads before the sums; 9 us with both dots' always read.  With strided != nullptr the
 // per-thread strided sums come from k_bfin_strided (the same values).  host
 // (mapped, may be NULL): the column's flags, which the host's stopping test
 // reads, written there directly.
@@ -265,18 +267,25 @@ static __global__ __launch_bounds__(FIN_THREADS) void k_bfinalize(const double *
     constexpr int NW = FIN_THREADS / 64;
     __shared__ double lds[2 * NW];
     const int j = blockIdx.x, t = threadIdx.x;
+    const bool two = op == BF_PQ_FCG;   // the only one that takes both dots
     double s0 = 0.0, s1 = 0.0;
     if (strided) {
         s0 = strided[j * FIN_THREADS + t];
-        s1 = strided[(NB + j) * FIN_THREADS + t];
+        if (two) s1 = strided[(NB + j) * FIN_THREADS + t];
     } else {
-#pragma unroll 4
-        for (int b = t; b < nblk; b += FIN_THREADS) {
-            s0 += partial[(2 * b) * NB + j];
-            s1 += partial[(2 * b + 1) * NB + j];
+        // at most four partials a thread (bfinalize), all loaded before the sums
+        double v0[4], v1[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int b = t + u * FIN_THREADS;
+            v0[u] = b < nblk ? partial[(2 * b) * NB + j] : 0.0;
+            v1[u] = two && b < nblk ? partial[(2 * b + 1) * NB + j] : 0.0;
         }
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (t + u * FIN_THREADS < nblk) { s0 += v0[u]; s1 += v1[u]; }
     }
-    const double a = block_sum_n<NW>(s0, lds), b = block_sum_n<NW>(s1, lds + NW);
+    const double a = block_sum_n<NW>(s0, lds), b = two ? block_sum_n<NW>(s1, lds + NW) : 0.0;
     if (t != 0) return;
     {
         double *F = sc + B_FLAG * NB + j, *D = sc + B_DONE * NB + j;
