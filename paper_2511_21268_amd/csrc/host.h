@@ -79,6 +79,7 @@ struct Coarsener {
 
 // Status codes follow amg_status.
 int validate_csr(const CsrView &K, std::string &err);
+int validate_rows(const CsrView &K, std::string &err);   // its checks of n and the row pointers alone
 int build_hierarchy(const CsrView &K0, const double *w, const SetupParams &prm,
                     HostHierarchy &H, std::string &err, Coarsener *dev = nullptr);
 // Test vector on the host: `sweeps` l1-Jacobi sweeps on K w = 0 from w0, each

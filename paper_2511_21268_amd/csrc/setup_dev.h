@@ -45,7 +45,7 @@ struct DevSetupInfo {
     int sweeps = 0;         // matching sweeps run
     int rounds_total = 0;   // rounds of locally dominant edges, summed
     int rounds_max = 0;     // and the most in one sweep
-    std::vector<DevCsr> levels;   // the levels' matrices, for the images built next
+    std::vector<DevCsr> levels;   // the levels' matrices, for the images built next (level 0: may be there before)
 };
 
 // Returns 0 or an amg_status code (err set): -1 unsupported input (smoothed
@@ -59,6 +59,8 @@ int build_hierarchy_on_device(const CsrView &K0, const double *w, const SetupPar
 //
 // Device copy of a host CSR.
 int csr_to_device(const CsrView &K, void *stream, DevCsr &D, std::string &err);
+// Whether validate_csr would accept the entries (its row pointers are valid).
+int check_csr(const DevCsr &K, void *stream, bool &valid, std::string &err);
 // K P (kp_product's bits) from the device copies of K, the aggregates and the
 // prolongator's coefficients; rp: its row pointers on the host, max_gap: the
 // widest column gap within a row.  K has fewer than 2^31 entries.

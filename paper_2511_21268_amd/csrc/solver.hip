@@ -1662,7 +1662,18 @@ static amg_status setup_common(int64_t n, const int64_t *row_ptr, const int32_t 
     }
     CsrView K0{n, row_ptr, col, val};
     std::string err;
-    if (amgiga::validate_csr(K0, err)) { set_err(err); return AMG_ERR_ARG; }
+    // A device set-up needs K on the device: its entries are checked there, and by
+    // the host where that finds a fault (for the message) or cannot be done.
+    amgiga::SetupMemory memory;
+    amgiga::DevCsr level0;
+    bool valid = false;
+    if (P.setup_device && amgiga::validate_rows(K0, err) == 0 && K0.nnz() < (int64_t(1) << 31)) {
+        std::string derr;
+        if (amgiga::csr_to_device(K0, hip_stream, level0, derr) ||
+            amgiga::check_csr(level0, hip_stream, valid, derr))
+            level0 = amgiga::DevCsr();
+    }
+    if (!valid && amgiga::validate_csr(K0, err)) { set_err(err); return AMG_ERR_ARG; }
     if (w)
         for (int64_t i = 0; i < n; i++)
             if (!std::isfinite(w[i])) { set_err("non-finite test vector"); return AMG_ERR_ARG; }
@@ -1672,7 +1683,10 @@ static amg_status setup_common(int64_t n, const int64_t *row_ptr, const int32_t 
         c->prm = P;
         c->host_only = host_only;
         c->stream = (hipStream_t)hip_stream;
-        amgiga::SetupMemory memory;
+        if (level0.rp) {
+            c->setup_info.levels.resize(1);
+            c->setup_info.levels[0] = std::move(level0);
+        }
         amgiga::SetupParams sp;
         sp.sweeps = P.sweeps_per_level;
         sp.max_coarse = P.max_coarse;

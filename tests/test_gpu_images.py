@@ -87,3 +87,33 @@ def test_device_setup_either_side_of_the_lanes_rule(amg, half):
             assert np.array_equal(a, b)
         for a, b in zip(dev.coarse_matrix(l + 1), host.coarse_matrix(l + 1)):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("row", [0, 31, 2999])
+@pytest.mark.parametrize("fault", ["range", "order", "nan", "diag", "values"])
+@pytest.mark.parametrize("half", [8, 60])
+def test_device_check_refuses_what_the_host_refuses(amg, half, fault, row):
+    """One fault in one row (16 or 64 lanes a row): the host's code and message."""
+    print(f"case check {half} {fault} {row}", flush=True)
+    n = 3000
+    k = np.arange(1, half + 1)
+    K = sp.diags([np.full(n, 200.0)] + [np.full(n - s, -1.0) for s in k] * 2, [0, *k, *-k], format="csr")
+    K.sort_indices()
+    rp, ci, v = K.indptr.astype(np.int64), K.indices.astype(np.int32), K.data.copy()
+    a, b = rp[row], rp[row + 1]
+    if fault == "range":
+        ci[b - 1] = n
+    elif fault == "order":
+        ci[a + 1] = ci[a]
+    elif fault == "nan":
+        v[a] = np.nan
+    elif fault == "diag":
+        v[a + int(np.searchsorted(ci[a:b], row))] = -1.0
+    else:
+        v[a + (1 if ci[a] == row else 0)] = -1.5
+    errors = []
+    for kw in ({"setup_device": 1}, {"host_only": True}):
+        with pytest.raises(amg.AmgError) as e:
+            amg.Context(rp, ci, v, **kw)
+        errors.append(str(e.value))
+    assert errors[0] == errors[1]
