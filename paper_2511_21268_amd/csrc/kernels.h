@@ -479,7 +479,8 @@ template <typename VT, typename FT, int EPI, int NDOT> struct RowOps {
         } else if (EPI == EPI_ADD) {
             return (OT)((VT)fr + acc);
         } else {
-            return (OT)(coef * (di * (VT)fr) + di * acc);
+            // the contraction is written out: every kernel has to take the same one
+            return (OT)fma(di, acc, coef * (di * (VT)fr));
         }
     }
 };

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void k_sell_blk(const Sell<VT, IT> A, const VT
             } else {
                 const VT di = invd[row];
 #pragma unroll
-                for (int j = 0; j < NB; j++) Y[o + j] = (OT)(coef * (di * (VT)F[o + j]) + di * acc[j]);
+                for (int j = 0; j < NB; j++) Y[o + j] = (OT)fma(di, acc[j], coef * (di * (VT)F[o + j]));
             }
         }
     }
@@ -326,7 +326,7 @@ __device__ __forceinline__ void win_epilogue(VT (&acc)[R][NB / R], int64_t row0,
                 if (NDOT >= 1) d0[i][jj] = (double)out * G0[o];
                 if (NDOT >= 2) d1[i][jj] = (double)out * G1[o];
             } else {
-                Y[o] = (OT)(coef * (di * (VT)F[o]) + di * a);
+                Y[o] = (OT)fma(di, a, coef * (di * (VT)F[o]));
             }
         }
     }
@@ -416,7 +416,7 @@ __device__ __forceinline__ void gather_slice(const Sell<VT, IT> &A, int64_t s, i
             } else {
                 const VT di = invd[row];
 #pragma unroll
-                for (int j = 0; j < NB; j++) Y[o + j] = (OT)(coef * (di * (VT)F[o + j]) + di * acc[j]);
+                for (int j = 0; j < NB; j++) Y[o + j] = (OT)fma(di, acc[j], coef * (di * (VT)F[o + j]));
             }
         }
     }
@@ -915,7 +915,7 @@ __global__ __launch_bounds__(512) void k_sellb(const Sell<VT, IT> A, const VT *_
             } else {
                 const VT di = invd[row];
 #pragma unroll
-                for (int j = 0; j < RPL; j++) Y[o + j] = (OT)(coef * (di * (VT)F[o + j]) + di * acc[j]);
+                for (int j = 0; j < RPL; j++) Y[o + j] = (OT)fma(di, acc[j], coef * (di * (VT)F[o + j]));
             }
         }
     }
@@ -1126,7 +1126,7 @@ __global__ __launch_bounds__(64 * SPLITB_WAVES) void k_splitb(const Sell<VT, IT>
         if (EPI == EPI_SPMV) Y[o + j] = (OT)acc[j];
         else if (EPI == EPI_RESID) Y[o + j] = (OT)((VT)F[o + j] - acc[j]);
         else if (EPI == EPI_SMOOTH) Y[o + j] = (OT)(X[o + j] + di * ((VT)F[o + j] - acc[j]));
-        else Y[o + j] = (OT)(coef * (di * (VT)F[o + j]) + di * acc[j]);
+        else Y[o + j] = (OT)fma(di, acc[j], coef * (di * (VT)F[o + j]));
     }
 }
 
