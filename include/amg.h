@@ -324,7 +324,9 @@ const char *amg_last_error(void);
  *   reads its entries there, instead of one gather per entry; runs whose 1 KB
  *   would leave x take the gathers.  amg_setup times both walks on the level-0
  *   residual and keeps the faster (the gathers gain more from a faster memory;
- *   the two differ by a few percent either way).  Bitwise the same results.
+ *   the two differ by a few percent either way).  Images of fewer than 1,200
+ *   slices take several wavefronts per slice and the gathers either way.
+ *   Bitwise the same results.
  * amg_get_option returns the current value of an option. */
 typedef enum {
     AMG_OPT_GRAPH = 1,
