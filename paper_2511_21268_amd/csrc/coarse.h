@@ -1,5 +1,5 @@
 // Coarsest-level dense Cholesky factorization on the device (FP64), run once
-// in amg_setup, and the inverse matrix that every coarse solve applies.
+// in amg_setup, and the inverse of the factor used by every coarse solve.
 //
 // Right-looking blocked algorithm with 16 x 16 tiles in one 256-thread block:
 // for each diagonal tile, an unblocked factorization in LDS, a triangular solve
@@ -86,34 +86,29 @@ __global__ __launch_bounds__(256) void k_chol_mfma(int npad, double *A, int *sta
     }
 }
 
-// Inverse of the lower factor by forward substitution, one column per thread
-// (row-major, lower; zeros above).
+// Inverse of the lower factor by forward substitution, one column per thread;
+// writes L^{-1} (row-major, lower, zeros above) and its transpose.
 __global__ __launch_bounds__(256) void k_tri_inv(int n, int npad, const double *__restrict__ L,
-                                                 double *__restrict__ Linv)
+                                                 double *__restrict__ Linv, double *__restrict__ LinvT)
 {
     for (int j = blockIdx.x * 256 + threadIdx.x; j < n; j += gridDim.x * 256) {
-        for (int i = 0; i < j; i++) Linv[(int64_t)i * npad + j] = 0.0;
-        Linv[(int64_t)j * npad + j] = 1.0 / L[(int64_t)j * npad + j];
+        for (int i = 0; i < j; i++) {
+            Linv[(int64_t)i * npad + j] = 0.0;
+            LinvT[(int64_t)j * npad + i] = 0.0;
+        }
+        const double xjj = 1.0 / L[(int64_t)j * npad + j];
+        Linv[(int64_t)j * npad + j] = xjj;
+        LinvT[(int64_t)j * npad + j] = xjj;
         for (int i = j + 1; i < n; i++) {
             const double *row = L + (int64_t)i * npad;
             double s = 0.0;
 #pragma unroll 8
             for (int k = j; k < i; k++) s = fma(row[k], Linv[(int64_t)k * npad + j], s);
-            Linv[(int64_t)i * npad + j] = -s / row[i];
+            const double xij = -s / row[i];
+            Linv[(int64_t)i * npad + j] = xij;
+            LinvT[(int64_t)j * npad + i] = xij;
         }
     }
-}
-
-// K^{-1} = L^{-T} L^{-1} (row-major, symmetric to the bit: entries (i, j) and
-// (j, i) sum the same products in the same order); one thread per entry.
-__global__ __launch_bounds__(256) void k_sym_inv(int n, int ld, const double *__restrict__ Linv,
-                                                 double *__restrict__ M)
-{
-    const int i = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= n) return;
-    double s = 0.0;
-    for (int k = i > j ? i : j; k < n; k++) s = fma(Linv[(int64_t)k * ld + i], Linv[(int64_t)k * ld + j], s);
-    M[(int64_t)i * ld + j] = s;
 }
 
 }  // namespace amgk

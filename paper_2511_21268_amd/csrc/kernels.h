@@ -671,67 +671,89 @@ __global__ void k_prolong(int64_t n, const int32_t *__restrict__ agg, const VT *
     u[i] = u[i] + prod;
 }
 
-// Coarsest level: e = K^{-1} f with the inverse matrix M (n x n, symmetric,
-// leading dimension ld), FP64 whatever the level type.  Row i is summed in
-// COARSE_SEGS segments of consecutive k, each an ascending chain, then
-// (s0 + s1) + (s2 + s3); the 16-column kernel and the V-cycle tail keep that
-// order.  One product instead of two triangular ones with L^{-1}: the same
-// bytes, half the dependent chain, and a quarter of it in each segment
-// (n = 154: 10.6 -> 4.8 us per call, most of it the launch).
+// Coarsest level: e = L^{-T} (L^{-1} f) with the precomputed inverse Cholesky
+// factor (row-major, leading dimension ld) and its transpose, FP64 whatever the
+// level type.  Two triangular products, not one with K^{-1}: the residual of
+// that grows with the condition of K (1e10, smooth f: 5e-7 |f|; of the two
+// products 3e-15 |f|).  A row is summed in COARSE_SEGS segments of coarse_len
+// consecutive k, each an ascending chain, then (s0 + s1) + (s2 + s3); the
+// 16-column kernels and the V-cycle tail keep that order.
 constexpr int COARSE_SEGS = 4, COARSE_MAXN = 2048;
-__device__ __forceinline__ double coarse_segment(int n, int ld, const double *__restrict__ M, const double *f, int i,
-                                                 int seg)
+__host__ __device__ inline int coarse_len(int n) { return (n + 8 * COARSE_SEGS - 1) / (8 * COARSE_SEGS) * 8; }
+// rows of the factors in memory, zeros from n on
+__host__ __device__ inline int coarse_rows(int n) { return COARSE_SEGS * coarse_len(n); }
+
+// One wave: rows r0 .. r0 + 15 (r0 a multiple of 16), a lane per row and segment,
+// LOWER: sum_{k<=i} M_ki f_k, else sum_{k>=i} M_ki f_k; the other half of M holds
+// zeros, so every lane takes the groups of 8 terms that one of them needs (lanes
+// without a term switched off instead: 5.4 us against 5.1 at n = 67, 821 against
+// 780 at n = 2,000).  f in LDS, zeros from n on.  Valid in all lanes of a row.
+template <bool LOWER>
+__device__ __forceinline__ double coarse_row16(int n, int ld, const double *__restrict__ M, const double *f, int r0)
 {
-    const int len = (n + COARSE_SEGS - 1) / COARSE_SEGS, k0 = seg * len, k1 = min(k0 + len, n);
+    constexpr int TG = 2;  // groups in flight
+    const int lane = threadIdx.x & 63, len = coarse_len(n), k0 = (lane >> 4) * len;
+    const int ga = LOWER ? 0 : max(0, r0 - (COARSE_SEGS - 1) * len) / 8, gb = LOWER ? min(len, r0 + 16) / 8 : len / 8;
     double s = 0.0;
-    int k = k0;
-    for (; k + 32 <= k1; k += 32) {
-        double m[32];
+    for (int g = ga; g < gb; g += TG) {
+        double m[8 * TG];
 #pragma unroll
-        for (int t = 0; t < 32; t++) m[t] = M[(int64_t)(k + t) * ld + i];
+        for (int h = 0; h < TG; h++)
+            if (g + h < gb)
 #pragma unroll
-        for (int t = 0; t < 32; t++) s = fma(m[t], f[k + t], s);
+                for (int t = 0; t < 8; t++)
+                    m[8 * h + t] = M[(unsigned)(k0 + 8 * (g + h) + t) * (unsigned)ld + (unsigned)(r0 + (lane & 15))];
+#pragma unroll
+        for (int h = 0; h < TG; h++)
+            if (g + h < gb)
+#pragma unroll
+                for (int t = 0; t < 8; t++) s = fma(m[8 * h + t], f[k0 + 8 * (g + h) + t], s);
     }
-    for (; k + 8 <= k1; k += 8) {
-        double m[8];
-#pragma unroll
-        for (int t = 0; t < 8; t++) m[t] = M[(int64_t)(k + t) * ld + i];
-#pragma unroll
-        for (int t = 0; t < 8; t++) s = fma(m[t], f[k + t], s);
-    }
-    for (; k < k1; k++) s = fma(M[(int64_t)k * ld + i], f[k], s);
-    return s;
+    s += __shfl_xor(s, 16, 64);
+    return s + __shfl_xor(s, 32, 64);
 }
-// the block's threads (a multiple of 256): thread = (row of a group, segment);
-// put(i, x) gets each result once.  f in LDS.
-template <int THREADS, typename Put>
-__device__ __forceinline__ void coarse_apply(int n, int ld, const double *__restrict__ M, const double *f,
-                                             double *segs /* THREADS */, Put put)
+// Both products by one block: fill(i) gives f_i, put(i, x) takes each result
+// once.  Bound by the latency of each product's loads (a wave has 16 in flight;
+// 24 gain nothing): n = 67 5.1 us, 281 8.8 us; K^{-1} f took 3.5 and 6.1 us.
+template <int THREADS, typename Fill, typename Put>
+__device__ __forceinline__ void coarse_apply(int n, int ld, const double *__restrict__ Linv,
+                                             const double *__restrict__ LinvT, Fill fill, Put put)
 {
-    constexpr int ROWS = THREADS / COARSE_SEGS;
-    const int row = threadIdx.x % ROWS, seg = threadIdx.x / ROWS;
-    for (int i0 = 0; i0 < n; i0 += ROWS) {
-        const int i = i0 + row;
-        __syncthreads();
-        segs[threadIdx.x] = i < n ? coarse_segment(n, ld, M, f, i, seg) : 0.0;
-        __syncthreads();
-        if (seg == 0 && i < n) put(i, (segs[row] + segs[ROWS + row]) + (segs[2 * ROWS + row] + segs[3 * ROWS + row]));
+    __shared__ double fs[COARSE_MAXN], ys[COARSE_MAXN];
+    const int first = 16 * wave_id(), step = THREADS / 4;
+    const int lane = threadIdx.x & 63;
+    for (int i = threadIdx.x; i < coarse_rows(n); i += THREADS) {
+        fs[i] = i < n ? fill(i) : 0.0;
+        if (i >= n) ys[i] = 0.0;
+    }
+    __syncthreads();
+    for (int r0 = first; r0 < n; r0 += step) {
+        const double y = coarse_row16<true>(n, ld, LinvT, fs, r0);
+        if (lane < 16 && r0 + lane < n) ys[r0 + lane] = y;
+    }
+    __syncthreads();
+    for (int r0 = first; r0 < n; r0 += step) {
+        const double x = coarse_row16<false>(n, ld, Linv, ys, r0);
+        if (lane < 16 && r0 + lane < n) put(r0 + lane, x);
     }
 }
 
-// One block.  With members: f is the residual of the level above, restricted
-// here (its launch saved); else the right-hand side itself.
+// Column blockIdx.x of 1 or NB (row-major) columns.  With members: f is the
+// residual of the level above, restricted here (its launch saved); else the
+// right-hand side itself.
 constexpr int COARSE_THREADS = 1024;
 template <typename VT>
-__global__ __launch_bounds__(COARSE_THREADS) void k_coarse_solve(int n, int ld, const double *__restrict__ M, int mw,
+__global__ __launch_bounds__(COARSE_THREADS) void k_coarse_solve(int n, int ld, const double *__restrict__ Linv,
+                                                                 const double *__restrict__ LinvT, int mw,
                                                                  const int32_t *__restrict__ members,
                                                                  const VT *__restrict__ pc, const VT *__restrict__ f,
                                                                  VT *__restrict__ e)
 {
-    __shared__ double fs[COARSE_MAXN], segs[COARSE_THREADS];
-    for (int i = threadIdx.x; i < n; i += COARSE_THREADS)
-        fs[i] = members ? (double)restrict_sum(mw, members, pc, f, i) : (double)f[i];
-    coarse_apply<COARSE_THREADS>(n, ld, M, fs, segs, [&](int i, double x) { e[i] = (VT)x; });
+    const int cols = gridDim.x, j = blockIdx.x;
+    coarse_apply<COARSE_THREADS>(
+        n, ld, Linv, LinvT,
+        [&](int i) { return members ? (double)restrict_sum(mw, members, pc, f, i) : (double)f[(int64_t)i * cols + j]; },
+        [&](int i, double x) { e[(int64_t)i * cols + j] = (VT)x; });
 }
 
 // Dot-product partials: one per block of a fixed grid (grid-stride).

@@ -84,20 +84,23 @@ __global__ void k_add_blk(int64_t n, const VT *__restrict__ x, const VT *__restr
     y[i] = (OT)(x[i] + c[i]);
 }
 
-// Coarsest level for 16 columns: E = K^{-1} F with the inverse matrix M, one
-// element (row i, column j) per thread in k_coarse_solve's segments and order,
-// so each column equals its result.  The rows of F and the block's columns of
-// M come through LDS, 64 of each segment at a time: one thread per element
-// reading them from memory waited a latency every few terms (n = 117: 36 us; two
-// triangular products 23 us; this 5 us, most of it the launch).
+// Coarsest level for 16 columns, one of the two products of k_coarse_solve per
+// launch: LOWER Y = L^{-1} F (M: the transposed inverse factor), else E = L^{-T} Y
+// (M: the inverse factor; Y: global scratch, n x 16).  One element (row i, column
+// j) per thread in k_coarse_solve's segments and order, so each column equals its
+// result.  The rows of F and the block's columns of M come through LDS, 64 of
+// each segment at a time: one thread per element reading them from memory
+// waited a latency every few terms.
 constexpr int CBLK_ROWS = 256 / NB, CBLK_K = 64;
-template <typename VT>
-__global__ __launch_bounds__(256) void k_coarse_solve_blk(int n, int ld, const double *__restrict__ M,
-                                                          const VT *__restrict__ f, VT *__restrict__ e)
+template <bool LOWER, typename FT, typename ET>
+__global__ __launch_bounds__(256) void k_coarse_product_blk(int n, int ld, const double *__restrict__ M,
+                                                            const FT *__restrict__ f, ET *__restrict__ e)
 {
     __shared__ double fs[COARSE_SEGS * CBLK_K][NB], ms[COARSE_SEGS * CBLK_K][CBLK_ROWS + 1];
     const int j = threadIdx.x & (NB - 1), r = threadIdx.x / NB, i0 = blockIdx.x * CBLK_ROWS;
-    const int len = (n + COARSE_SEGS - 1) / COARSE_SEGS;
+    const int len = coarse_len(n);
+    // the terms of the block's rows; M is zero in the rest of its square
+    const int ka = LOWER ? 0 : i0, kb = LOWER ? min(i0 + CBLK_ROWS, n) : n;
     double s[COARSE_SEGS];
 #pragma unroll
     for (int q = 0; q < COARSE_SEGS; q++) s[q] = 0.0;
@@ -107,7 +110,7 @@ __global__ __launch_bounds__(256) void k_coarse_solve_blk(int n, int ld, const d
 #pragma unroll
         for (int g = 0; g < COARSE_SEGS * CBLK_K / CBLK_ROWS; g++) {
             const int h = g * CBLK_ROWS + r, q = h / CBLK_K, t = c + h % CBLK_K, k = q * len + t;
-            const bool live = t < len && k < n;
+            const bool live = t < len && k >= ka && k < kb;
             fs[h][j] = live ? (double)f[(int64_t)k * NB + j] : 0.0;
             ms[h][j] = live && i0 + j < n ? M[(int64_t)k * ld + i0 + j] : 0.0;
         }
@@ -115,25 +118,27 @@ __global__ __launch_bounds__(256) void k_coarse_solve_blk(int n, int ld, const d
         const int steps = min(CBLK_K, len - c);
         for (int t = 0; t < steps; t++)
 #pragma unroll
-            for (int q = 0; q < COARSE_SEGS; q++)
-                if (q * len + c + t < n) s[q] = fma(ms[q * CBLK_K + t][r], fs[q * CBLK_K + t][j], s[q]);
+            for (int q = 0; q < COARSE_SEGS; q++) {
+                const int k = q * len + c + t;
+                if (k >= ka && k < kb) s[q] = fma(ms[q * CBLK_K + t][r], fs[q * CBLK_K + t][j], s[q]);
+            }
     }
-    if (i0 + r < n) e[(int64_t)(i0 + r) * NB + j] = (VT)((s[0] + s[1]) + (s[2] + s[3]));
+    if (i0 + r < n) e[(int64_t)(i0 + r) * NB + j] = (ET)((s[0] + s[1]) + (s[2] + s[3]));
 }
 
 // the same sum for one element in one thread (V-cycle tail of 16 columns)
-template <typename VT>
-__device__ __forceinline__ double coarse_row_blk(int n, int ld, const double *__restrict__ M, const VT *__restrict__ f,
+template <bool LOWER, typename FT>
+__device__ __forceinline__ double coarse_row_blk(int n, int ld, const double *__restrict__ M, const FT *__restrict__ f,
                                                  int i, int j)
 {
-    const int len = (n + COARSE_SEGS - 1) / COARSE_SEGS;
+    const int len = coarse_len(n);
     double s[COARSE_SEGS];
 #pragma unroll
     for (int q = 0; q < COARSE_SEGS; q++) {
         s[q] = 0.0;
-        const int k1 = min((q + 1) * len, n);
+        const int k0 = LOWER ? q * len : max(q * len, i), k1 = min((q + 1) * len, LOWER ? i + 1 : n);
 #pragma unroll 8
-        for (int k = q * len; k < k1; k++) s[q] = fma(M[(int64_t)k * ld + i], (double)f[(int64_t)k * NB + j], s[q]);
+        for (int k = k0; k < k1; k++) s[q] = fma(M[(int64_t)k * ld + i], (double)f[(int64_t)k * NB + j], s[q]);
     }
     return (s[0] + s[1]) + (s[2] + s[3]);
 }

@@ -132,7 +132,7 @@ struct amg_ctx {
     std::vector<Level> lev;
     int nlev = 0;
     int nL = 0, ldL = 0;
-    double *Minv = nullptr;   // inverse of the coarsest matrix, nL x nL, leading dimension ldL
+    double *Linv = nullptr, *LinvT = nullptr;   // inverse of the coarsest factor and its transpose (leading dimension ldL)
     // coarsest level for the CG coarse solver: CSR (int32) and 1 / k_ii
     int32_t *cg_rp = nullptr, *cg_ci = nullptr;
     double *cg_v = nullptr, *cg_dj = nullptr;
@@ -142,7 +142,7 @@ struct amg_ctx {
     int64_t partial_cap = 0;
     // batched solve (allocated on first use)
     double *bR = nullptr, *bZ = nullptr, *bP = nullptr, *bQ = nullptr, *bU = nullptr, *bF = nullptr;
-    double *bsc = nullptr, *hbsc = nullptr, *hbsc_dev = nullptr, *bpartial = nullptr, *bstrided = nullptr;
+    double *bY = nullptr, *bsc = nullptr, *hbsc = nullptr, *hbsc_dev = nullptr, *bpartial = nullptr, *bstrided = nullptr;
     double *bgram = nullptr, *bcoef = nullptr, *bgsave = nullptr;   // block CG: Gram partials, alpha / beta, G
     int blk_lpr = 1, blk_threads = 256;   // block-kernel variant (autotuned when prm.nrhs > 1)
     int blk_win = 4;       // stencil images: staged-window block kernel with this many rows per lane (0: off)
@@ -714,11 +714,11 @@ struct amg_ctx {
         Level &C = lev[nlev - 1];
         if (blk) {
             hipLaunchKernelGGL((k_vtail_blk<VT>), dim3(1), dim3(TAIL_THREADS), 0, stream,
-                               (const TailLevel<VT> *)tail_dev_blk, nt, nL, ldL, Minv, (VT *)C.bf,
-                               (VT *)C.bu);
+                               (const TailLevel<VT> *)tail_dev_blk, nt, nL, ldL, Linv, LinvT, (VT *)C.bf,
+                               (VT *)C.bu, bY);
         } else {
             hipLaunchKernelGGL((k_vtail<VT>), dim3(1), dim3(TAIL_THREADS), 0, stream, (const TailLevel<VT> *)tail_dev,
-                               nt, nL, ldL, Minv, (VT *)C.f, (VT *)C.u);
+                               nt, nL, ldL, Linv, LinvT, (VT *)C.f, (VT *)C.u);
         }
         HIPCHK(hipGetLastError());
         return (VT *)(blk ? lev[tail_start].bu2 : lev[tail_start].u2);
@@ -728,7 +728,7 @@ struct amg_ctx {
     // the solve; with P null f is the right-hand side itself
     template <typename VT> void coarse_solve(const Level *P, const VT *f, VT *e)
     {
-        hipLaunchKernelGGL((k_coarse_solve<VT>), dim3(1), dim3(COARSE_THREADS), 0, stream, nL, ldL, Minv,
+        hipLaunchKernelGGL((k_coarse_solve<VT>), dim3(1), dim3(COARSE_THREADS), 0, stream, nL, ldL, Linv, LinvT,
                            P ? P->mw : 0, P ? P->members : nullptr, P ? P->pc<VT>() : nullptr, f, e);
         HIPCHK(hipGetLastError());
     }
@@ -1210,6 +1210,7 @@ struct amg_ctx {
         size_t nb = (size_t)n * NB;
         bR = alloc<double>(nb); bZ = alloc<double>(nb); bP = alloc<double>(nb);
         bQ = alloc<double>(nb); bU = alloc<double>(nb); bF = alloc<double>(nb);
+        bY = alloc<double>((size_t)std::max(nL, 1) * NB);
         bsc = alloc<double>(B_NSLOTS * NB);
         bpartial = alloc<double>((size_t)partial_cap * NB);
         bstrided = alloc<double>((size_t)2 * NB * FIN_THREADS);
@@ -1275,10 +1276,24 @@ struct amg_ctx {
         HIPCHK(hipGetLastError());
         bfinalize(g, BF_RR, 0.0, hbsc_dev);
     }
+    // Coarsest solve of the 16 columns: one launch with a block per column, each
+    // reading the whole factor, or, from this many rows on, the tiled products
+    // (two launches), which read it once.  CG iteration on a single-level system,
+    // us, per column / tiled: 117 rows 10.5 / 13.8, 400 rows 17.7 / 22.5, 512 rows
+    // 21.8 / 24.9, 700 rows 32.6 / 30.9, 2,000 rows 194 / 82.
+    static constexpr int COARSE_BLK_ROWS = 640;
     template <typename VT> void coarse_blk(const VT *f, VT *e)
     {
-        const unsigned g = (unsigned)((nL + CBLK_ROWS - 1) / CBLK_ROWS);
-        hipLaunchKernelGGL((k_coarse_solve_blk<VT>), dim3(g), dim3(256), 0, stream, nL, ldL, Minv, f, e);
+        if (nL < COARSE_BLK_ROWS) {
+            hipLaunchKernelGGL((k_coarse_solve<VT>), dim3(NB), dim3(COARSE_THREADS), 0, stream, nL, ldL, Linv, LinvT, 0,
+                               (const int32_t *)nullptr, (const VT *)nullptr, f, e);
+        } else {
+            const unsigned g = (unsigned)((nL + CBLK_ROWS - 1) / CBLK_ROWS);
+            hipLaunchKernelGGL((k_coarse_product_blk<true, VT, double>), dim3(g), dim3(256), 0, stream, nL, ldL, LinvT,
+                               f, bY);
+            hipLaunchKernelGGL((k_coarse_product_blk<false, double, VT>), dim3(g), dim3(256), 0, stream, nL, ldL, Linv,
+                               bY, e);
+        }
         HIPCHK(hipGetLastError());
     }
     unsigned bdot_partials(int64_t m, const double *a, const double *b, const double *c)
@@ -1564,12 +1579,13 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
         }
         c->nL = nl;
         c->ldL = npad;
-        c->Minv = c->alloc<double>((size_t)npad * npad);
-        double *Linv = c->alloc<double>((size_t)npad * npad);
-        hipLaunchKernelGGL(k_tri_inv, dim3((nl + 255) / 256), dim3(256), 0, c->stream, nl, npad, dA, Linv);
-        hipLaunchKernelGGL(k_sym_inv, dim3((nl + 255) / 256, nl), dim3(256), 0, c->stream, nl, npad, Linv, c->Minv);
+        const size_t entries = (size_t)coarse_rows(nl) * npad;
+        c->Linv = c->alloc<double>(entries);
+        c->LinvT = c->alloc<double>(entries);
+        for (double *M : {c->Linv, c->LinvT}) HIPCHK(hipMemsetAsync(M, 0, entries * sizeof(double), c->stream));
+        hipLaunchKernelGGL(k_tri_inv, dim3((nl + 255) / 256), dim3(256), 0, c->stream, nl, npad, dA, c->Linv,
+                           c->LinvT);
         HIPCHK(hipStreamSynchronize(c->stream));
-        c->release(Linv);
         c->release(dA);
         HIPCHK(hipGetLastError());
     }

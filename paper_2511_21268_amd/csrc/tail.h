@@ -73,9 +73,9 @@ __device__ inline void tail_post(const Sell<VT, IT> &A, const VT *e, const VT *u
 // solution of the coarsest level.  Output: T[0].u2.
 template <typename VT>
 __global__ __launch_bounds__(TAIL_THREADS) void k_vtail(const TailLevel<VT> *__restrict__ T, int nt, int nL, int ld,
-                                                        const double *__restrict__ M, VT *fL, VT *eL)
+                                                        const double *__restrict__ Linv,
+                                                        const double *__restrict__ LinvT, VT *fL, VT *eL)
 {
-    __shared__ double fs[COARSE_MAXN], segs[TAIL_THREADS];
     for (int t = 0; t < nt; t++) {
         const TailLevel<VT> &L = T[t];
         if (L.a16) tail_resid(L.A16, L.f, L.u, L.r);
@@ -93,8 +93,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_vtail(const TailLevel<VT> *__r
         __syncthreads();
     }
     // coarsest level, k_coarse_solve's order
-    for (int i = threadIdx.x; i < nL; i += TAIL_THREADS) fs[i] = (double)fL[i];
-    coarse_apply<TAIL_THREADS>(nL, ld, M, fs, segs, [&](int i, double x) { eL[i] = (VT)x; });
+    coarse_apply<TAIL_THREADS>(
+        nL, ld, Linv, LinvT, [&](int i) { return (double)fL[i]; }, [&](int i, double x) { eL[i] = (VT)x; });
     __syncthreads();
     for (int t = nt - 1; t >= 0; t--) {
         const TailLevel<VT> &L = T[t];
@@ -159,10 +159,12 @@ __device__ inline void tail_post_blk(const Sell<VT, IT> &A, const VT *E, const V
     }
 }
 
-// As k_vtail for 16 columns.
+// As k_vtail for 16 columns; Yc: global scratch of the coarse solve (nL x 16).
 template <typename VT>
 __global__ __launch_bounds__(TAIL_THREADS) void k_vtail_blk(const TailLevel<VT> *__restrict__ T, int nt, int nL,
-                                                            int ld, const double *__restrict__ M, VT *FL, VT *EL)
+                                                            int ld, const double *__restrict__ Linv,
+                                                            const double *__restrict__ LinvT, VT *FL, VT *EL,
+                                                            double *Yc)
 {
     for (int t = 0; t < nt; t++) {
         const TailLevel<VT> &L = T[t];
@@ -197,9 +199,12 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_vtail_blk(const TailLevel<VT> 
         }
         __syncthreads();
     }
-    // coarsest level, k_coarse_solve_blk's order
+    // coarsest level, k_coarse_product_blk's order: Y = L^{-1} F, then E = L^{-T} Y
     for (int q = threadIdx.x; q < nL * NB; q += TAIL_THREADS)
-        EL[q] = (VT)coarse_row_blk(nL, ld, M, FL, q / NB, q % NB);
+        Yc[q] = coarse_row_blk<true>(nL, ld, LinvT, FL, q / NB, q % NB);
+    __syncthreads();
+    for (int q = threadIdx.x; q < nL * NB; q += TAIL_THREADS)
+        EL[q] = (VT)coarse_row_blk<false>(nL, ld, Linv, Yc, q / NB, q % NB);
     __syncthreads();
     for (int t = nt - 1; t >= 0; t--) {
         const TailLevel<VT> &L = T[t];

@@ -1,4 +1,4 @@
-"""GPU: the coarsest-level solve (product with the inverse matrix in four
+"""GPU: the coarsest-level solve (products with the inverse factor in four
 segments per row) at the edges of its segments, row groups and tiles, on
 single-level systems, whose V-cycle is that solve; the restriction inside the kernel
 and the 16-column kernel on a two-level system, bit for bit."""
@@ -71,3 +71,29 @@ def test_two_level_restriction(amg, n, fp32):
         assert one["status"] == 0 and one["iters"] == out["iters"][j]
         if not fp32:
             assert torch.equal(one["u"], out["U"][:, j].contiguous())
+
+
+@pytest.mark.parametrize("n", [65, 150, 1000])
+def test_residual_of_an_ill_conditioned_coarsest_matrix(amg, n):
+    """Condition 1e12, smooth solutions: the residual of the solve is that of
+    products with the triangular inverses (n u sqrt(cond)), not of one with the
+    inverse matrix (u cond: 7e-5 |f| at n = 150)."""
+    print(f"case coarse residual n={n}", flush=True)
+    one = np.ones(n - 1)
+    d = np.full(n, 2.0)
+    d[0] = d[-1] = 1.0
+    K = sp.diags([d + 4e-12, -one, -one], [0, 1, -1]).tocsr()
+    ctx = _context(amg, K, max_coarse=2000)
+    assert ctx.nlevels == 1
+    F = K @ np.random.default_rng(n).standard_normal((n, 3))
+    # both products' and the factor's errors: 4 n u sqrt(cond) (|f| + |K| |z|)
+    tol = 4 * n * 2.0 ** -53 * 1e6
+    Ft = torch.from_numpy(np.ascontiguousarray(F.T)).cuda()
+    for j in range(3):
+        z = ctx.vcycle(Ft[j]).cpu().numpy()
+        res, scale = np.linalg.norm(K @ z - F[:, j]), np.linalg.norm(F[:, j]) + 4 * np.linalg.norm(z)
+        print(f"  residual {res / scale:.1e}, bound {tol:.1e}", flush=True)
+        assert res <= tol * scale
+    if n <= 150:    # the bound times |F|'s share of the scale is below 1e-6
+        assert list(ctx.solve_batched(Ft.t(), tol=1e-6)["iters"]) == [1, 1, 1]
+        assert ctx.solve(Ft[0], tol=1e-6)["iters"] == 1
