@@ -305,11 +305,13 @@ __device__ __forceinline__ void mlp_chain_loss(const float *__restrict__ Y, cons
             if (v < wid) before += sums[v];
             run += sums[v];
         }
-        const float l0 = (float)(before + (upto - s));
+        const double below = __shfl_up(upto, 1, 64);
+        const float l0 = (float)(lane ? before + below : before);
         float l = l0;
 #pragma unroll
         for (int k = 0; k < MLP_SEG; k++) l = fmaf(e[k], e[k], l);
-        grown += (double)l - (double)l0;
+        // past an overflow the chain stays at infinity (or NaN)
+        grown += isinf(l0) ? (double)l : (double)l - (double)l0;
     }
     grown = wave_sum(grown);
     __syncthreads();

@@ -70,3 +70,36 @@ def test_mlp_batches(B):
     assert np.all(abs(Y[:B * 4].cpu().numpy().reshape(B, 4) - Yr) <= 387 * u * (top + 64))
     assert np.all(abs(g[:amg.MLP_NPARAM].cpu().numpy() - gr) <= 387 * u * (ga + ga.max()))
     assert abs(float(loss[0]) - lr) <= 387 * u * float((top ** 2).mean())
+
+
+def _loss(tr, X, T):
+    """Loss, gradient and outputs of one forward and backward pass."""
+    from paper_2511_21268_amd import amg
+    Xd, Td = torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda()
+    act = torch.empty(len(X), amg.MLP_NACT, device="cuda")
+    Y = tr.forward(Xd, act)
+    return tr.backward(Xd, act, Y, Td), tr.grad.cpu().numpy(), Y.cpu().numpy()
+
+
+@pytest.mark.parametrize("B", [1, 58, 76, 1000, 16384, 20001])
+@pytest.mark.parametrize("fault,expect", [("inf", np.inf), ("square", np.inf), ("sum", np.inf), ("nan", np.nan),
+                                          ("inf nan", np.nan)])
+def test_loss_of_a_diverged_training(B, fault, expect):
+    """Targets that are infinite, whose squares or whose sum of squares
+    overflow, or NaN, at the batch's start, middle or end: the loss is that of
+    the ascending FP32 sum."""
+    print(f"case mlp loss {fault} B={B}", flush=True)
+    from paper_2511_21268_amd.learned import Trainer
+    tr = Trainer(seed=1)
+    r = np.random.default_rng(B)
+    X = r.standard_normal((B, 8)).astype(np.float32)
+    for at in {0, B // 2, B - 1}:
+        T = r.standard_normal((B, 4)).astype(np.float32)
+        if fault == "sum":
+            T[:] = 1.2e19 if B == 1 else 3.7e38 ** 0.5 / B ** 0.5      # squares add up past 3.4e38
+        else:
+            T[at] = {"inf": np.inf, "square": 1e25, "nan": np.nan, "inf nan": np.inf}[fault]
+        if fault == "inf nan":
+            T[B - 1 - at, 3] = np.nan
+        loss = _loss(tr, X, T)[0]
+        assert np.array_equal(loss, expect, equal_nan=True), (at, loss)
