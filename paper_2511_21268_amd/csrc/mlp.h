@@ -142,6 +142,7 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_fwd(const uint16_t *__restr
 constexpr int MLP_ROWS = 64;              // samples per tile
 constexpr int MLP_PART = MLP_NPARAM + 4;  // floats of one block's sums
 constexpr int MLP_MAX_BLOCKS = 512;
+constexpr int MLP_ONE_BLOCK = 2;          // most tiles of a batch that one block takes
 
 // samples per block, and blocks: as many as the caller's workspace (MLP_DEL
 // floats per sample) holds partial sums of, at most one per tile
@@ -154,6 +155,7 @@ struct MlpSplit {
         n = n < 1 ? 1 : n > MLP_MAX_BLOCKS ? MLP_MAX_BLOCKS : n;
         n = n > tiles ? tiles : n;
         const int64_t per = (tiles + n - 1) / n;   // tiles per block
+        static_assert(MLP_ONE_BLOCK * MLP_ROWS * MLP_DEL >= 2 * MLP_PART, "two blocks past MLP_ONE_BLOCK tiles");
         chunk = (int)(per * MLP_ROWS);
         blocks = (int)((tiles + per - 1) / per);
     }
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_back(const uint16_t *__rest
 {
     __shared__ __align__(16) float h1s[MLP_ROWS * MLP_LD], h2s[MLP_ROWS * MLP_LD];
     __shared__ __align__(16) float d1s[MLP_ROWS * MLP_LD], d2s[MLP_ROWS * MLP_LD];
-    __shared__ float xs[MLP_ROWS][MLP_IN], dys[MLP_ROWS][MLP_OUT], ls[MLP_THREADS];
+    __shared__ float xs[MLP_ROWS][MLP_IN], dys[MLP_ROWS][MLP_OUT], es[MLP_ONE_BLOCK * MLP_THREADS];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int64_t c0 = (int64_t)blockIdx.x * chunk, c1 = c0 + chunk < B ? c0 + chunk : B;
     const float scale = 2.0f / (float)((int64_t)MLP_OUT * B);
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_back(const uint16_t *__rest
     // this lane's sums: W2 quadrant (wid / 2, wid % 2); W1[lane][2 wid], [2 wid
     // + 1]; W3[wid][lane]; one bias: b1 (wave 0), b2 (wave 1), b3 (wave 2)
     vf16 g2 = {};
-    float g1a = 0.0f, g1b = 0.0f, g3 = 0.0f, gb = 0.0f, l = 0.0f;
+    float g1a = 0.0f, g1b = 0.0f, g3 = 0.0f, gb = 0.0f;
     for (int64_t t0 = c0; t0 < c1; t0 += MLP_ROWS) {
         __syncthreads();   // the tile before is summed
         // the tile's inputs, zeros past the chunk: one dy per thread, x, and the
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_back(const uint16_t *__rest
             const int64_t s = t0 + tid / MLP_OUT, at = t0 * MLP_OUT + tid;
             const float e = s < c1 ? Y[at] - T[at] : 0.0f;
             dys[tid / MLP_OUT][tid % MLP_OUT] = scale * e;
-            l = fmaf(e, e, l);
+            if (gridDim.x == 1) es[at] = e;   // all of the batch, for the loss
         }
 #pragma unroll
         for (int at = tid; at < MLP_ROWS * MLP_IN; at += MLP_THREADS)
@@ -256,19 +258,19 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_back(const uint16_t *__rest
     if (wid == 0) out[MLP_B1 + lane] = gb;
     else if (wid == 1) out[MLP_B2 + lane] = gb;
     else if (wid == 2 && lane < MLP_OUT) out[MLP_B3 + lane] = gb;
-    ls[tid] = l;
-    __syncthreads();
     if (tid == 0 && gridDim.x == 1 && loss) {
-        float t = 0.0f;
-        for (int v = 0; v < MLP_THREADS; v++) t += ls[v];
-        *loss = t / (float)((int64_t)MLP_OUT * B);
+        float l = 0.0f;
+#pragma unroll 8
+        for (int v = 0; v < MLP_OUT * B; v++) l = fmaf(es[v], es[v], l);
+        *loss = l / (float)(MLP_OUT * B);
     }
 }
 
-// The loss as the ascending FP32 chain l = fma(e, e, l) over all outputs gives
-// it (for a large batch that chain is some 1e-5 below the sum of its terms, the
-// terms having shrunk to a few units of the sum's last place; callers compare
-// losses of runs, so the value stays): every thread runs 32 links of the chain,
+// The loss is the ascending FP32 chain l = fma(e, e, l) over all outputs, for
+// every batch size (for a large batch that chain is some 1e-5 below the sum of
+// its terms, the terms having shrunk to a few units of the sum's last place;
+// callers compare losses of runs, so the value stays).  A single block walks it
+// itself; here every thread runs 32 links of the chain,
 // started from the FP64 sum of the terms before them, and the links' growth is
 // added in FP64.  What a link rounds away depends on the running sum's binade,
 // not on its low bits, so the segments together equal the chain to 1e-7.

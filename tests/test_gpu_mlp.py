@@ -103,3 +103,22 @@ def test_loss_of_a_diverged_training(B, fault, expect):
             T[B - 1 - at, 3] = np.nan
         loss = _loss(tr, X, T)[0]
         assert np.array_equal(loss, expect, equal_nan=True), (at, loss)
+
+
+@pytest.mark.parametrize("B", [1, 7, 16, 58, 64, 65, 75, 76, 129, 1000, 16384, 40000])
+def test_loss_is_the_ascending_chain(B):
+    """One definition for every batch size: l = fma(e, e, l) in FP32 over the
+    outputs in order, divided by their number.  One block walks the chain
+    itself; several form it from segments, which differ from it where a segment
+    starts next to a binade's end and in the final roundings (16 units of 2^-24)."""
+    print(f"case mlp loss chain B={B}", flush=True)
+    from paper_2511_21268_amd.learned import Trainer
+    r = np.random.default_rng(B)
+    X, T = (r.standard_normal((B, k)).astype(np.float32) for k in (8, 4))
+    loss, _, Y = _loss(Trainer(seed=2), X, T)
+    l = np.float32(0.0)
+    for e in (Y - T).ravel():
+        l = np.float32(np.float64(e) * np.float64(e) + np.float64(l))   # exact product, one FP64 sum
+    chain = float(l / np.float32(4 * B))
+    # equal but for the FP64 sum's own rounding before the FP32 one (a tie, rarely)
+    assert abs(loss - chain) <= (1 if B < 76 else 16) * 2.0 ** -24 * chain
