@@ -218,7 +218,8 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_back(const uint16_t *__rest
                 float d = 0.0f;
 #pragma unroll
                 for (int i = 0; i < MLP_OUT; i++) d = fmaf(w3[i], dys[r][i], d);
-                d2s[r * MLP_LD + lane] = d * (1.0f - h2[g + k] * h2[g + k]);
+                // rows past the chunk add nothing, whatever the weights (inf * 0)
+                d2s[r * MLP_LD + lane] = t0 + r < c1 ? d * (1.0f - h2[g + k] * h2[g + k]) : 0.0f;
                 h1s[r * MLP_LD + lane] = h1[g + k];
                 h2s[r * MLP_LD + lane] = h2[g + k];
                 a[k] = 0.0f;
@@ -227,7 +228,7 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_back(const uint16_t *__rest
             mlp_chain(a, w2, d2s + r0 * MLP_LD);
 #pragma unroll
             for (int k = 0; k < MLP_TILE; k++)
-                d1s[(r0 + k) * MLP_LD + lane] = a[k] * (1.0f - h1[g + k] * h1[g + k]);
+                d1s[(r0 + k) * MLP_LD + lane] = t0 + r0 + k < c1 ? a[k] * (1.0f - h1[g + k] * h1[g + k]) : 0.0f;
         }
         __syncthreads();
         // W2: A = dh2^T (32 units x 2 samples), B = h1 (2 samples x 32 units)

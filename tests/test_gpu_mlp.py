@@ -122,3 +122,26 @@ def test_loss_is_the_ascending_chain(B):
     chain = float(l / np.float32(4 * B))
     # equal but for the FP64 sum's own rounding before the FP32 one (a tie, rarely)
     assert abs(loss - chain) <= (1 if B < 76 else 16) * 2.0 ** -24 * chain
+
+
+@pytest.mark.parametrize("B", [58, 64, 100, 1000])
+def test_gradient_of_infinite_weights(B):
+    """An infinite output weight: where the sum over the samples is infinite it
+    stays so, also in batches that do not fill their last tile (a tile's rows
+    past the batch hold zeros, and inf * 0 is NaN)."""
+    print(f"case mlp infinite weight B={B}", flush=True)
+    from paper_2511_21268_amd.learned import Trainer
+    tr = Trainer(seed=3)
+    w = tr.w.view(torch.bfloat16)
+    b2, W3 = 64 * 8 + 64 + 64 * 64, 64 * 8 + 64 + 64 * 64 + 64
+    w[W3 + 7] = float("inf")
+    w[b2 + 7] = 0.75                                       # hidden unit 7 positive for every sample
+    w[64 * 8 + 64 + 7 * 64: 64 * 8 + 64 + 8 * 64] *= 0.01
+    r = np.random.default_rng(B)
+    X, T = (r.standard_normal((B, k)).astype(np.float32) for k in (8, 4))
+    _, g, _ = _loss(tr, X, T)
+    with np.errstate(all="ignore"):
+        gr = _reference(w.double().cpu().numpy(), X.astype(np.float64), T.astype(np.float64))[5]
+    at = b2 + 7                                            # sum of inf * (1 - h2^2) over the samples
+    assert gr[at] == np.inf and g[at] == np.inf, (gr[at], g[at])
+    assert g[W3 + 7] == np.inf == gr[W3 + 7]
