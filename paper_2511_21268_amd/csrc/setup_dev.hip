@@ -17,6 +17,7 @@
 //    ascending e.  Entry indices are sorted by position with a stable radix
 //    sort, and one thread per position sums its run in that order from +0.0.
 #include "setup_dev.h"
+#include "grid.h"
 
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
@@ -175,14 +176,13 @@ __device__ inline int64_t find_col(const int64_t *rp, const int32_t *ci, int64_t
 // (25 a row) 11.8 ms against 26.8 with 64, 2D p=3 (49) 8.5 against 14.5, 3D p=2
 // (114) 1.9 against 2.3 but keys 0.44 against 0.35.
 #define FOR_ROW(L)                                                                      \
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L;             \
     const int lane = threadIdx.x % L;                                                   \
-    if (i >= n) return;
+    for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L; i < n; i += (int64_t)gridDim.x * 256 / L)
 #define LAUNCH_ROWS(kernel, n, nnz, s, ...)                                                                      \
     do {                                                                                                         \
         if ((nnz) >= 100 * (n))                                                                                  \
-            hipLaunchKernelGGL((kernel<64>), dim3(grid((n) * 64)), dim3(256), 0, s, n, __VA_ARGS__);             \
-        else hipLaunchKernelGGL((kernel<16>), dim3(grid((n) * 16)), dim3(256), 0, s, n, __VA_ARGS__);            \
+            hipLaunchKernelGGL((kernel<64>), dim3(lanes_grid(n, 64)), dim3(256), 0, s, n, __VA_ARGS__);          \
+        else hipLaunchKernelGGL((kernel<16>), dim3(lanes_grid(n, 16)), dim3(256), 0, s, n, __VA_ARGS__);         \
         DCHK(hipGetLastError());                                                                                 \
     } while (0)
 
@@ -235,30 +235,30 @@ __global__ void k_edge_c(int64_t n, const int64_t *__restrict__ rp, const int32_
                          const double *__restrict__ v, const double *__restrict__ diag, const double *__restrict__ w,
                          int positive_only, double *__restrict__ cw, unsigned long long *cnt)
 {
-    FOR_ROW(L)
     unsigned long long missing = 0;
-    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
-        const int64_t j = ci[k];
-        double val = __builtin_nan("");
-        if (j != i) {
-            double kv;
-            if (i < j) {
-                kv = v[k];
-                if (find_col(rp, ci, j, (int32_t)i) < 0) missing++;
-            } else {
-                const int64_t t = find_col(rp, ci, j, (int32_t)i);
-                if (t < 0) missing++;
-                kv = t >= 0 ? v[t] : 0.0;
+    FOR_ROW(L)
+        for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
+            const int64_t j = ci[k];
+            double val = __builtin_nan("");
+            if (j != i) {
+                double kv;
+                if (i < j) {
+                    kv = v[k];
+                    if (find_col(rp, ci, j, (int32_t)i) < 0) missing++;
+                } else {
+                    const int64_t t = find_col(rp, ci, j, (int32_t)i);
+                    if (t < 0) missing++;
+                    kv = t >= 0 ? v[t] : 0.0;
+                }
+                if (kv != 0.0) {
+                    const int64_t a = i < j ? i : j, b = i < j ? j : i;
+                    const double c = cij_dev(kv, diag[a], diag[b], w[a], w[b]);
+                    const bool ok = isfinite(c) && (!positive_only || c > 1.0);
+                    if (ok) val = c;
+                }
             }
-            if (kv != 0.0) {
-                const int64_t a = i < j ? i : j, b = i < j ? j : i;
-                const double c = cij_dev(kv, diag[a], diag[b], w[a], w[b]);
-                const bool ok = isfinite(c) && (!positive_only || c > 1.0);
-                if (ok) val = c;
-            }
+            cw[k] = val;
         }
-        cw[k] = val;
-    }
     if (missing) atomicAdd(cnt, missing);
 }
 
@@ -279,28 +279,29 @@ __global__ void k_ld_point(int64_t n, const int64_t *__restrict__ rp, const int3
                            const double *__restrict__ cw, const int32_t *__restrict__ mate,
                            int32_t *__restrict__ ptr)
 {
-    FOR_ROW(L)
-    if (mate[i] >= 0) {
-        if (lane == 0) ptr[i] = -1;
-        return;
-    }
-    int best = -1;
-    double bc = 0.0;
-    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
-        const double c = cw[k];
-        if (c != c) continue;
-        const int v = ci[k];
-        if (mate[v] >= 0) continue;
-        if (best >= 0 && !edge_precedes(i, c, v, bc, best)) continue;
-        best = v; bc = c;
-    }
+    FOR_ROW(L) {
+        if (mate[i] >= 0) {
+            if (lane == 0) ptr[i] = -1;
+            continue;
+        }
+        int best = -1;
+        double bc = 0.0;
+        for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
+            const double c = cw[k];
+            if (c != c) continue;
+            const int v = ci[k];
+            if (mate[v] >= 0) continue;
+            if (best >= 0 && !edge_precedes(i, c, v, bc, best)) continue;
+            best = v; bc = c;
+        }
 #pragma unroll
-    for (int m = L / 2; m > 0; m /= 2) {
-        const int v = __shfl_xor(best, m, L);
-        const double c = __shfl_xor(bc, m, L);
-        if (v >= 0 && (best < 0 || edge_precedes(i, c, v, bc, best))) { best = v; bc = c; }
+        for (int m = L / 2; m > 0; m /= 2) {
+            const int v = __shfl_xor(best, m, L);
+            const double c = __shfl_xor(bc, m, L);
+            if (v >= 0 && (best < 0 || edge_precedes(i, c, v, bc, best))) { best = v; bc = c; }
+        }
+        if (lane == 0) ptr[i] = best;
     }
-    if (lane == 0) ptr[i] = best;
 }
 
 // any: set where a vertex had a candidate, by one store a block (stores of every
@@ -357,14 +358,15 @@ __global__ void k_gal_keys(int64_t n, const int64_t *__restrict__ rp, const int3
                            const double *__restrict__ v, const int32_t *__restrict__ agg, const double *__restrict__ pc,
                            uint64_t *__restrict__ keys, int32_t *__restrict__ vals, double *__restrict__ t, int cb)
 {
-    FOR_ROW(L)
-    const uint64_t I = (uint64_t)(uint32_t)agg[i];
-    const double pi = pc[i];
-    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
-        const int32_t j = ci[k];
-        keys[k] = (I << cb) | (uint64_t)(uint32_t)agg[j];
-        vals[k] = (int32_t)k;
-        t[k] = (pi * v[k]) * pc[j];
+    FOR_ROW(L) {
+        const uint64_t I = (uint64_t)(uint32_t)agg[i];
+        const double pi = pc[i];
+        for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
+            const int32_t j = ci[k];
+            keys[k] = (I << cb) | (uint64_t)(uint32_t)agg[j];
+            vals[k] = (int32_t)k;
+            t[k] = (pi * v[k]) * pc[j];
+        }
     }
 }
 
@@ -421,12 +423,12 @@ __global__ void k_kp_keys(int64_t n, const int64_t *__restrict__ rp, const int32
                           uint64_t *__restrict__ keys, int32_t *__restrict__ vals, double *__restrict__ t, int cb)
 {
     FOR_ROW(L)
-    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
-        const int32_t j = ci[k];
-        keys[k] = ((uint64_t)i << cb) | (uint64_t)(uint32_t)agg[j];
-        vals[k] = (int32_t)k;
-        t[k] = v[k] * pc[j];
-    }
+        for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
+            const int32_t j = ci[k];
+            keys[k] = ((uint64_t)i << cb) | (uint64_t)(uint32_t)agg[j];
+            vals[k] = (int32_t)k;
+            t[k] = v[k] * pc[j];
+        }
 }
 
 // Raises bad unless the entries are in range, ascending, finite and symmetric
@@ -436,24 +438,25 @@ template <int L>
 __global__ void k_check_csr(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                             const double *__restrict__ v, unsigned int *__restrict__ bad)
 {
-    FOR_ROW(L)
-    bool ok = true, diag = false;
-    for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
-        const int32_t j = ci[k];
-        const double x = v[k];
-        if (j < 0 || j >= n || (k > rp[i] && j <= ci[k - 1]) || !isfinite(x)) ok = false;
-        else if (j == i) {
-            diag = true;
-            ok = ok && x > 0.0;
-        } else {
-            const int64_t t = find_col(rp, ci, j, (int32_t)i);
-            ok = ok && t >= 0 && v[t] == x;
+    FOR_ROW(L) {
+        bool ok = true, diag = false;
+        for (int64_t k = rp[i] + lane; k < rp[i + 1]; k += L) {
+            const int32_t j = ci[k];
+            const double x = v[k];
+            if (j < 0 || j >= n || (k > rp[i] && j <= ci[k - 1]) || !isfinite(x)) ok = false;
+            else if (j == i) {
+                diag = true;
+                ok = ok && x > 0.0;
+            } else {
+                const int64_t t = find_col(rp, ci, j, (int32_t)i);
+                ok = ok && t >= 0 && v[t] == x;
+            }
         }
-    }
-    int d = diag;
+        int d = diag;
 #pragma unroll
-    for (int m = L / 2; m > 0; m /= 2) d |= __shfl_xor(d, m, L);
-    if (!ok || !d) __hip_atomic_store(bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int m = L / 2; m > 0; m /= 2) d |= __shfl_xor(d, m, L);
+        if (!ok || !d) __hip_atomic_store(bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // widest column gap within a row; a wavefront's rows are gridDim.x * 256 / L apart
@@ -909,9 +912,12 @@ int kp_on_device(const DevCsr &K, int64_t nc, const int32_t *agg, const double *
 int fill_sell(const DevCsr &K, int C, int64_t nslices, const SellFill &F, void *stream, std::string &err)
 {
     return guarded(err, [&] {
-        hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)nslices), dim3(256), 0, (hipStream_t)stream, K.n, (int64_t)0,
-                           (int64_t)0, K.rp, K.ci, K.v, C, (int64_t)0, F);
-        DCHK(hipGetLastError());
+        for (int64_t s0 = 0; s0 < nslices; s0 += MAX_BLOCKS) {
+            const unsigned g = (unsigned)std::min<int64_t>(nslices - s0, MAX_BLOCKS);
+            hipLaunchKernelGGL(k_fill_sell, dim3(g), dim3(256), 0, (hipStream_t)stream, K.n, (int64_t)0, (int64_t)0,
+                               K.rp, K.ci, K.v, C, s0, F);
+            DCHK(hipGetLastError());
+        }
     });
 }
 

@@ -117,3 +117,36 @@ def test_device_check_refuses_what_the_host_refuses(amg, half, fault, row):
             amg.Context(rp, ci, v, **kw)
         errors.append(str(e.value))
     assert errors[0] == errors[1]
+
+
+@pytest.mark.parametrize("d,p,n,nrhs", [(2, 1, 1100, 16), (3, 2, 65, 1)])
+def test_device_setup_past_one_grid(amg, d, p, n, nrhs):
+    """More rows than one pass of the grid holds (16 lanes: 2^20 rows, 64 lanes:
+    2^18), and more slices than one launch of the fill (65,536): the host
+    set-up's hierarchy bit for bit, and the block kernels' first iterate on the
+    lanes-per-row images against one lane per row."""
+    print(f"case device set-up past one grid d={d} p={p} n={n}", flush=True)
+    rp, ci, v, _ = amg.iga_poisson(d, p, n, want_F=False)
+    dev = amg.Context(rp, ci, v, setup_device=1, nrhs=nrhs, itmax=1)
+    host = amg.Context(rp, ci, v, host_only=True)
+    assert dev.nlevels == host.nlevels
+    for l in range(host.nlevels - 1):
+        for a, b in zip(dev.aggregates(l), host.aggregates(l)):
+            assert np.array_equal(a, b)
+        for a, b in zip(dev.coarse_matrix(l + 1), host.coarse_matrix(l + 1)):
+            assert np.array_equal(a, b)
+    K = sp.csr_matrix((v, ci, rp))
+    x = np.random.default_rng(1).standard_normal(len(rp) - 1)
+    y = dev.spmv(torch.from_numpy(x).cuda()).cpu().numpy()
+    w = int(np.diff(rp).max())
+    # ascending sums of w products on both sides
+    assert np.all(np.abs(y - K @ x) <= 2 * (w + 1) * 2.0 ** -53 * (abs(K) @ np.abs(x)))
+    if nrhs == 1:
+        return
+    F = torch.from_numpy(np.random.default_rng(n).standard_normal((16, len(rp) - 1))).cuda().t()
+    got = dev.solve_batched(F)["U"]
+    dev.set_batched_variant(1, 256)
+    ref = dev.solve_batched(F)["U"]
+    # two sums of N products each: 2 N u on sums of absolute terms at most about
+    # ten times their value
+    assert torch.linalg.norm(got - ref) <= 20 * len(rp) * 2.0 ** -53 * torch.linalg.norm(ref)
