@@ -367,8 +367,14 @@ inline void mlp_gradient(const uint16_t *w, const float *X, const float *act, co
 }
 inline void mlp_forward(const uint16_t *w, const float *X, int B, float *Y, float *act, hipStream_t st)
 {
+    // 16 threads a sample: a launch holds fewer than 2^28 samples
     constexpr int S = MLP_WAVES * MLP_TILE;
-    hipLaunchKernelGGL(k_mlp_fwd, dim3((unsigned)(((int64_t)B + S - 1) / S)), dim3(MLP_THREADS), 0, st, w, X, B, Y, act);
+    constexpr int64_t MOST = int64_t(1) << 27;
+    for (int64_t s0 = 0; s0 < B; s0 += MOST) {
+        const int n = (int)(B - s0 < MOST ? B - s0 : MOST);
+        hipLaunchKernelGGL(k_mlp_fwd, dim3((unsigned)((n + S - 1) / S)), dim3(MLP_THREADS), 0, st, w, X + s0 * MLP_IN, n,
+                           Y + s0 * MLP_OUT, act ? act + s0 * MLP_ACT : nullptr);
+    }
 }
 
 // Adam on the FP32 master weights, then the BF16 copy (round to nearest even).

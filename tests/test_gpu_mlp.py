@@ -145,3 +145,19 @@ def test_gradient_of_infinite_weights(B):
     at = b2 + 7                                            # sum of inf * (1 - h2^2) over the samples
     assert gr[at] == np.inf and g[at] == np.inf, (gr[at], g[at])
     assert g[W3 + 7] == np.inf == gr[W3 + 7]
+
+
+@pytest.mark.parametrize("B", [1 << 27, (1 << 27) + 5, 1 << 28])
+def test_forward_of_more_samples_than_one_launch_holds(B):
+    """The launch limit is 2^32 threads, 16 a sample (13 GB of inputs and
+    outputs at 2^28): the last samples' outputs are those of a small batch."""
+    print(f"case mlp forward B={B}", flush=True)
+    from paper_2511_21268_amd.learned import Trainer
+    tr = Trainer(seed=4)
+    tail = torch.randn(40, 8, generator=torch.Generator().manual_seed(1)).cuda()
+    X = torch.zeros(B, 8, device="cuda")
+    X[-40:] = tail
+    X[:40] = tail
+    Y, small = tr.forward(X), tr.forward(tail)
+    assert torch.equal(Y[-40:], small) and torch.equal(Y[:40], small)
+    assert bool((Y[40:-40] == Y[50]).all())
