@@ -47,6 +47,16 @@ struct InputError : std::runtime_error {
         if (e_ != hipSuccess) throw HipError(std::string("HIP error in set-up: ") + hipGetErrorString(e_)); \
     } while (0)
 
+// hipMalloc whose failure is in its result alone: the runtime also keeps it for
+// the next hipGetLastError, where a launch that succeeded (of this library, after
+// a way round the failure, or of its caller) would find it.
+hipError_t device_malloc(void **p, size_t bytes)
+{
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 // Device memory of one set-up call: a released block serves the next request
 // of the call that fits it (all work of the call is in one stream, so the next
 // use is ordered behind the last), the rest goes back when the call ends.
@@ -72,11 +82,10 @@ struct Pool {
             return used.back().p;
         }
         void *p = nullptr;
-        hipError_t e = hipMalloc(&p, bytes);
+        hipError_t e = device_malloc(&p, bytes);
         if (e == hipErrorOutOfMemory && !idle.empty()) {
-            (void)hipGetLastError();
             trim();
-            e = hipMalloc(&p, bytes);
+            e = device_malloc(&p, bytes);
         }
         DCHK(e);
         used.push_back({p, bytes});
@@ -106,7 +115,7 @@ void *dev_alloc(size_t bytes)
 {
     if (t_pool) return t_pool->take(bytes);
     void *p = nullptr;
-    DCHK(hipMalloc(&p, bytes));
+    DCHK(device_malloc(&p, bytes));
     return p;
 }
 void dev_free(void *p)

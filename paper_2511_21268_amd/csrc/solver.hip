@@ -79,7 +79,9 @@ template <typename T> T *dalloc(size_t n)
 {
     void *p = nullptr;
     if (n == 0) n = 1;
-    HIPCHK(hipMalloc(&p, n * sizeof(T)));
+    const hipError_t e = hipMalloc(&p, n * sizeof(T));
+    if (e != hipSuccess) (void)hipGetLastError();   // told by e: a later check is not to find it
+    HIPCHK(e);
     return (T *)p;
 }
 
