@@ -55,7 +55,7 @@ int build_hierarchy_on_device(const CsrView &K0, const double *w, const SetupPar
                               std::string &err, void *stream, DevSetupInfo *info);
 
 // The pieces of the image set-up that run on the device (stream: hipStream_t);
-// 0, or -3 / -4 with err set.
+// 0, or with err set -3, or -4 where device or host memory ran out.
 //
 // Device copy of a host CSR.
 int csr_to_device(const CsrView &K, void *stream, DevCsr &D, std::string &err);

@@ -37,14 +37,24 @@ namespace {
 struct HipError : std::runtime_error {
     using std::runtime_error::runtime_error;
 };
+struct OutOfMemory : HipError {
+    using HipError::HipError;
+};
 struct InputError : std::runtime_error {
     using std::runtime_error::runtime_error;
 };
 
+[[noreturn]] void fail(hipError_t e)
+{
+    const std::string m = std::string("HIP error in set-up: ") + hipGetErrorString(e);
+    if (e == hipErrorOutOfMemory) throw OutOfMemory(m);
+    throw HipError(m);
+}
+
 #define DCHK(x)                                                                                      \
     do {                                                                                             \
         hipError_t e_ = (x);                                                                         \
-        if (e_ != hipSuccess) throw HipError(std::string("HIP error in set-up: ") + hipGetErrorString(e_)); \
+        if (e_ != hipSuccess) fail(e_);                                                              \
     } while (0)
 
 // hipMalloc whose failure is in its result alone: the runtime also keeps it for
@@ -836,6 +846,9 @@ template <typename F> static int guarded(std::string &err, F f)
     try {
         f();
         return 0;
+    } catch (OutOfMemory &e) {
+        err = e.what();
+        return -4;
     } catch (HipError &e) {
         err = e.what();
         return -3;
@@ -930,25 +943,36 @@ int fill_sell(const DevCsr &K, int C, int64_t nslices, const SellFill &F, void *
     });
 }
 
+static void fill_pieces(const CsrView &K, int C, const SellFill &F, hipStream_t s, int64_t piece)
+{
+    const int64_t win = 4 * C;   // rows of a sorted window: the pieces end between windows
+    for (int64_t a = 0, b; a < K.n; a = b) {
+        b = std::min(K.n, a + win);
+        while (b < K.n && K.rp[std::min(K.n, b + win)] - K.rp[a] <= piece) b = std::min(K.n, b + win);
+        const int64_t e0 = K.rp[a], m = K.rp[b] - e0;
+        DBuf<int64_t> rp;
+        DBuf<int32_t> ci;
+        DBuf<double> v;
+        up(rp, K.rp + a, b - a + 1, s);
+        up(ci, K.ci + e0, m, s);
+        up(v, K.v + e0, m, s);
+        hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)((b - a + C - 1) / C)), dim3(256), 0, s, K.n, a, e0, rp.p, ci.p,
+                           v.p, C, a / C, F);
+        DCHK(hipGetLastError());
+        DCHK(hipStreamSynchronize(s));
+    }
+}
+
 int fill_sell(const CsrView &K, int C, const SellFill &F, void *stream, std::string &err)
 {
     return guarded(err, [&] {
-        hipStream_t s = (hipStream_t)stream;
-        const int64_t win = 4 * C;   // rows of a sorted window: the pieces end between windows
-        for (int64_t a = 0, b; a < K.n; a = b) {
-            b = std::min(K.n, a + win);
-            while (b < K.n && K.rp[std::min(K.n, b + win)] - K.rp[a] <= FILL_PIECE) b = std::min(K.n, b + win);
-            const int64_t e0 = K.rp[a], m = K.rp[b] - e0;
-            DBuf<int64_t> rp;
-            DBuf<int32_t> ci;
-            DBuf<double> v;
-            up(rp, K.rp + a, b - a + 1, s);
-            up(ci, K.ci + e0, m, s);
-            up(v, K.v + e0, m, s);
-            hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)((b - a + C - 1) / C)), dim3(256), 0, s, K.n, a, e0, rp.p, ci.p,
-                               v.p, C, a / C, F);
-            DCHK(hipGetLastError());
-            DCHK(hipStreamSynchronize(s));
+        for (int64_t piece = FILL_PIECE;; piece /= 64) {   // smaller pieces where memory is short
+            try {
+                return fill_pieces(K, C, F, (hipStream_t)stream, piece);
+            } catch (OutOfMemory &) {
+                if (piece < 64) throw;
+                SetupMemory::trim();
+            }
         }
     });
 }

@@ -75,21 +75,28 @@ void set_err(const std::string &m) { g_err = m; }
         }                                                                                      \
     } while (0)
 
-template <typename T> T *dalloc(size_t n)
+// Device memory; NULL where there is none, even without what a running set-up
+// has idle.
+void *try_alloc(size_t bytes)
 {
     void *p = nullptr;
-    if (n == 0) n = 1;
-    const hipError_t e = hipMalloc(&p, n * sizeof(T));
+    hipError_t e = hipMalloc(&p, bytes);
     if (e != hipSuccess) (void)hipGetLastError();   // told by e: a later check is not to find it
+    if (e == hipErrorOutOfMemory) {
+        amgiga::SetupMemory::trim();
+        e = hipMalloc(&p, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+    }
+    if (e == hipErrorOutOfMemory) return nullptr;
     HIPCHK(e);
-    return (T *)p;
+    return p;
 }
 
-template <typename T> T *dupload(const T *h, size_t n)
+template <typename T> T *dalloc(size_t n)
 {
-    T *d = dalloc<T>(n);
-    if (n) HIPCHK(hipMemcpy(d, h, n * sizeof(T), hipMemcpyHostToDevice));
-    return d;
+    void *p = try_alloc(std::max<size_t>(n, 1) * sizeof(T));
+    if (!p) HIPCHK(hipErrorOutOfMemory);
+    return (T *)p;
 }
 
 inline unsigned nblocks(int64_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
@@ -220,6 +227,7 @@ struct amg_ctx {
     };
     std::vector<std::pair<std::string, double>> tune_log;
     amgiga::DevSetupInfo setup_info;
+    std::vector<amgiga::DevCsr> copies;   // of the level matrices, during set-up (build_device); empty after
     double *sc = nullptr;
     double *hsc = nullptr;     // pinned host copy of the scalar block
     double *hsc_dev = nullptr; // its device address: k_finalize writes the stopping test's scalars there
@@ -237,18 +245,31 @@ struct amg_ctx {
     int64_t prof_launches = 0;
     double prof_ms = 0.0, prof_bytes = 0.0;
 
+    // The copies only make the set-up faster: without them K P is formed on the host
+    // and the images are filled from the host's matrices.
+    void drop_copies()
+    {
+        for (amgiga::DevCsr &d : copies) d = amgiga::DevCsr();
+        amgiga::SetupMemory::trim();
+    }
     template <typename T> T *alloc(size_t k)
     {
-        T *d = dalloc<T>(k);
-        allocs.push_back(d);
-        return d;
+        void *p = try_alloc(std::max<size_t>(k, 1) * sizeof(T));
+        if (!p && !copies.empty()) {
+            drop_copies();
+            p = try_alloc(std::max<size_t>(k, 1) * sizeof(T));
+        }
+        if (!p) HIPCHK(hipErrorOutOfMemory);
+        allocs.push_back(p);
+        return (T *)p;
     }
-    template <typename T> T *upload(const std::vector<T> &h)
+    template <typename T> T *upload(const T *h, size_t k)
     {
-        T *d = dupload(h.data(), h.size());
-        allocs.push_back(d);
+        T *d = alloc<T>(k);
+        if (k) HIPCHK(hipMemcpy(d, h, k * sizeof(T), hipMemcpyHostToDevice));
         return d;
     }
+    template <typename T> T *upload(const std::vector<T> &h) { return upload(h.data(), h.size()); }
     void release(void *p)
     {
         if (!p) return;
@@ -280,9 +301,9 @@ struct amg_ctx {
         A.n = K.n; A.ncols = square ? K.n : ncols; A.nnz = K.nnz(); A.stored = K.nnz(); A.C = 0;
         A.index_bytes = 4.0 * (double)K.nnz() + 8.0 * (double)(K.n + 1);
         A.lpr = mean >= 512.0 ? 64 : mean >= 256.0 ? 32 : mean >= 64.0 ? 16 : 8;
-        A.crp = dupload(K.rp, (size_t)K.n + 1); allocs.push_back(A.crp);
-        A.cci = dupload(K.ci, (size_t)K.nnz()); allocs.push_back(A.cci);
-        A.cv = dupload(K.v, (size_t)K.nnz()); allocs.push_back(A.cv);
+        A.crp = upload(K.rp, (size_t)K.n + 1);
+        A.cci = upload(K.ci, (size_t)K.nnz());
+        A.cv = upload(K.v, (size_t)K.nnz());
         return A;
     }
     // y = acc, f + acc or f - acc over an image (SELL or CSR), FP64, no dots.
@@ -365,8 +386,16 @@ struct amg_ctx {
             int32_t *ulen = S.nshared > 0 ? upload(S.ulen) : nullptr;
             const amgiga::SellFill F{A.soff, A.ibase, A.perm, A.shoff, ulen, A.v64, A.v32, A.d16, A.col0, A.c32, A.gcol};
             std::string err;
-            if (D && D->rp) check_setup(amgiga::fill_sell(*D, C, S.nslices, F, stream, err), err);
-            else check_setup(amgiga::fill_sell(K, C, F, stream, err), err);
+            if (D && D->rp) {
+                check_setup(amgiga::fill_sell(*D, C, S.nslices, F, stream, err), err);
+            } else {
+                int rc = amgiga::fill_sell(K, C, F, stream, err);
+                if (rc == AMG_ERR_OOM) {
+                    drop_copies();
+                    rc = amgiga::fill_sell(K, C, F, stream, err);
+                }
+                check_setup(rc, err);
+            }
             HIPCHK(hipStreamSynchronize(stream));   // before ulen and D go
             release(ulen);
         }
@@ -390,12 +419,17 @@ struct amg_ctx {
         KpProduct p;
         std::string err;
         if (D->rp) {
-            check_setup(amgiga::kp_on_device(*D, host.lev[l + 1].n, lev[l].agg, lev[l].pc64, stream, p.dev, p.host.rp, p.max_gap, err),
-                        err);
-            p.host.n = K.n;
-        } else {
-            p.host = amgiga::kp_product(K, host.lev[l + 1].n, host.lev[l].agg.data(), host.lev[l].pc.data());
+            const int rc = amgiga::kp_on_device(*D, host.lev[l + 1].n, lev[l].agg, lev[l].pc64, stream, p.dev, p.host.rp,
+                                                p.max_gap, err);
+            if (rc != AMG_ERR_OOM) {
+                check_setup(rc, err);
+                p.host.n = K.n;
+                return p;
+            }
+            drop_copies();   // too little memory for the product's work space
+            p = KpProduct();
         }
+        p.host = amgiga::kp_product(K, host.lev[l + 1].n, host.lev[l].agg.data(), host.lev[l].pc.data());
         return p;
     }
     DevMat upload_kp(const KpProduct &p, int C, int l)
@@ -504,7 +538,7 @@ struct amg_ctx {
     // row on the SELL-64 images or 4, 8 or 16 on SELL-(64/lanes) images with
     // 256 or 512 threads per block, timed on the level-0 K P pass and a
     // level-1 pass; the fastest variant's images are then built for every level.
-    void tune_blocks(const CsrView &K0, const std::vector<amgiga::DevCsr> &dev)
+    void tune_blocks(const CsrView &K0)
     {
         blk_alloc();
         const bool f32 = fp32();
@@ -548,13 +582,13 @@ struct amg_ctx {
         tune_log.push_back({"lpr=1 threads=256", best.ms});
         // level-0 K P product, formed once for every candidate image
         KpProduct kp0;
-        if (nlev > 1) kp0 = kp_product(K0, &dev[0], 0);
+        if (nlev > 1) kp0 = kp_product(K0, &copies[0], 0);
         struct Imgs { DevMat a0, a1, kp0; };
         Imgs keep;
         for (int lpr : {4, 8, 16}) {
             Imgs im;
-            if (lvl0) im.a0 = upload_sell(K0, 64 / lpr, true, f32, 0, &dev[0]);
-            if (nlev > 2) im.a1 = upload_sell(amgiga::view(host.lev[1].K), 64 / lpr, !f32, f32, 0, &dev[1]);
+            if (lvl0) im.a0 = upload_sell(K0, 64 / lpr, true, f32, 0, &copies[0]);
+            if (nlev > 2) im.a1 = upload_sell(amgiga::view(host.lev[1].K), 64 / lpr, !f32, f32, 0, &copies[1]);
             if (nlev > 1) im.kp0 = upload_kp(kp0, 64 / lpr, 0);
             lev[0].Ab = im.a0;
             if (nlev > 2) lev[1].Ab = im.a1;
@@ -585,9 +619,9 @@ struct amg_ctx {
             if (nlev > 2) lev[1].Ab = keep.a1;
             if (nlev > 1) lev[0].KPb = keep.kp0;
             for (int l = 2; l < nlev - 1; l++)
-                lev[l].Ab = upload_sell(amgiga::view(host.lev[l].K), 64 / best.lpr, !f32, f32, 0, &dev[l]);
+                lev[l].Ab = upload_sell(amgiga::view(host.lev[l].K), 64 / best.lpr, !f32, f32, 0, &copies[l]);
             for (int l = 1; l < nlev - 1; l++) {
-                lev[l].KPb = upload_kp(kp_product(amgiga::view(host.lev[l].K), &dev[l], l), 64 / best.lpr, l);
+                lev[l].KPb = upload_kp(kp_product(amgiga::view(host.lev[l].K), &copies[l], l), 64 / best.lpr, l);
             }
             blk_img_lpr = best.lpr;
         }
@@ -1467,7 +1501,7 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
     // filled from the host's matrices piece by piece.  3D p=3 h=1/32 (10.5M
     // entries), set-up and first V-cycle: 178 ms with the products and images
     // made on the host, 96 ms so (all else equal).
-    std::vector<amgiga::DevCsr> dev = std::move(c->setup_info.levels);
+    c->copies = std::move(c->setup_info.levels);
     // Images of a GB and more go to memory that the hierarchy's blocks have left:
     // laid beside them, the matrix passes of 3D p=3 h=1/128 (707M entries) were
     // 1 to 4% slower (V-cycle 2143 us against 2077).  Below, the blocks serve
@@ -1481,8 +1515,11 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
         HIPCHK(hipMemGetInfo(&mem_free, &mem_total));
     }
     const bool copies = K0.nnz() < (int64_t(1) << 31) && (double)mem_free > 100.0 * (double)K0.nnz();
-    if (!copies) dev.clear();
-    dev.resize(c->nlev);
+    if (!copies) {
+        c->copies.clear();
+        amgiga::SetupMemory::trim();   // their blocks
+    }
+    c->copies.resize(c->nlev);
     for (int l = 0; l < c->nlev; l++) {
         auto &hl = H.lev[l];
         Level &L = c->lev[l];
@@ -1495,8 +1532,12 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
             if (c->prm.smoother == 2 && l > 0) L.A = c->upload_image(K);
             else {
                 std::string err;
-                if (copies && !dev[l].rp && !c->general_vcycle()) c->check_setup(amgiga::csr_to_device(K, c->stream, dev[l], err), err);
-                L.A = c->upload_sell(K, SLICE, (l == 0) || !fp32, fp32, 0, &dev[l]);
+                amgiga::DevCsr &D = c->copies[l];
+                if (copies && !D.rp && !c->general_vcycle()) {
+                    const int rc = amgiga::csr_to_device(K, c->stream, D, err);
+                    if (rc != AMG_ERR_OOM) c->check_setup(rc, err);
+                }
+                L.A = c->upload_sell(K, SLICE, (l == 0) || !fp32, fp32, 0, &D);
             }
         }
         L.invd64 = c->upload(hl.invd);
@@ -1518,7 +1559,7 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
                 }
             } else {
                 CsrView K = l == 0 ? K0 : amgiga::view(hl.K);
-                L.KP = c->upload_kp(c->kp_product(K, &dev[l], l), SLICE, l);
+                L.KP = c->upload_kp(c->kp_product(K, &c->copies[l], l), SLICE, l);
             }
             int64_t nc = H.lev[l + 1].n;
             L.mw = hl.max_members;
@@ -1607,9 +1648,9 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
     c->tune_xwin();
     if (c->prm.nrhs > 1) {
         amgiga::SetupMemory::trim();
-        c->tune_blocks(K0, dev);
+        c->tune_blocks(K0);
     }
-    dev.clear();
+    c->copies.clear();
     HIPCHK(hipStreamSynchronize(c->stream));
     return AMG_OK;
 }

@@ -94,3 +94,29 @@ def test_a_fault_is_named_without_memory_for_the_check(scarce):
         messages.append(str(e.value))
     assert messages[0] == messages[1]
     other()
+
+
+# 20 bytes an entry: less than the copies of the level matrices (12 bytes for
+# each of 3.7 entries), and far less than the products' work space
+@pytest.mark.parametrize("spare", [20, 30, 50, 70])
+@pytest.mark.parametrize("device", [0, 1])
+def test_copies_and_idle_blocks_go_before_the_images_fail(scarce, spare, device):
+    amg, arrays, x, z, size, card, _ = scarce
+    print(f"case scarce memory spare={spare} B/entry device={device}", flush=True)
+    card.leave(size + spare * len(arrays[1]))
+    ctx = amg.Context(*arrays, setup_device=device)
+    # the products of host and device have the same bits, and so the images
+    assert torch.equal(ctx.vcycle(x), z)
+    ctx.close()
+
+
+@pytest.mark.parametrize("device", [0, 1])
+def test_images_without_memory_are_out_of_memory(scarce, device):
+    """The images do not fit: AMG_ERR_OOM, with the products on either side."""
+    amg, arrays, x, z, size, card, _ = scarce
+    print(f"case no memory device={device}", flush=True)
+    for share in (0.6, 0.75, 0.9):
+        card.leave(share * size)
+        with pytest.raises(amg.AmgError) as e:
+            amg.Context(*arrays, setup_device=device)
+        assert e.value.status == -4, (share, str(e.value))
