@@ -325,7 +325,8 @@ const char *amg_last_error(void);
  *   would leave x take the gathers.  amg_setup times both walks on the level-0
  *   residual and keeps the faster (the gathers gain more from a faster memory;
  *   the two differ by a few percent either way).  Images of fewer than 1,200
- *   slices take several wavefronts per slice and the gathers either way.
+ *   slices start without: their passes then take several wavefronts per slice
+ *   and the gathers; with the option on, one wavefront and the windows.
  *   Bitwise the same results.
  * amg_get_option returns the current value of an option. */
 typedef enum {

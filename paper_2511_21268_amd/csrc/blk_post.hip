@@ -10,7 +10,7 @@ template <typename VT, typename OT, int NDOT>
 unsigned blk_post(const BlkCfg &c, const DevMat &A, bool multi, const PostVecs<VT, OT> &v)
 {
     if constexpr (NDOT == 0) {
-        if (multi && A.split > 1) {
+        if (multi && A.waves() > 1) {
 #define LAUNCH(IT, LPR)                                                                                           \
     hipLaunchKernelGGL((k_splitb_post<VT, OT, IT, LPR>), dim3((unsigned)A.nslices), dim3(64 * SPLITB_WAVES), 0,   \
                        c.stream, A.sv<VT, IT>(), v.e, v.u, v.r, v.invd, v.agg, v.pc, v.y)

@@ -7,7 +7,7 @@ namespace amgk {
 BLK_DECL(blk_rows)
 {
     if constexpr (NDOT == 0) {
-        if (A.split > 1) {
+        if (A.waves() > 1) {
 #define LAUNCH(IT, LPR)                                                                                           \
     hipLaunchKernelGGL((k_splitb<VT, FT, OT, IT, EPI, LPR>), dim3((unsigned)A.nslices), dim3(64 * SPLITB_WAVES), 0, \
                        c.stream, A.sv<VT, IT>(), v.x, v.f, v.invd, v.y, v.coef)

@@ -15,7 +15,7 @@ struct DevMat {
     // windows shared by the four slices of a block (batched stencil images)
     int32_t *wgtab = nullptr, *wgst = nullptr;
     int wg_sigma = 0;
-    int split = 1;  // wavefronts per slice of the single-vector passes (split_waves)
+    int split = 1;  // wavefronts per slice by the rule (split_waves, or split_waves_blk)
     int xwin = 0;   // single-vector K passes through x windows (shared-offset images with run tables)
     double wg_ratio = 0.0;   // rows the shared windows copy / rows per-wave windows copy
     uint16_t *d16 = nullptr;
@@ -28,6 +28,8 @@ struct DevMat {
     int32_t *cci = nullptr;
     double *cv = nullptr;
     bool built() const { return soff || crp; }
+    // wavefronts per slice of its passes: the windows are walked by one
+    int waves() const { return xwin ? 1 : split; }
     template <typename VT> const VT *val() const;
     template <typename IT> const IT *idx() const;
     template <typename VT, typename IT> Sell<VT, IT> sv() const

@@ -357,7 +357,7 @@ struct amg_ctx {
         if (!S.shoff.empty()) {
             A.shoff = upload(S.shoff);
             A.shrun = upload(S.shrun);
-            A.xwin = C == SLICE && S.nshared > 0 ? 1 : 0;
+            A.xwin = C == SLICE && S.nshared > 0 && A.split == 1 ? 1 : 0;
             if (C == SLICE && S.nshared > 0) {
                 // the block kernels' windows shared by a block's slices
                 amgiga::WgStages W;
@@ -483,7 +483,7 @@ struct amg_ctx {
     void tune_xwin()
     {
         DevMat &A = lev[0].A;
-        if (!A.xwin || !A.v64 || A.split > 1) return;   // the passes of a split image gather
+        if (!A.xwin || !A.v64) return;
         for (double *v : {p, r})
             hipLaunchKernelGGL((k_fill<double>), dim3(vgrid(n)), dim3(256), 0, stream, n, 1.0, v);
         HIPCHK(hipGetLastError());
@@ -790,7 +790,7 @@ struct amg_ctx {
     void launch_sell(const DevMat &A, unsigned nb, const VT *x, const FT *f, const VT *invd, OT *y,
                      const double *g0, const double *g1, VT coef)
     {
-        if (A.split > 1)
+        if (A.waves() > 1)
             split_pass<VT, FT, OT, EPI, NDOT>(stream, A, {x, f, invd, y, g0, g1, coef}, partial);
         else if (A.idx16)
             hipLaunchKernelGGL((k_sell<VT, FT, OT, uint16_t, EPI, NDOT>), dim3(nb), dim3(256), 0, stream,
@@ -804,7 +804,7 @@ struct amg_ctx {
     // wavefront of whole blocks, or one per slice
     unsigned dot_blocks(const DevMat &A) const
     {
-        return A.split > 1 ? (unsigned)A.nslices : (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES) * SELL_WAVES;
+        return A.waves() > 1 ? (unsigned)A.nslices : (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES) * SELL_WAVES;
     }
     unsigned sell_blocks(int l) const { return (unsigned)((lev[l].A.nslices + SELL_WAVES - 1) / SELL_WAVES); }
     // Fused prolongation + first post-smoothing sweep on level l (needs K P).
@@ -818,7 +818,7 @@ struct amg_ctx {
 #define POST_LAUNCH(IT, ND)                                                                                   \
     hipLaunchKernelGGL((k_sell_post<VT, OT, IT, ND>), dim3(nb), dim3(256), 0, stream, A.sv<VT, IT>(), e, u,     \
                        (const VT *)L.r, L.invd<VT>(), L.agg, L.pc<VT>(), y, g0, g1, partial)
-        if (A.split > 1) {
+        if (A.waves() > 1) {
             const PostVecs<VT, OT> v{e, u, (const VT *)L.r, L.invd<VT>(), L.agg, L.pc<VT>(), y, g0};
             if constexpr (std::is_same_v<OT, double>) {
                 if (ndot) split_post<VT, OT, 1>(stream, A, v, partial);
@@ -852,7 +852,7 @@ struct amg_ctx {
         const DevMat &A = L.KP;
         unsigned nb = (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES);
         if (l == 0) prof_begin();
-        if (A.split > 1)
+        if (A.waves() > 1)
             split_post_res<VT>(stream, A, e, u, (VT *)L.r, L.agg, L.pc<VT>(), y);
         else if (A.idx16)
             hipLaunchKernelGGL((k_sell_post_res<VT, uint16_t>), dim3(nb), dim3(256), 0, stream, A.sv<VT, uint16_t>(),
@@ -1094,7 +1094,7 @@ struct amg_ctx {
         }
         unsigned nb = (unsigned)((A.nslices + SELL_WAVES - 1) / SELL_WAVES);
         if (l == 0) prof_begin();
-        if (A.split > 1)
+        if (A.waves() > 1)
             split_cheb<MODE>(stream, A, x, f, r, L.invd64, u, dn, a, b, first);
         else if (A.idx16)
             hipLaunchKernelGGL((k_sell_cheb<uint16_t, MODE>), dim3(nb), dim3(256), 0, stream,

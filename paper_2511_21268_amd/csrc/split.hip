@@ -7,7 +7,7 @@ namespace amgk {
 // KER<types..., W> for the image's index type and wavefronts per slice
 #define SPLIT_W(KER, IT, ...)                                                                                     \
     do {                                                                                                          \
-        if (A.split == 4) KER(IT, 4, __VA_ARGS__);                                                                \
+        if (A.waves() == 4) KER(IT, 4, __VA_ARGS__);                                                                \
         else KER(IT, 8, __VA_ARGS__);                                                                             \
     } while (0)
 #define SPLIT(KER, ...)                                \
