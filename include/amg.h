@@ -328,6 +328,10 @@ const char *amg_last_error(void);
  *   slices start without: their passes then take several wavefronts per slice
  *   and the gathers; with the option on, one wavefront and the windows.
  *   Bitwise the same results.
+ * AMG_OPT_SPLIT (default on): the matrix passes over images of few slices take
+ *   several wavefronts per slice (single vector: below 1,200 slices, 4 or 8;
+ *   lanes-per-row images of the batched solve: below 1,024, 4).  Off: one
+ *   everywhere.  Bitwise the same results.
  * amg_get_option returns the current value of an option. */
 typedef enum {
     AMG_OPT_GRAPH = 1,
@@ -335,7 +339,8 @@ typedef enum {
     AMG_OPT_BLOCK_WINDOW = 3,
     AMG_OPT_TAIL = 4,
     AMG_OPT_WINDOW_SHARE = 5,
-    AMG_OPT_X_WINDOW = 6
+    AMG_OPT_X_WINDOW = 6,
+    AMG_OPT_SPLIT = 7
 } amg_option;
 amg_status amg_set_option(amg_ctx *c, int option, int value);
 amg_status amg_get_option(const amg_ctx *c, int option, int *value);

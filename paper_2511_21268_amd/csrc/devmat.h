@@ -16,6 +16,7 @@ struct DevMat {
     int32_t *wgtab = nullptr, *wgst = nullptr;
     int wg_sigma = 0;
     int split = 1;  // wavefronts per slice by the rule (split_waves, or split_waves_blk)
+    int one_wave = 0;   // AMG_OPT_SPLIT off
     int xwin = 0;   // single-vector K passes through x windows (shared-offset images with run tables)
     double wg_ratio = 0.0;   // rows the shared windows copy / rows per-wave windows copy
     uint16_t *d16 = nullptr;
@@ -29,7 +30,7 @@ struct DevMat {
     double *cv = nullptr;
     bool built() const { return soff || crp; }
     // wavefronts per slice of its passes: the windows are walked by one
-    int waves() const { return xwin ? 1 : split; }
+    int waves() const { return xwin || one_wave ? 1 : split; }
     template <typename VT> const VT *val() const;
     template <typename IT> const IT *idx() const;
     template <typename VT, typename IT> Sell<VT, IT> sv() const

@@ -169,6 +169,7 @@ struct amg_ctx {
     // longer than the per-level launches it replaces, 9 us per V-cycle single
     // vector and 110 us per 16-column V-cycle)
     int use_tail = 0, tail_start = -1;
+    int use_split = 1;   // several wavefronts per slice in images of few slices
     void *tail_dev = nullptr, *tail_dev_blk = nullptr;
     hipStream_t gstream = nullptr;
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
@@ -2210,6 +2211,12 @@ amg_status amg_set_option(amg_ctx *c, int option, int value)
         }
         c->drop_graphs();
         break;
+    case AMG_OPT_SPLIT:
+        for (Level &L : c->lev)
+            for (DevMat *M : {&L.A, &L.Ab, &L.KP, &L.KPb, &L.Pm, &L.Rm}) M->one_wave = value ? 0 : 1;
+        c->use_split = value ? 1 : 0;
+        c->drop_graphs();
+        break;
     case AMG_OPT_WINDOW_SHARE:
         if (value < 0 || value > 3) {
             set_err("AMG_OPT_WINDOW_SHARE takes a mask: 1 FP64-value passes, 2 FP32-value passes");
@@ -2250,6 +2257,7 @@ amg_status amg_get_option(const amg_ctx *c, int option, int *value)
     case AMG_OPT_WINDOW_SHARE: *value = c->lev[0].A.wgtab ? c->blk_share : 0; break;
     case AMG_OPT_X_WINDOW: *value = c->nlev > 0 ? c->lev[0].A.xwin : 0; break;
     case AMG_OPT_BLOCK_WINDOW: *value = c->blk_win; break;
+    case AMG_OPT_SPLIT: *value = c->use_split; break;
     default: set_err("unknown option"); return AMG_ERR_ARG;
     }
     return AMG_OK;
