@@ -1499,15 +1499,19 @@ static amg_status build_device(amg_ctx *c, const CsrView &K0)
     // images filled.  They, the products' work space and the images take up to
     // 100 bytes an entry of K; with less memory than that, or entries past the
     // 32-bit indices of the products, the host forms K P and the images are
-    // filled from the host's matrices piece by piece.  3D p=3 h=1/32 (10.5M
-    // entries), set-up and first V-cycle: 178 ms with the products and images
-    // made on the host, 96 ms so (all else equal).
+    // filled from the host's matrices piece by piece; so they are where the
+    // estimate proves too small (rows of very different lengths pad an image to
+    // several times its entries): an allocation that fails drops the copies.
+    // 3D p=3 h=1/32 (10.5M entries), set-up and first V-cycle: 178 ms with the
+    // products and images made on the host, 96 ms so (all else equal).
     c->copies = std::move(c->setup_info.levels);
-    // Images of a GB and more go to memory that the hierarchy's blocks have left:
-    // laid beside them, the matrix passes of 3D p=3 h=1/128 (707M entries) were
-    // 1 to 4% slower (V-cycle 2143 us against 2077).  Below, the blocks serve
-    // on: 88M entries solve in the same time either way, and a set-up of 10.5M
-    // takes 6% longer without them.
+    // After a device set-up of a large matrix the idle blocks go back before the
+    // images are laid (a host set-up has none yet): 3D p=3 h=1/128 (707M
+    // entries) V-cycle 2077 us so, 2143 with the blocks kept; 88M entries
+    // solve in the same time either way, and a set-up of 10.5M takes 6% longer
+    // without its blocks.  The line lies between the two sizes; why the place of
+    // the images matters is not known (copies of the matrices beside them, as a
+    // host set-up has, made no such difference).
     if (K0.nnz() >= (int64_t(1) << 27)) amgiga::SetupMemory::trim();
     size_t mem_free = 0, mem_total = 0;
     HIPCHK(hipMemGetInfo(&mem_free, &mem_total));

@@ -16,11 +16,13 @@
 // cycles (T = 32: 32 dependent FMAs, an LDS write and read, the barrier),
 // 2 us for 330 entries, below what the loads took.
 //
-// Measured, one wave per slice against this: SpMV of 36k rows of 729 entries
-// 92 -> 44 us (2.3 -> 4.7 TB/s); FP32 residual of 33k rows of 1,331 entries
+// Measured, kernel times, one wave per slice against this: SpMV of 36k rows of
+// 729 entries 92 -> 44 us (2.3 -> 4.7 TB/s); FP32 residual of 33k rows of 1,331 entries
 // 98 -> 52 us, of its coarse levels (129, 33, 9 slices) 67, 39, 22 -> 29, 16, 9
-// us; the V-cycle of that system 365 -> 184 us.  Now each pass is bound by the
-// loads' latency at its start, the turns, and from about 500 slices by HBM.
+// us; the V-cycle of that system 365 -> 180 us.  Now a pass is bound by the
+// loads in flight: in FP64 near HBM's rate from about 500 slices on, in FP32 half
+// as many bytes a wave (2.6 TB/s at 512 slices, of whose 52 us the turns are 9),
+// with fewer slices by their latency.
 //
 // After the last turn wave 0 runs the epilogue of k_sell on the sums, one lane
 // per row, dot partials included; it asked for the epilogue's operands first.
