@@ -35,8 +35,8 @@ TRAFFIC_SOURCE = "profiles/k_sell_c4_fp64_pmc.md"
 MEASURED_TRAFFIC = {
     # (workload, SHA-256 of kernels.h + solver.hip, x windows on): bytes per
     # launch, SpMV and residual launches of one solve
-    ("c4", "9c40f6d0073b9ed475e3afc8f6f5e9f1c5137286a905a09e4dc79c308bb8d2ef", 1): 6629786832,
-    ("c4", "9c40f6d0073b9ed475e3afc8f6f5e9f1c5137286a905a09e4dc79c308bb8d2ef", 0): 5936292790,
+    ("c4", "67f227e8e5095a5ee1504dc9425827bd03c5247682fa6b699dea15495b6cf860", 1): 6656403877,
+    ("c4", "67f227e8e5095a5ee1504dc9425827bd03c5247682fa6b699dea15495b6cf860", 0): 5936679945,
 }
 
 

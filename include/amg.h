@@ -424,7 +424,7 @@ amg_status amg_iga_cube(int p, int n, int64_t *row_ptr, int32_t *col, double *va
 #define AMG_MLP_NPARAM 4996
 #define AMG_MLP_NFEAT 8
 #define AMG_MLP_NACT 128     /* stored activations per sample (h1, h2)        */
-#define AMG_MLP_NDEL 132     /* stored deltas per sample (dy, dh2, dh1)        */
+#define AMG_MLP_NDEL 132     /* workspace floats per sample of the gradient    */
 
 /* Features of level `level` (host output, AMG_MLP_NFEAT floats), all
  * independent of the problem size: log10(nnz/n)/3, (longest row)/(nnz/n) - 1,
