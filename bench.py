@@ -35,8 +35,8 @@ TRAFFIC_SOURCE = "profiles/k_sell_c4_fp64_pmc.md"
 MEASURED_TRAFFIC = {
     # (workload, SHA-256 of kernels.h + solver.hip, x windows on): bytes per
     # launch, SpMV and residual launches of one solve
-    ("c4", "67f227e8e5095a5ee1504dc9425827bd03c5247682fa6b699dea15495b6cf860", 1): 6656403877,
-    ("c4", "67f227e8e5095a5ee1504dc9425827bd03c5247682fa6b699dea15495b6cf860", 0): 5936679945,
+    ("c4", "28aa4490a59b44603f8b6dde6ca3df07cfe1f1930cad3cdc5ac57bfc6aba6e48", 1): 6656601300,
+    ("c4", "28aa4490a59b44603f8b6dde6ca3df07cfe1f1930cad3cdc5ac57bfc6aba6e48", 0): 5936689696,
 }
 
 

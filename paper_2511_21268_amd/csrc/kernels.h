@@ -687,34 +687,50 @@ __host__ __device__ inline int coarse_rows(int n) { return COARSE_SEGS * coarse_
 // LOWER: sum_{k<=i} M_ki f_k, else sum_{k>=i} M_ki f_k; the other half of M holds
 // zeros, so every lane takes the groups of 8 terms that one of them needs (lanes
 // without a term switched off instead: 5.4 us against 5.1 at n = 67, 821 against
-// 780 at n = 2,000).  f in LDS, zeros from n on.  Valid in all lanes of a row.
-template <bool LOWER>
-__device__ __forceinline__ double coarse_row16(int n, int ld, const double *__restrict__ M, const double *f, int r0)
-{
-    constexpr int TG = 2;  // groups in flight
-    const int lane = threadIdx.x & 63, len = coarse_len(n), k0 = (lane >> 4) * len;
-    const int ga = LOWER ? 0 : max(0, r0 - (COARSE_SEGS - 1) * len) / 8, gb = LOWER ? min(len, r0 + 16) / 8 : len / 8;
-    double s = 0.0;
-    for (int g = ga; g < gb; g += TG) {
-        double m[8 * TG];
-#pragma unroll
-        for (int h = 0; h < TG; h++)
-            if (g + h < gb)
-#pragma unroll
-                for (int t = 0; t < 8; t++)
-                    m[8 * h + t] = M[(unsigned)(k0 + 8 * (g + h) + t) * (unsigned)ld + (unsigned)(r0 + (lane & 15))];
-#pragma unroll
-        for (int h = 0; h < TG; h++)
-            if (g + h < gb)
-#pragma unroll
-                for (int t = 0; t < 8; t++) s = fma(m[8 * h + t], f[k0 + 8 * (g + h) + t], s);
+// 780 at n = 2,000, loads after the vector in both).  f in LDS, zeros from n on.  Valid in all lanes of a row.
+template <bool LOWER> struct CoarseRow16 {
+    static constexpr int TG = 2;   // groups in flight
+    const double *__restrict__ M;
+    unsigned at, ld;
+    int k0, ga, gb;
+    double m[8 * TG];
+    // asks for the first terms (none for rows past the last)
+    __device__ __forceinline__ CoarseRow16(int n, int ld_, const double *__restrict__ M_, int r0) : M(M_), ld(ld_)
+    {
+        const int lane = threadIdx.x & 63, len = coarse_len(n);
+        k0 = (lane >> 4) * len;
+        at = (unsigned)(r0 + (lane & 15));
+        ga = LOWER ? 0 : max(0, r0 - (COARSE_SEGS - 1) * len) / 8;
+        gb = r0 >= n ? ga : LOWER ? min(len, r0 + 16) / 8 : len / 8;
+        load(ga);
     }
-    s += __shfl_xor(s, 16, 64);
-    return s + __shfl_xor(s, 32, 64);
-}
+    __device__ __forceinline__ void load(int g)
+    {
+#pragma unroll
+        for (int h = 0; h < TG; h++)
+            if (g + h < gb)
+#pragma unroll
+                for (int t = 0; t < 8; t++) m[8 * h + t] = M[(unsigned)(k0 + 8 * (g + h) + t) * ld + at];
+    }
+    __device__ __forceinline__ double sum(const double *f)
+    {
+        double s = 0.0;
+        for (int g = ga; g < gb; g += TG) {
+            if (g > ga) load(g);
+#pragma unroll
+            for (int h = 0; h < TG; h++)
+                if (g + h < gb)
+#pragma unroll
+                    for (int t = 0; t < 8; t++) s = fma(m[8 * h + t], f[k0 + 8 * (g + h) + t], s);
+        }
+        s += __shfl_xor(s, 16, 64);
+        return s + __shfl_xor(s, 32, 64);
+    }
+};
 // Both products by one block: fill(i) gives f_i, put(i, x) takes each result
 // once.  Bound by the latency of each product's loads (a wave has 16 in flight;
-// 24 gain nothing): n = 67 5.1 us, 281 8.8 us; K^{-1} f took 3.5 and 6.1 us.
+// 24 gain nothing), the first of which are asked for before the product's vector
+// is there: n = 67 4.9 us (after it 5.4), 281 8.0 us (8.8); K^{-1} f took 3.9 and 6.5.
 template <int THREADS, typename Fill, typename Put>
 __device__ __forceinline__ void coarse_apply(int n, int ld, const double *__restrict__ Linv,
                                              const double *__restrict__ LinvT, Fill fill, Put put)
@@ -722,18 +738,22 @@ __device__ __forceinline__ void coarse_apply(int n, int ld, const double *__rest
     __shared__ double fs[COARSE_MAXN], ys[COARSE_MAXN];
     const int first = 16 * wave_id(), step = THREADS / 4;
     const int lane = threadIdx.x & 63;
+    CoarseRow16<true> lower(n, ld, LinvT, first);
     for (int i = threadIdx.x; i < coarse_rows(n); i += THREADS) {
         fs[i] = i < n ? fill(i) : 0.0;
         if (i >= n) ys[i] = 0.0;
     }
-    __syncthreads();
+    lds_barrier();
     for (int r0 = first; r0 < n; r0 += step) {
-        const double y = coarse_row16<true>(n, ld, LinvT, fs, r0);
+        if (r0 > first) lower = CoarseRow16<true>(n, ld, LinvT, r0);
+        const double y = lower.sum(fs);
         if (lane < 16 && r0 + lane < n) ys[r0 + lane] = y;
     }
-    __syncthreads();
+    CoarseRow16<false> upper(n, ld, Linv, first);
+    lds_barrier();
     for (int r0 = first; r0 < n; r0 += step) {
-        const double x = coarse_row16<false>(n, ld, Linv, ys, r0);
+        if (r0 > first) upper = CoarseRow16<false>(n, ld, Linv, r0);
+        const double x = upper.sum(ys);
         if (lane < 16 && r0 + lane < n) put(r0 + lane, x);
     }
 }
